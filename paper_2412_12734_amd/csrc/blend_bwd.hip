@@ -9,11 +9,10 @@
 //   uv branch: du += dq u, dv += dq v; low-pass branch: d(dx, dy) += dq 2 (dx, dy) / (2 var),
 //   (u, v) = (rho0, rho1) / rho2 -> d rho -> d H (7 entries) and d(dx, dy) -> d c2 = -d(dx, dy).
 //
-// A lane owns PIX vertically adjacent pixels (the launch uses PIX = 1: waves of 8 x 8 pixels).
-// Per splat, a lane first adds up its pixels' contributions; the ten per-splat scalars are
-// then summed over the wave by a transposing reduction (permlane swaps across the wave's
-// halves and row pairs, then a DPP butterfly inside each row) that leaves each total in one
-// lane, which adds it to the splat's LDS slot. Texel gradients are grouped by grid cell (with
+// A lane owns one pixel (waves of 8 x 8 pixels). Per splat, twelve sums over the wave are taken
+// by a transposing reduction (permlane swaps across the wave's halves and row pairs, then a DPP
+// butterfly inside each row) that leaves each total in one lane, which adds it to the splat's
+// LDS slot; the ten record gradients are formed from them once per batch. Texel gradients are grouped by grid cell (with
 // sigma = 0.5 the grid covers only the splat's core, so most blended pixels are border-clamped
 // and share a few cells); each group's four corners and three channels are reduced the same
 // way, one group after another until every pixel's cell has been taken (a step that blended
@@ -28,49 +27,55 @@ namespace gbb {
 
 namespace {
 
-// Per-pixel backward state and the outputs of one (pixel, splat) step.
+// Sums over pixels that the backward keeps per staged splat in LDS. With (dx, dy) a pixel's
+// offset from the projected centre and dr the adjoint of rho: dr0 (dx, dy), dr1 (dx, dy),
+// dr2 (dx, dy), dr2, dr0, dr1, dq_lp (dx, dy) and the opacity's adjoint. The ten record
+// gradients follow from them once per batch (record_gradient): the part of d c2 that comes
+// through rho is -H^T dr with H constant over the splat, so that summing dr0 and dr1 (two more
+// values in the reduction) replaces six multiply-adds of every pixel.
+constexpr int kSums = 12;
+
+// Per-pixel backward state and the outputs of one (pixel, splat) step. Only the colour's
+// component along the pixel's adjoint g matters (d alpha = g . (col T - S / (1 - alpha))), so
+// the colour behind the splat is carried as the scalar Sg = g . S.
 struct PixState {
-  float T, S0, S1, S2, g0, g1, g2;
+  float T, Sg, g0, g1, g2;
   uint32_t last;
 };
 
 struct PixOut {
-  bool act;
-  int k00;                       // cell (first corner) in the [N][N] gradient grid
-  float w[4];                    // corner weights (00, 01, 10, 11)
-  float dc0, dc1, dc2;           // colour adjoint alpha T g
-  float gh[7], gc2x, gc2y, go;   // record gradients
+  int cell;         // first corner's index in the LDS texel layout (TexLayout)
+  float w[4];       // alpha T times the corner weights (00, 01, 10, 11)
+  float sum[kSums];
 };
 
 // One (pixel, splat) step of the reverse walk. `act`: the pixel blended this splat. A lane
-// that did not runs the same arithmetic with a zero weight and adjoint and a unit
-// transmittance factor, so that all of its outputs are zero and its state is unchanged
-// without a branch or zeroed outputs; its u, v and 1 / rho2 are replaced by 0 (they are
-// infinite where rho2 = 0). Its cell and corner weights are left unspecified.
+// that did not runs the same arithmetic with a zero opacity, so that its weights, adjoints and
+// state come out unchanged or zero without a branch; its u, v and 1 / rho2 are replaced by 0
+// (they are infinite where rho2 = 0). Its cell is left unspecified.
+// The four corner texels are multiplied by g first (12 multiply-adds) and interpolated as
+// scalars: the value and both fractional-position adjoints then cost 9 operations instead of 33
+// over three channels. Together with the scalar Sg this took the 8 x 8 kernel from 287 to about
+// 245 VALU instructions per wave step.
 // MIXED: gc holds the grid-coordinate constants of the splat's grid (grid_consts).
 template <int N, bool MIXED = false>
 __device__ __forceinline__ void pixel_step(const StagedGeo& g, const float4* tex,
                                            const PixelEval& e, bool act, PixState& ps,
                                            const BlendParams& p, PixOut& o,
                                            float4 gc = make_float4(0.f, 0.f, 0.f, 0.f)) {
-  o.act = act;
   const float inv = act ? e.inv : 0.f;
   const float u = act ? e.u : 0.f, v = act ? e.v : 0.f;
-  const float inv1m = act ? __builtin_amdgcn_rcpf(1.0f - e.alpha) : 1.0f;
+  const float alpha = act ? e.alpha : 0.f;
+  const float inv1m = __builtin_amdgcn_rcpf(1.0f - alpha);
   ps.T = ps.T * inv1m;  // transmittance in front of this splat
-  float c0, c1, c2;
+  const float wgt = alpha * ps.T;
+  float col;  // g . colour
   float du = 0.f, dv = 0.f;
-  const float wgt = act ? e.alpha * ps.T : 0.f;
-  o.dc0 = wgt * ps.g0;
-  o.dc1 = wgt * ps.g1;
-  o.dc2 = wgt * ps.g2;
   if constexpr (N == 1) {
     const float4 t = tex[0];
-    c0 = t.x;
-    c1 = t.y;
-    c2 = t.z;
-    o.k00 = 0;
-    o.w[0] = 1.f;
+    col = ps.g0 * t.x + ps.g1 * t.y + ps.g2 * t.z;
+    o.cell = 0;
+    o.w[0] = wgt;
     o.w[1] = o.w[2] = o.w[3] = 0.f;
   } else {
     int iu, iv;
@@ -82,57 +87,68 @@ __device__ __forceinline__ void pixel_step(const StagedGeo& g, const float4* tex
       grid_coord<N>(u, p, iu, fu);
       grid_coord<N>(v, p, iv, fv);
     }
-    o.k00 = iu * N + iv;
-    const int l00 = TexLayout<N>::at(iu, iv), kr = TexLayout<N>::kRow;
-    const float4 t00 = tex[l00], t01 = tex[l00 + 1], t10 = tex[l00 + kr], t11 = tex[l00 + kr + 1];
-    const float a0 = t00.x + fv * (t01.x - t00.x), b0_ = t10.x + fv * (t11.x - t10.x);
-    const float a1 = t00.y + fv * (t01.y - t00.y), b1 = t10.y + fv * (t11.y - t10.y);
-    const float a2 = t00.z + fv * (t01.z - t00.z), b2 = t10.z + fv * (t11.z - t10.z);
-    c0 = a0 + fu * (b0_ - a0);
-    c1 = a1 + fu * (b1 - a1);
-    c2 = a2 + fu * (b2 - a2);
-    o.w[0] = (1.f - fu) * (1.f - fv);
-    o.w[1] = (1.f - fu) * fv;
-    o.w[2] = fu * (1.f - fv);
-    o.w[3] = fu * fv;
+    const int kr = TexLayout<N>::kRow;
+    o.cell = TexLayout<N>::at(iu, iv);
+    const float4 *t = tex + o.cell;
+    const float4 t00 = t[0], t01 = t[1], t10 = t[kr], t11 = t[kr + 1];
+    const float q00 = ps.g0 * t00.x + ps.g1 * t00.y + ps.g2 * t00.z;
+    const float q01 = ps.g0 * t01.x + ps.g1 * t01.y + ps.g2 * t01.z;
+    const float q10 = ps.g0 * t10.x + ps.g1 * t10.y + ps.g2 * t10.z;
+    const float q11 = ps.g0 * t11.x + ps.g1 * t11.y + ps.g2 * t11.z;
+    const float d0 = q01 - q00, d1 = q11 - q10;
+    const float a = q00 + fv * d0, d = (q10 + fv * d1) - a;
+    col = a + fu * d;
     // fractional-position adjoints (Alg. 2), zero where the coordinate is clamped
-    const float dfu = o.dc0 * (b0_ - a0) + o.dc1 * (b1 - a1) + o.dc2 * (b2 - a2);
-    const float fv0 = (t01.x - t00.x) * (1.f - fu) + (t11.x - t10.x) * fu;
-    const float fv1 = (t01.y - t00.y) * (1.f - fu) + (t11.y - t10.y) * fu;
-    const float fv2 = (t01.z - t00.z) * (1.f - fu) + (t11.z - t10.z) * fu;
-    const float dfv = o.dc0 * fv0 + o.dc1 * fv1 + o.dc2 * fv2;
-    const float tsc = MIXED ? gc.x : p.tex_scale;
-    du = fabsf(u) < p.sigma ? tsc * dfu : 0.f;  // (-sigma, sigma): one compare with |u|
-    dv = fabsf(v) < p.sigma ? tsc * dfv : 0.f;
+    const float wsc = wgt * (MIXED ? gc.x : p.tex_scale);
+    du = fabsf(u) < p.sigma ? wsc * d : 0.f;  // (-sigma, sigma): one compare with |u|
+    dv = fabsf(v) < p.sigma ? wsc * (d0 + fu * (d1 - d0)) : 0.f;
+    const float w1 = wgt * fu, w0 = wgt - w1;
+    o.w[3] = w1 * fv;
+    o.w[2] = w1 - o.w[3];
+    o.w[1] = w0 * fv;
+    o.w[0] = w0 - o.w[1];
   }
-  const float dalpha_act = ps.g0 * (c0 * ps.T - ps.S0 * inv1m) +
-                           ps.g1 * (c1 * ps.T - ps.S1 * inv1m) + ps.g2 * (c2 * ps.T - ps.S2 * inv1m);
-  const float dalpha = act ? dalpha_act : 0.f;
-  ps.S0 += wgt * c0;
-  ps.S1 += wgt * c1;
-  ps.S2 += wgt * c2;
-  const bool unclamped = g.g0.w * e.G <= p.alpha_max;
-  o.go = unclamped ? dalpha * e.G : 0.f;
-  const float dq = unclamped ? -e.G * g.g0.w * dalpha : 0.f;
+  const float da = col * ps.T - ps.Sg * inv1m;
+  ps.Sg += wgt * col;
+  // zero where the pixel did not blend the splat or alpha was clamped to alpha_max
+  const float oG = g.g0.w * e.G;
+  const float dalpha = (act && oG <= p.alpha_max) ? da : 0.f;
   // the falloff's adjoint goes to (u, v) or to the low-pass offset, selected without a branch
-  const float dq_uv = e.uv_branch ? dq : 0.f;
-  const float dq_lp = e.uv_branch ? 0.f : dq * 2.f * p.lp_scale;
+  const float dq = -oG * dalpha;
+  const float dq_uv = e.uv_branch ? dq : 0.f, dq_lp = e.uv_branch ? 0.f : dq;
   du += dq_uv * u;
   dv += dq_uv * v;
   const float dr0 = du * inv, dr1 = dv * inv;
   const float dr2 = -(du * u + dv * v) * inv;
-  o.gh[0] = dr0 * e.dx;
-  o.gh[1] = dr0 * e.dy;
-  o.gh[2] = dr1 * e.dx;
-  o.gh[3] = dr1 * e.dy;
-  o.gh[4] = dr2 * e.dx;
-  o.gh[5] = dr2 * e.dy;
-  o.gh[6] = dr2;
-  // d c2 collects the low-pass term and the uv term through rho's dependence on the offset
-  // (c2 enters both with a minus sign; written as negated products, which fold into the
-  // multiply-adds)
-  o.gc2x = -(dq_lp * e.dx) - dr0 * g.g1.x - dr1 * g.g1.z - dr2 * g.g2.x;
-  o.gc2y = -(dq_lp * e.dy) - dr0 * g.g1.y - dr1 * g.g1.w - dr2 * g.g2.y;
+  o.sum[0] = dr0 * e.dx;
+  o.sum[1] = dr0 * e.dy;
+  o.sum[2] = dr1 * e.dx;
+  o.sum[3] = dr1 * e.dy;
+  o.sum[4] = dr2 * e.dx;
+  o.sum[5] = dr2 * e.dy;
+  o.sum[6] = dr2;
+  o.sum[7] = dr0;
+  o.sum[8] = dr1;
+  o.sum[9] = dq_lp * e.dx;
+  o.sum[10] = dq_lp * e.dy;
+  o.sum[11] = dalpha * e.G;
+}
+
+// Row of a cell index of the LDS texel layout.
+template <int N>
+__device__ __forceinline__ int cell_row(int cell) {
+  return (int)((unsigned)cell / (unsigned)TexLayout<N>::kRow);
+}
+
+// Record gradient r (in the order of kRecGrad) from a splat's sums x and its staged H.
+__device__ __forceinline__ float record_gradient(int r, const float* x, const float4& g1,
+                                                 const float4& g2, float lp_scale) {
+  if (r < 7) return x[r];
+  if (r == 9) return x[11];
+  // d c2: minus the low-pass term's and rho's adjoints of the offset
+  const bool y = r == 8;
+  const float lp = 2.f * lp_scale * x[y ? 10 : 9];
+  return -lp - x[7] * (y ? g1.y : g1.x) - x[8] * (y ? g1.w : g1.z) - x[6] * (y ? g2.y : g2.x);
 }
 
 // With batches of 8 the LDS allows 7 workgroups per CU (22.6 KB each for 8 x 8 grids, with
@@ -172,7 +188,7 @@ constexpr int bwd_stage_ahead() { return N >= 16 ? 4 : 64 / B; }
 // registers, the prefix pass's list; other tiles only walk the prefix list.
 // MIXED: each splat has a grid side of its own (at most N), read from p.grid_n; its texel
 // gradients go to its own n x n grid at p.grid_at.
-template <int N, bool BF16, int B, int PIX, bool MIXED>
+template <int N, bool BF16, int B, bool MIXED>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(bwd_min_waves<N, B, MIXED>())))
 blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__ rec,
                  PairList first, PairList rest, const uint32_t* __restrict__ open_bits,
@@ -180,7 +196,6 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
                  const float* __restrict__ T_final, const float* __restrict__ d_rgb,
                  float* __restrict__ d_rec, float* __restrict__ d_tex) {
   constexpr int TEXG = 3 * N * N;
-  constexpr int BH = 8 * PIX;  // wave block: 8 columns x BH rows
   // Per-splat geometry and indices of AHEAD batches (slot k holds [k B, (k + 1) B)): every
   // AHEAD-th batch stages its own and the next AHEAD - 1 batches' geometry in one pass of the
   // staging threads.
@@ -191,7 +206,7 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
   __shared__ uint32_t s_recid[AHEAD * B];
   __shared__ float4 s_tex[B * TexLayout<N>::kPerSplat];
   __shared__ __attribute__((aligned(16))) float s_gtex[B * TEXG];
-  __shared__ float s_grec[B * kRecGrad];  // per splat
+  __shared__ float s_sum[B * kSums];  // per splat
   __shared__ uint32_t s_tile_last;
   __shared__ int32_t s_gn[MIXED ? AHEAD * B : 1];
   __shared__ float4 s_gc[MIXED ? AHEAD * B : 1];
@@ -212,41 +227,37 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int waves_x = p.tile_w >> 3;
   const int n_waves = nthr >> 6;
-  const int bx = (w % waves_x) * 8, by = (w / waves_x) * BH;
+  const int bx = (w % waves_x) * 8, by = (w / waves_x) * 8;
   const int lxi = bx + (lane & 7);
   // pixel centres relative to the wave block's centre (exact half-integers); the block centre
   // relative to the tile's (wave-uniform integers)
   const float lx = (float)(lane & 7) - 3.5f;
   const int tcx = tile_x0 + (p.tile_w >> 1), tcy = tile_y0 + (p.tile_h >> 1);
-  const float bcx = (float)(tile_x0 + bx + 4 - tcx), bcy = (float)(tile_y0 + by + BH / 2 - tcy);
-  float ly[PIX];
-  PixState ps[PIX];
-  // packed index of the lane's s-th pixel, or -1 outside the view (recomputed when needed)
-  auto pixel_index = [&](int s) -> int64_t {
-    const int px = tile_x0 + lxi, py = tile_y0 + by + PIX * (lane >> 3) + s;
+  const float bcx = (float)(tile_x0 + bx + 4 - tcx), bcy = (float)(tile_y0 + by + 4 - tcy);
+  const float ly = (float)(lane >> 3) - 3.5f;
+  // packed index of the lane's pixel, or -1 outside the view (recomputed when needed)
+  auto pixel_index = [&]() -> int64_t {
+    const int px = tile_x0 + lxi, py = tile_y0 + by + (lane >> 3);
     return (px < V.W && py < V.H) ? (int64_t)V.pix_base + (int64_t)py * V.W + px : -1;
   };
-#pragma unroll
-  for (int s = 0; s < PIX; ++s) {
-    ly[s] = (float)(PIX * (lane >> 3) + s) - 0.5f * (float)(BH - 1);
-    const int64_t pix = pixel_index(s);
-    ps[s].T = 1.0f;
-    ps[s].g0 = ps[s].g1 = ps[s].g2 = 0.f;
+  PixState ps;
+  {
+    const int64_t pix = pixel_index();
+    ps.T = 1.0f;
+    ps.g0 = ps.g1 = ps.g2 = 0.f;
     if (pix >= 0) {
-      ps[s].T = T_final[pix];
-      ps[s].g0 = d_rgb[3 * pix + 0];
-      ps[s].g1 = d_rgb[3 * pix + 1];
-      ps[s].g2 = d_rgb[3 * pix + 2];
+      ps.T = T_final[pix];
+      ps.g0 = d_rgb[3 * pix + 0];
+      ps.g1 = d_rgb[3 * pix + 1];
+      ps.g2 = d_rgb[3 * pix + 2];
     }
-    ps[s].S0 = ps[s].T * p.bg[0];
-    ps[s].S1 = ps[s].T * p.bg[1];
-    ps[s].S2 = ps[s].T * p.bg[2];
+    ps.Sg = ps.T * (ps.g0 * p.bg[0] + ps.g1 * p.bg[1] + ps.g2 * p.bg[2]);
   }
   // which wave total each lane receives from the reductions below
   int rec_slot, tex_slot;
   bool rec_owner, tex_owner;
   const SwapSides sides = swap_sides();
-  wave_scatter_slot<kRecGrad>(sides, rec_slot, rec_owner);
+  wave_scatter_slot<kSums>(sides, rec_slot, rec_owner);
   // texel sums: the three channels of each of the four cell corners (one corner when N = 1);
   // tex_off is the lane's value's offset from the cell's first channel
   constexpr int KT = N == 1 ? 3 : 12;
@@ -256,26 +267,22 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
   // the per-batch LDS sums start at zero; each batch's flush clears what it read
   // (the first barrier of the list loop orders these stores before any add)
   for (int e = tid; e < B * TEXG; e += nthr) s_gtex[e] = 0.f;
-  for (int e = tid; e < B * kRecGrad; e += nthr) s_grec[e] = 0.f;
+  for (int e = tid; e < B * kSums; e += nthr) s_sum[e] = 0.f;
 
 #pragma unroll 1
   for (int li = tile_open ? 0 : 1; li < 2; ++li) {
     const PairList L = li == 0 ? rest : first;
     const uint32_t* __restrict__ pair_vals = L.pair_vals;
     const uint32_t start = L.ranges[2 * tile];
-#pragma unroll
-    for (int s = 0; s < PIX; ++s) {
-      const int64_t pix = pixel_index(s);
-      ps[s].last = pix >= 0 ? L.n_last[pix] : start;
+    {
+      const int64_t pix = pixel_index();
+      ps.last = pix >= 0 ? L.n_last[pix] : start;
     }
-    uint32_t lane_last = ps[0].last;
-#pragma unroll
-    for (int s = 1; s < PIX; ++s) lane_last = ps[s].last > lane_last ? ps[s].last : lane_last;
 
     __syncthreads();  // every thread has read the previous list's bound
     if (tid == 0) s_tile_last = start;
     __syncthreads();
-    atomicMax(&s_tile_last, lane_last);  // largest bound over the tile's pixels
+    atomicMax(&s_tile_last, ps.last);  // largest bound over the tile's pixels
     __syncthreads();
     const uint32_t tile_last = s_tile_last;
 
@@ -302,11 +309,11 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
         const int jj = h * B + j;
         const uint32_t r = pair_vals[hstart + j];
         const SplatRec R = rec[r];
-        const int kbx = tile_x0 + (b % waves_x) * 8, kby = tile_y0 + (b / waves_x) * BH;
-        const StagedGeo g = stage_geo(R, kbx + 4, kby + BH / 2, tcx, tcy);
+        const int kbx = tile_x0 + (b % waves_x) * 8, kby = tile_y0 + (b / waves_x) * 8;
+        const StagedGeo g = stage_geo(R, kbx + 4, kby + 4, tcx, tcy);
         s_geo.store(b, jj, g);
         s_reach[b][jj] = block_may_contribute(g, (float)(kbx + 4 - tcx),
-                                              (float)(kby + BH / 2 - tcy), kbx, kby, p, 8, BH)
+                                              (float)(kby + 4 - tcy), kbx, kby, p)
                              ? 1
                              : 0;
         if (b == 0) {
@@ -352,76 +359,43 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
         const int j = 63 - (int)__builtin_clzll(todo);
         todo &= ~(1ull << j);
         const uint32_t jg = bstart + (uint32_t)j;
-        if (ballot(jg < lane_last) == 0) continue;
+        if (ballot(jg < ps.last) == 0) continue;
         const StagedGeo g = s_geo.load(w, so + j);
         const float4* tex = s_tex + j * TexLayout<N>::kPerSplat;
-        PixelEval e[PIX];
-        bool act[PIX];
-        // lanes that blended this splat (one mask per pixel slot); the masks serve the skip test
-        // below and the texel scatter
-        uint64_t pend[PIX], any_act = 0;
-#pragma unroll
-        for (int s = 0; s < PIX; ++s) {
-          e[s] = eval_splat(g, lx, ly[s], lx + bcx, ly[s] + bcy, p);
-          act[s] = (jg < ps[s].last) && e[s].hit;
-          pend[s] = ballot(act[s]);
-          any_act |= pend[s];
-        }
-        if (any_act == 0) continue;  // no pixel of the wave blended this splat
-        PixOut po[PIX];
+        const PixelEval e = eval_splat(g, lx, ly, lx + bcx, ly + bcy, p);
+        const bool act = (jg < ps.last) && e.hit;
+        const uint64_t pend = ballot(act);  // lanes that blended this splat
+        if (pend == 0) continue;            // no pixel of the wave blended it
+        PixOut po;
         if constexpr (MIXED) {
           const float4 gc = s_gc[so + j];
-#pragma unroll
-          for (int s = 0; s < PIX; ++s)
-            pixel_step<N, true>(g, tex, e[s], act[s], ps[s], p, po[s], gc);
+          pixel_step<N, true>(g, tex, e, act, ps, p, po, gc);
         } else {
-#pragma unroll
-          for (int s = 0; s < PIX; ++s) pixel_step<N>(g, tex, e[s], act[s], ps[s], p, po[s]);
+          pixel_step<N>(g, tex, e, act, ps, p, po);
         }
 
-        // Wave sums of the per-splat scalars (a lane first adds its own pixels); the one lane
-        // that owns each total adds it to the splat's LDS slot.
+        // Wave sums of the per-splat scalars; the one lane that owns each total adds it to the
+        // splat's LDS slot.
         {
-          float red[kRecGrad];
-#pragma unroll
-          for (int k = 0; k < 7; ++k) red[k] = po[0].gh[k];
-          red[7] = po[0].gc2x;
-          red[8] = po[0].gc2y;
-          red[9] = po[0].go;
-#pragma unroll
-          for (int s = 1; s < PIX; ++s) {
-#pragma unroll
-            for (int k = 0; k < 7; ++k) red[k] += po[s].gh[k];
-            red[7] += po[s].gc2x;
-            red[8] += po[s].gc2y;
-            red[9] += po[s].go;
-          }
-          const float tot = wave_reduce_scatter<kRecGrad>(red);
-          if (rec_owner) atomicAdd(&s_grec[j * kRecGrad + rec_slot], tot);
+          const float tot = wave_reduce_scatter<kSums>(po.sum);
+          if (rec_owner) atomicAdd(&s_sum[j * kSums + rec_slot], tot);
         }
 
-        // Texel gradients, grouped by cell over all pixels of the wave.
-        float* gt = s_gtex + j * TEXG + tex_off;  // this lane's value in cell 0
-        // A wave step that blended few pixels (small or distant splats) adds each pixel's
-        // bilinear corners to LDS directly; up to kLaneAddMax lanes this costs less than group
-        // passes.
-        int n_act = 0;
+        // Texel gradients, grouped by cell over all pixels of the wave. A wave step that blended
+        // few pixels (small or distant splats) adds each pixel's bilinear corners to LDS
+        // directly; up to kLaneAddMax lanes this costs less than group passes.
+        float* const gb = s_gtex + j * TEXG;
+        if (__builtin_popcountll(pend) <= kLaneAddMax) {
+          if (act) {
+            const int iu = cell_row<N>(po.cell), k00 = po.cell - iu;
 #pragma unroll
-        for (int s = 0; s < PIX; ++s) n_act += __builtin_popcountll(pend[s]);
-        if (n_act <= kLaneAddMax) {
-          float* gb = s_gtex + j * TEXG;
-#pragma unroll
-          for (int s = 0; s < PIX; ++s) {
-            if (act[s]) {  // this lane's bit of pend[s]
-#pragma unroll
-              for (int q = 0; q < KT / 3; ++q) {
-                const float wq = po[s].w[q];
-                if (wq != 0.f) {
-                  float* dst = gb + 3 * (po[s].k00 + (q & 1) + (q >> 1) * N);
-                  atomicAdd(dst + 0, wq * po[s].dc0);
-                  atomicAdd(dst + 1, wq * po[s].dc1);
-                  atomicAdd(dst + 2, wq * po[s].dc2);
-                }
+            for (int q = 0; q < KT / 3; ++q) {
+              const float wq = po.w[q];
+              if (wq != 0.f) {
+                float* dst = gb + 3 * (k00 + (q & 1) + (q >> 1) * N);
+                atomicAdd(dst + 0, wq * ps.g0);
+                atomicAdd(dst + 1, wq * ps.g1);
+                atomicAdd(dst + 2, wq * ps.g2);
               }
             }
           }
@@ -431,30 +405,26 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
           // 1M splats and 1080p (10 % of wave steps have more than four cells), eight passes
           // 1.73 ms: the per-lane adds, serialised on shared addresses, cost more than passes.
           // Each pending lane carries its cell as the group key, -1 once its group is taken;
-          // non-members contribute through zeroed adjoints. (The lean form of the pass: about
-          // four VALU instructions fewer than testing the pending mask bit and selecting the
-          // four corner weights; backward 1.41 -> 1.39 ms at 1M splats and 1080p.)
-          static_assert(PIX == 1, "one pixel per lane");
-          int key = act[0] ? po[0].k00 : -1;  // act[0]: this lane's bit of pend[0]
-  #pragma unroll 1
-          for (uint64_t left = pend[0]; left != 0;) {
-            const int lead_cell = __builtin_amdgcn_readlane(key, (int)__builtin_ctzll(left));
-            const bool in = key == lead_cell;
+          // non-members contribute through zeroed weights.
+          int key = act ? po.cell : -1;
+#pragma unroll 1
+          for (uint64_t left = pend; left != 0;) {
+            const int lead = __builtin_amdgcn_readlane(key, (int)__builtin_ctzll(left));
+            const bool in = key == lead;
             key = in ? -1 : key;
             left &= ~ballot(in);
             // all corners and channels in one transposing wave reduction, so that one lane per
             // value adds it to LDS: one add instruction per group
-            const float d0 = in ? po[0].dc0 : 0.f, d1 = in ? po[0].dc1 : 0.f,
-                        d2 = in ? po[0].dc2 : 0.f;
             float red[KT];
-  #pragma unroll
+#pragma unroll
             for (int q = 0; q < KT / 3; ++q) {
-              red[3 * q] = po[0].w[q] * d0;
-              red[3 * q + 1] = po[0].w[q] * d1;
-              red[3 * q + 2] = po[0].w[q] * d2;
+              const float wq = in ? po.w[q] : 0.f;
+              red[3 * q] = wq * ps.g0;
+              red[3 * q + 1] = wq * ps.g1;
+              red[3 * q + 2] = wq * ps.g2;
             }
             const float tot = wave_reduce_scatter<KT>(red);
-            if (tex_owner) atomicAdd(gt + 3 * lead_cell, tot);
+            if (tex_owner) atomicAdd(gb + tex_off + 3 * (lead - cell_row<N>(lead)), tot);
           }
         }
       }
@@ -512,10 +482,16 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
           }
         }
       }
-      for (int e = tid; e < nb * kRecGrad; e += nthr) {
-        const int j = e / kRecGrad, r = e - j * kRecGrad;
-        const float x = s_grec[e];
-        s_grec[e] = 0.f;
+      // sixteen lanes of one wave per splat: each reads the sums its record gradient needs, and
+      // only then are they cleared
+      for (int e = tid; e < 16 * nb; e += nthr) {
+        const int j = e >> 4, r = e & 15;
+        const float x = r < kRecGrad ? record_gradient(r, &s_sum[j * kSums], s_geo.g1[so + j],
+                                                       s_geo.g2[so + j], p.lp_scale)
+                                     : 0.f;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (r < kSums) s_sum[j * kSums + r] = 0.f;
         if (x != 0.f) atomicAdd(&d_rec[(int64_t)s_recid[so + j] * kRecGrad + r], x);
       }
       // the next batch: its texels (and, when it starts a staging pass, the pass's geometry)
@@ -537,16 +513,16 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
   }  // lists
 }
 
-template <int N, bool BF16, int PIX, bool MIXED = false>
+template <int N, bool BF16, bool MIXED = false>
 hipError_t launch_np(const Plan& pl, const gb_splats& sp, const BlendParams& bp,
                      const ViewDev* views, const SplatRec* rec, const PairList& first,
                      const PairList& rest, const uint32_t* open_bits, const float* T_final,
                      const float* d_rgb, float* d_rec, float* d_tex, hipStream_t s) {
   const dim3 grid((unsigned)(bp.tile_order ? (int64_t)bp.total_tiles
                                            : 8 * (int64_t)bp.tiles_per_xcd));
-  const dim3 block((unsigned)(pl.tile_w * pl.tile_h / PIX));
+  const dim3 block((unsigned)(pl.tile_w * pl.tile_h));
 #define GBB_BWD_B(BB)                                                                         \
-  hipLaunchKernelGGL((blend_bwd_kernel<N, BF16, BB, PIX, MIXED>), grid, block, 0, s, views, rec, \
+  hipLaunchKernelGGL((blend_bwd_kernel<N, BF16, BB, MIXED>), grid, block, 0, s, views, rec, \
                      first, rest, open_bits, sp.textures, bp, T_final, d_rgb, d_rec, d_tex)
   if constexpr (N >= 16) {
     // the only batch built for N = 16: at 8 splats of 16 x 16 texels (texels and their
@@ -583,22 +559,22 @@ hipError_t launch_blend_bwd(const Plan& pl, const gb_splats& sp, const gb_option
     bp.grid_n = sp.tex_side;
     bp.grid_at = sp.tex_offset;
     if (pl.N == 16)
-      return bf ? launch_np<16, true, 1, true>(pl, sp, bp, views, rec, first, rest, open_bits,
+      return bf ? launch_np<16, true, true>(pl, sp, bp, views, rec, first, rest, open_bits,
                                                T_final, d_rgb, d_rec, d_tex, s)
-                : launch_np<16, false, 1, true>(pl, sp, bp, views, rec, first, rest, open_bits,
+                : launch_np<16, false, true>(pl, sp, bp, views, rec, first, rest, open_bits,
                                                 T_final, d_rgb, d_rec, d_tex, s);
-    return bf ? launch_np<8, true, 1, true>(pl, sp, bp, views, rec, first, rest, open_bits,
+    return bf ? launch_np<8, true, true>(pl, sp, bp, views, rec, first, rest, open_bits,
                                             T_final, d_rgb, d_rec, d_tex, s)
-              : launch_np<8, false, 1, true>(pl, sp, bp, views, rec, first, rest, open_bits,
+              : launch_np<8, false, true>(pl, sp, bp, views, rec, first, rest, open_bits,
                                              T_final, d_rgb, d_rec, d_tex, s);
   }
   // One pixel per lane. Two pixels per lane (8 x 16 wave blocks) measured slower on the
   // 1M-splat 1080p workload (3.0 vs 2.3 ms): LDS limits such blocks to two waves per SIMD and
   // the per-wave cull is coarser.
 #define GBB_BWD(NN)                                                                           \
-  return bf ? launch_np<NN, true, 1>(pl, sp, bp, views, rec, first, rest, open_bits, T_final, \
+  return bf ? launch_np<NN, true>(pl, sp, bp, views, rec, first, rest, open_bits, T_final, \
                                      d_rgb, d_rec, d_tex, s)                                  \
-            : launch_np<NN, false, 1>(pl, sp, bp, views, rec, first, rest, open_bits, T_final,\
+            : launch_np<NN, false>(pl, sp, bp, views, rec, first, rest, open_bits, T_final,\
                                       d_rgb, d_rec, d_tex, s)
   switch (pl.N) {
     case 1: GBB_BWD(1);
