@@ -9,19 +9,24 @@
 //   uv branch: du += dq u, dv += dq v; low-pass branch: d(dx, dy) += dq 2 (dx, dy) / (2 var),
 //   (u, v) = (rho0, rho1) / rho2 -> d rho -> d H (7 entries) and d(dx, dy) -> d c2 = -d(dx, dy).
 //
-// A lane owns one pixel (waves of 8 x 8 pixels). Per splat, twelve sums over the wave are taken
-// by a transposing reduction (permlane swaps across the wave's halves and row pairs, then a DPP
-// butterfly inside each row) that leaves each total in one lane, which adds it to the splat's
-// LDS slot; the ten record gradients are formed from them once per batch. Texel gradients are grouped by grid cell (with
-// sigma = 0.5 the grid covers only the splat's core, so most blended pixels are border-clamped
-// and share a few cells); each group's four corners and three channels are reduced the same
-// way, one group after another until every pixel's cell has been taken (a step that blended
-// at most kLaneAddMax pixels adds each pixel's corners directly instead). A splat that no
-// pixel of the wave blended is skipped after evaluation. After each batch the non-zero LDS
-// sums go to global memory with one float atomic each, while the next batch's texels are
-// staged; one staging pass prepares the geometry of several batches (bwd_stage_ahead).
+// A lane owns one pixel (waves of 8 x 8 pixels). The list is taken in passes of 64 entries: each
+// wave stages the entries' geometry for its own block, one entry per lane, and votes which can
+// reach it; entries that reach some block of the tile get slots, in batches, for their texels and
+// for the sums over pixels. Per splat and wave, twelve sums are taken by masked DPP adds inside
+// the rows of 16 lanes; texel gradients are grouped by grid cell (with sigma = 0.5 the grid covers
+// only the splat's core, so most blended pixels are border-clamped and share a few cells), one
+// group after another, over the corners that the group weights (a step that blended at most
+// kLaneAddMax pixels adds each pixel's corners directly instead). After each batch the non-zero
+// sums go to global memory with one float atomic each, while the next batch's texels are staged.
+//
+// The sums are 64-bit in LDS: ds_add_f64 serves 64 lanes with distinct addresses in 8.7 cycles of
+// the CU's LDS (12 lanes 6.5, and 3 per lane on one address), where ds_add_f32 takes 3 cycles for
+// every lane whatever the addresses (12 lanes 38, 64 lanes 193), which had made the LDS the
+// limit. What bounds the kernel now is VALU issue (1M splats at 1080p: 88 % of the cycles; 0.65 G
+// wave instructions, about 228 per wave step). At 1M splats and 1080p 1.35 -> 1.05 ms, 3M splats
+// on four 1080p views 14.5 -> 13.2, 16 uneven views with 4 x 4 grids 8.28 -> 6.53, 16 x 16 grids
+// 2.33 -> 1.87, sides {2, 4, 8} 1.53 -> 1.10.
 #include "blend_common.h"
-
 
 namespace gbb {
 
@@ -44,8 +49,9 @@ struct PixState {
 };
 
 struct PixOut {
-  int cell;         // first corner's index in the LDS texel layout (TexLayout)
-  float w[4];       // alpha T times the corner weights (00, 01, 10, 11)
+  int cell;          // first corner's index in the LDS texel layout (TexLayout)
+  float wgt, fu, fv; // alpha T and the position inside the cell
+  uint64_t in_u, in_v;  // lanes where |u| < sigma, |v| < sigma: not clamped to the border
   float sum[kSums];
 };
 
@@ -55,28 +61,30 @@ struct PixOut {
 // (they are infinite where rho2 = 0). Its cell is left unspecified.
 // The four corner texels are multiplied by g first (12 multiply-adds) and interpolated as
 // scalars: the value and both fractional-position adjoints then cost 9 operations instead of 33
-// over three channels. Together with the scalar Sg this took the 8 x 8 kernel from 287 to about
-// 245 VALU instructions per wave step.
+// over three channels.
+// CHANNELS keeps the interpolation per channel and every operation in the order written here.
+// Where the falloff is the low-pass's and one coordinate lies inside the grid while the other is
+// clamped, the adjoint of the other axis' scale is zero in exact arithmetic, and what comes out
+// is the rounding residue of terms that cancel. Adam divides a gradient by its own size, so that
+// this residue's sign moves the parameter by a full step: such lanes keep their operations, and
+// the order of their sums, so that a training run goes on as it did before the scalar form.
 // MIXED: gc holds the grid-coordinate constants of the splat's grid (grid_consts).
-template <int N, bool MIXED = false>
-__device__ __forceinline__ void pixel_step(const StagedGeo& g, const float4* tex,
-                                           const PixelEval& e, bool act, PixState& ps,
-                                           const BlendParams& p, PixOut& o,
-                                           float4 gc = make_float4(0.f, 0.f, 0.f, 0.f)) {
-  const float inv = act ? e.inv : 0.f;
-  const float u = act ? e.u : 0.f, v = act ? e.v : 0.f;
+template <int N, bool MIXED, bool CHANNELS>
+__device__ __forceinline__ void pixel_step(const float4* tex, const PixelEval& e, float inv,
+                                           float u, float v, bool act, PixState& ps,
+                                           const BlendParams& p, PixOut& o, const float4& gc) {
   const float alpha = act ? e.alpha : 0.f;
   const float inv1m = __builtin_amdgcn_rcpf(1.0f - alpha);
   ps.T = ps.T * inv1m;  // transmittance in front of this splat
   const float wgt = alpha * ps.T;
+  o.wgt = wgt;
   float col;  // g . colour
   float du = 0.f, dv = 0.f;
   if constexpr (N == 1) {
     const float4 t = tex[0];
     col = ps.g0 * t.x + ps.g1 * t.y + ps.g2 * t.z;
     o.cell = 0;
-    o.w[0] = wgt;
-    o.w[1] = o.w[2] = o.w[3] = 0.f;
+    o.fu = o.fv = 0.f;
   } else {
     int iu, iv;
     float fu, fv;
@@ -87,51 +95,86 @@ __device__ __forceinline__ void pixel_step(const StagedGeo& g, const float4* tex
       grid_coord<N>(u, p, iu, fu);
       grid_coord<N>(v, p, iv, fv);
     }
+    o.fu = fu;
+    o.fv = fv;
     const int kr = TexLayout<N>::kRow;
     o.cell = TexLayout<N>::at(iu, iv);
-    const float4 *t = tex + o.cell;
-    const float4 t00 = t[0], t01 = t[1], t10 = t[kr], t11 = t[kr + 1];
-    const float q00 = ps.g0 * t00.x + ps.g1 * t00.y + ps.g2 * t00.z;
-    const float q01 = ps.g0 * t01.x + ps.g1 * t01.y + ps.g2 * t01.z;
-    const float q10 = ps.g0 * t10.x + ps.g1 * t10.y + ps.g2 * t10.z;
-    const float q11 = ps.g0 * t11.x + ps.g1 * t11.y + ps.g2 * t11.z;
-    const float d0 = q01 - q00, d1 = q11 - q10;
-    const float a = q00 + fv * d0, d = (q10 + fv * d1) - a;
-    col = a + fu * d;
+    const float4* t = tex + o.cell;
+    const float4 t00 = load_texel(t), t01 = load_texel(t + 1);
+    const float4 t10 = load_texel(t + kr), t11 = load_texel(t + kr + 1);
+    const float tsc = MIXED ? gc.x : p.tex_scale;
     // fractional-position adjoints (Alg. 2), zero where the coordinate is clamped
-    const float wsc = wgt * (MIXED ? gc.x : p.tex_scale);
-    du = fabsf(u) < p.sigma ? wsc * d : 0.f;  // (-sigma, sigma): one compare with |u|
-    dv = fabsf(v) < p.sigma ? wsc * (d0 + fu * (d1 - d0)) : 0.f;
-    const float w1 = wgt * fu, w0 = wgt - w1;
-    o.w[3] = w1 * fv;
-    o.w[2] = w1 - o.w[3];
-    o.w[1] = w0 * fv;
-    o.w[0] = w0 - o.w[1];
+    if constexpr (CHANNELS) {
+#pragma clang fp contract(off)
+      const float g[3] = {ps.g0, ps.g1, ps.g2};
+      const float x0[3] = {t00.x, t00.y, t00.z}, x1[3] = {t01.x, t01.y, t01.z};
+      const float y0[3] = {t10.x, t10.y, t10.z}, y1[3] = {t11.x, t11.y, t11.z};
+      float c[3], dc[3], d[3], f[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const float xd = x1[k] - x0[k], yd = y1[k] - y0[k];
+        const float a = __builtin_fmaf(fv, xd, x0[k]), b = __builtin_fmaf(fv, yd, y0[k]);
+        dc[k] = wgt * g[k];
+        d[k] = b - a;
+        c[k] = __builtin_fmaf(fu, d[k], a);
+        f[k] = __builtin_fmaf(1.f - fu, xd, fu * yd);
+      }
+      const float dfu = __builtin_fmaf(dc[2], d[2], __builtin_fmaf(dc[0], d[0], dc[1] * d[1]));
+      const float dfv = __builtin_fmaf(dc[2], f[2], __builtin_fmaf(dc[0], f[0], dc[1] * f[1]));
+      col = __builtin_fmaf(g[2], c[2], __builtin_fmaf(g[0], c[0], g[1] * c[1]));
+      du = tsc * dfu;
+      dv = tsc * dfv;
+    } else {
+      const float q00 = ps.g0 * t00.x + ps.g1 * t00.y + ps.g2 * t00.z;
+      const float q01 = ps.g0 * t01.x + ps.g1 * t01.y + ps.g2 * t01.z;
+      const float q10 = ps.g0 * t10.x + ps.g1 * t10.y + ps.g2 * t10.z;
+      const float q11 = ps.g0 * t11.x + ps.g1 * t11.y + ps.g2 * t11.z;
+      const float d0 = q01 - q00, d1 = q11 - q10;
+      const float a = q00 + fv * d0, d = (q10 + fv * d1) - a;
+      col = a + fu * d;
+      const float wsc = wgt * tsc;
+      du = wsc * d;
+      dv = wsc * (d0 + fu * (d1 - d0));
+    }
+    du = __builtin_amdgcn_inverse_ballot_w64(o.in_u) ? du : 0.f;
+    dv = __builtin_amdgcn_inverse_ballot_w64(o.in_v) ? dv : 0.f;
   }
   const float da = col * ps.T - ps.Sg * inv1m;
   ps.Sg += wgt * col;
   // zero where the pixel did not blend the splat or alpha was clamped to alpha_max
-  const float oG = g.g0.w * e.G;
-  const float dalpha = (act && oG <= p.alpha_max) ? da : 0.f;
+  const float dalpha = (act && e.oG <= p.alpha_max) ? da : 0.f;
   // the falloff's adjoint goes to (u, v) or to the low-pass offset, selected without a branch
-  const float dq = -oG * dalpha;
+  const float dq = -e.oG * dalpha;
   const float dq_uv = e.uv_branch ? dq : 0.f, dq_lp = e.uv_branch ? 0.f : dq;
-  du += dq_uv * u;
-  dv += dq_uv * v;
-  const float dr0 = du * inv, dr1 = dv * inv;
-  const float dr2 = -(du * u + dv * v) * inv;
-  o.sum[0] = dr0 * e.dx;
-  o.sum[1] = dr0 * e.dy;
-  o.sum[2] = dr1 * e.dx;
-  o.sum[3] = dr1 * e.dy;
-  o.sum[4] = dr2 * e.dx;
-  o.sum[5] = dr2 * e.dy;
-  o.sum[6] = dr2;
-  o.sum[7] = dr0;
-  o.sum[8] = dr1;
+  {
+#pragma clang fp contract(off)
+    du = __builtin_fmaf(u, dq_uv, du);
+    dv = __builtin_fmaf(v, dq_uv, dv);
+    const float dr0 = du * inv, dr1 = dv * inv;
+    const float dr2 = -__builtin_fmaf(u, du, v * dv) * inv;
+    o.sum[0] = dr0 * e.dx;
+    o.sum[1] = dr0 * e.dy;
+    o.sum[2] = dr1 * e.dx;
+    o.sum[3] = dr1 * e.dy;
+    o.sum[4] = dr2 * e.dx;
+    o.sum[5] = dr2 * e.dy;
+    o.sum[6] = dr2;
+    o.sum[7] = dr0;
+    o.sum[8] = dr1;
+  }
   o.sum[9] = dq_lp * e.dx;
   o.sum[10] = dq_lp * e.dy;
   o.sum[11] = dalpha * e.G;
+}
+
+// w times the corner weights (00, 01, 10, 11) at (fu, fv). The multiply-adds are written out:
+// contracted from w - w f they could leave a rounding residue instead of 0 at f = 1.
+__device__ __forceinline__ void corner_weights(float w, float fu, float fv, float (&wc)[4]) {
+  const float w1 = w * fu, w0 = __builtin_fmaf(-w, fu, w);
+  wc[0] = __builtin_fmaf(-w0, fv, w0);
+  wc[1] = w0 * fv;
+  wc[2] = __builtin_fmaf(-w1, fv, w1);
+  wc[3] = w1 * fv;
 }
 
 // Row of a cell index of the LDS texel layout.
@@ -140,48 +183,60 @@ __device__ __forceinline__ int cell_row(int cell) {
   return (int)((unsigned)cell / (unsigned)TexLayout<N>::kRow);
 }
 
-// Record gradient r (in the order of kRecGrad) from a splat's sums x and its staged H.
-__device__ __forceinline__ float record_gradient(int r, const float* x, const float4& g1,
-                                                 const float4& g2, float lp_scale) {
-  if (r < 7) return x[r];
-  if (r == 9) return x[11];
-  // d c2: minus the low-pass term's and rho's adjoints of the offset
-  const bool y = r == 8;
-  const float lp = 2.f * lp_scale * x[y ? 10 : 9];
-  return -lp - x[7] * (y ? g1.y : g1.x) - x[8] * (y ? g1.w : g1.z) - x[6] * (y ? g2.y : g2.x);
+// Adds the total that row_sums or ordered_sums left in each owner lane to an LDS array at index
+// base + offset (base uniform over the wave).
+template <uint64_t OWNERS>
+__device__ __forceinline__ void lds_add(double* array, int base, int offset, float tot) {
+  base = __builtin_amdgcn_readfirstlane(base);
+  __asm__ volatile("" : "+s"(base));  // a scalar add, not part of a 64-bit multiply-add
+  if (__builtin_amdgcn_inverse_ballot_w64(OWNERS)) atomicAdd(array + offset + base, (double)tot);
 }
 
-// With batches of 8 the LDS allows 7 workgroups per CU (22.6 KB each for 8 x 8 grids, with
-// the geometry of 8 batches), but the register allocation (75 VGPRs unconstrained) stops at
-// 6 waves per SIMD; asking for 7 (at most 72 VGPRs; the compiler's resource report for
-// 8 x 8 FP32 grids gives 71 and no scratch) measured 4 % faster on the 1M-splat 1080p
-// workload, 8 (64 VGPRs) slower.
-// (N = 16 blocks, at a batch of 4 with a ring of 4 batches' geometry, hold 32 KB of LDS, five
-// per CU, so no register target applies there.)
-// Wave steps that blended at most this many pixels skip the cell grouping. Measured with the
-// multi-batch staging, backward ms for thresholds 16 / 24 / 28 / 32: 1M splats at 1080p 1.41 /
-// 1.41 / 1.41 / 1.42 (two runs each), 3M splats at 4 x 1080p 15.32 / 14.77 / 14.63 / 14.61,
-// 100k splats at 800x800 0.807 / 0.764 / 0.765 / 0.745.
-constexpr int kLaneAddMax = 28;
+// Record gradient r (in the order of kRecGrad) from a splat's sums x and its staged H.
+__device__ __forceinline__ float record_gradient(int r, const double* x, const float4& g1,
+                                                 const float4& g2, float lp_scale) {
+  if (r < 7) return (float)x[r];
+  if (r == 9) return (float)x[11];
+  // d c2: minus the low-pass term's and rho's adjoints of the offset
+  const bool y = r == 8;
+  const float lp = 2.f * lp_scale * (float)x[y ? 10 : 9];
+  return -lp - (float)x[7] * (y ? g1.y : g1.x) - (float)x[8] * (y ? g1.w : g1.z) -
+         (float)x[6] * (y ? g2.y : g2.x);
+}
 
-// Grids of several sides (MIXED) need a few more registers: at 7 waves they spilled 28-40
-// bytes, and 6 waves measured faster (sides {2, 4, 8} at 1M splats and 1080p: backward 1.567
-// against 1.605 ms).
-template <int N, int B, bool MIXED>
-constexpr int bwd_min_waves() { return (B <= 8 && N <= 8) ? (MIXED ? 6 : 7) : 1; }
+// Wave steps that blended at most this many pixels skip the cell grouping. Backward ms for
+// thresholds 8 / 16 / 20 / 28 / 40: 1M splats at 1080p 1.037 / 1.032 / 1.031 / 1.043 / 1.066, 3M
+// splats at 4 x 1080p 13.65 / 13.23 / 13.15 / 12.89 / 12.64, 100k splats at 800x800 0.673 /
+// 0.652 / 0.640 / 0.629 / 0.623.
+constexpr int kLaneAddMax = 24;
 
-// Batches whose geometry one staging pass prepares: as many as the workgroup's threads can
-// stage at once. A workgroup has 64 threads per wave block and a batch needs B per block, so
-// that is 64 / B whatever the tile shape. The staging pass is on every wave's path (the waves
-// wait for it at the barrier), so fewer, fuller passes shorten the walk: at 1M splats and
-// 1080p the backward took 1.540 ms staging every batch on its own (32 of one wave's 64 lanes
-// busy), 1.473 / 1.448 / 1.420 ms staging 2 / 4 / 8 batches at once; at 3M splats on four
-// 1080p views 16.82 / 15.95 / 15.60 / 15.50 ms. For 16 x 16 grids LDS decides instead: a ring
-// of 4 batches (16 splats) rather than 16 takes the workgroup from 37 to 32 KB, five per CU
-// rather than four; backward at 1M splats and 1080p 2.59 -> 2.36 ms (sides {4, 8, 16}:
-// 2.83 -> 2.62; a ring of 8 batches: 2.65 and 2.91).
+// Occupancy target: 7 waves per SIMD (at most 72 VGPRs; the kernels take 71-73 without scratch),
+// which the LDS also allows, see bwd_batch; 8 (64 VGPRs) spilled: 1M splats at 1080p 1.10 against
+// 1.03 ms, 3M splats at 4 x 1080p 14.7 against 13.2.
 template <int N, int B>
-constexpr int bwd_stage_ahead() { return N >= 16 ? 4 : 64 / B; }
+constexpr int bwd_min_waves() {
+  return N <= 2 || (N == 4 && B <= 16) || (N == 8 && B <= 6) ? 7 : N == 4 ? 5 : 1;
+}
+
+// Splats per batch: the number asked for, or fewer where that lets another workgroup share a
+// CU's 160 KB of LDS. 8 x 8 grids hold 2.8 KB per splat (texels and 64-bit sums) beside the
+// pass's 6 KB of geometry: six splats are 22.5 KB, seven workgroups; 4 / 6 / 8 splats took 1.047 /
+// 1.040 / 1.132 ms at 1M splats and 1080p and 13.20 / 12.76 / 14.27 at 3M splats on four 1080p
+// views. 4 x 4 grids, 16 uneven views of 1M splats: 8 / 12 / 16 / 32 splats 6.64 / 7.51 / 6.41 /
+// 7.26 ms. 16 x 16 grids: 1 / 2 / 3 splats 2.81 / 2.10 / 2.16 ms.
+template <int N>
+constexpr int bwd_batch(int asked) {
+  return N >= 16 ? 2 : N == 8 && asked == 8 ? 6 : N == 4 && asked == 32 ? 16 : asked;
+}
+
+// Entries per pass: half a pass for 16 x 16 grids, whose 3 KB less of geometry lets six workgroups
+// share a CU instead of five (backward at 1M splats and 1080p 2.10 -> 1.83 ms).
+template <int N>
+constexpr int bwd_pass_entries() { return N >= 16 ? 32 : kPassEntries; }
+
+// Lanes that flush one splat's sums: a whole wave, or sixteen lanes where the grid is small.
+template <int N>
+constexpr int flush_lanes() { return N >= 4 ? 64 : 16; }
 
 // Depth-prefix split: on a tile that the prefix left open the block first walks the rest
 // pass's list (the later splats) and then, with each pixel's T and S carried over in
@@ -189,28 +244,23 @@ constexpr int bwd_stage_ahead() { return N >= 16 ? 4 : 64 / B; }
 // MIXED: each splat has a grid side of its own (at most N), read from p.grid_n; its texel
 // gradients go to its own n x n grid at p.grid_at.
 template <int N, bool BF16, int B, bool MIXED>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(bwd_min_waves<N, B, MIXED>())))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(bwd_min_waves<N, B>())))
 blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__ rec,
                  PairList first, PairList rest, const uint32_t* __restrict__ open_bits,
                  const void* __restrict__ textures, BlendParams p,
                  const float* __restrict__ T_final, const float* __restrict__ d_rgb,
                  float* __restrict__ d_rec, float* __restrict__ d_tex) {
   constexpr int TEXG = 3 * N * N;
-  // Per-splat geometry and indices of AHEAD batches (slot k holds [k B, (k + 1) B)): every
-  // AHEAD-th batch stages its own and the next AHEAD - 1 batches' geometry in one pass of the
-  // staging threads.
-  constexpr int AHEAD = bwd_stage_ahead<N, B>();
-  __shared__ GeoLds<AHEAD * B> s_geo;
-  __shared__ uint8_t s_reach[4][AHEAD * B];  // [wave block][staged splat]: may reach the block
-  __shared__ int32_t s_splat[AHEAD * B];
-  __shared__ uint32_t s_recid[AHEAD * B];
+  constexpr int PE = bwd_pass_entries<N>();
+  __shared__ GeoLds<PE> s_geo;
   __shared__ float4 s_tex[B * TexLayout<N>::kPerSplat];
-  __shared__ __attribute__((aligned(16))) float s_gtex[B * TEXG];
-  __shared__ float s_sum[B * kSums];  // per splat
+  __shared__ __attribute__((aligned(16))) double s_gtex[B * TEXG];  // per slot
+  __shared__ double s_sum[B * kSums];
+  // the waves' votes of a pass, of which two can be in use at a time (a wave may vote on the
+  // next pass while another still reads this one's)
+  __shared__ uint64_t s_mask[2][4];
+  __shared__ uint8_t s_list[PE];
   __shared__ uint32_t s_tile_last;
-  __shared__ int32_t s_gn[MIXED ? AHEAD * B : 1];
-  __shared__ float4 s_gc[MIXED ? AHEAD * B : 1];
-  __shared__ int64_t s_toff[MIXED ? AHEAD * B : 1];
 
   const int tile = tile_of_block(p);
   if (tile >= p.total_tiles) return;
@@ -228,16 +278,15 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
   const int waves_x = p.tile_w >> 3;
   const int n_waves = nthr >> 6;
   const int bx = (w % waves_x) * 8, by = (w / waves_x) * 8;
-  const int lxi = bx + (lane & 7);
   // pixel centres relative to the wave block's centre (exact half-integers); the block centre
   // relative to the tile's (wave-uniform integers)
-  const float lx = (float)(lane & 7) - 3.5f;
+  const float lx = (float)(lane & 7) - 3.5f, ly = (float)(lane >> 3) - 3.5f;
   const int tcx = tile_x0 + (p.tile_w >> 1), tcy = tile_y0 + (p.tile_h >> 1);
-  const float bcx = (float)(tile_x0 + bx + 4 - tcx), bcy = (float)(tile_y0 + by + 4 - tcy);
-  const float ly = (float)(lane >> 3) - 3.5f;
+  const int kbx = tile_x0 + bx, kby = tile_y0 + by;  // the wave block's first pixel
+  const float bcx = (float)(kbx + 4 - tcx), bcy = (float)(kby + 4 - tcy);
   // packed index of the lane's pixel, or -1 outside the view (recomputed when needed)
   auto pixel_index = [&]() -> int64_t {
-    const int px = tile_x0 + lxi, py = tile_y0 + by + (lane >> 3);
+    const int px = kbx + (lane & 7), py = kby + (lane >> 3);
     return (px < V.W && py < V.H) ? (int64_t)V.pix_base + (int64_t)py * V.W + px : -1;
   };
   PixState ps;
@@ -253,262 +302,285 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
     }
     ps.Sg = ps.T * (ps.g0 * p.bg[0] + ps.g1 * p.bg[1] + ps.g2 * p.bg[2]);
   }
-  // which wave total each lane receives from the reductions below
-  int rec_slot, tex_slot;
-  bool rec_owner, tex_owner;
-  const SwapSides sides = swap_sides();
-  wave_scatter_slot<kSums>(sides, rec_slot, rec_owner);
-  // texel sums: the three channels of each of the four cell corners (one corner when N = 1);
-  // tex_off is the lane's value's offset from the cell's first channel
-  constexpr int KT = N == 1 ? 3 : 12;
-  wave_scatter_slot<KT>(sides, tex_slot, tex_owner);
-  const int tex_off = 3 * ((tex_slot / 3 & 1) + (tex_slot / 6) * N) + tex_slot % 3;
+  // the sum that row_sums leaves in this lane: its place among a splat's record sums, and its
+  // offset from the first texel's first channel in the three kinds of texel group (four corners;
+  // two texels along v, or along u; one texel), one byte each
+  const int rl = lane & 15;
+  // (the record sums' places: after row_sums, and after ordered_sums in the second byte)
+  int rec_slots;
+  {
+    const SwapSides sides = swap_sides();
+    rec_slots = (row_slot(kSums, rl) & 255) | ordered_slot(sides.halves, sides.rows, rl) << 8;
+  }
+  uint32_t tex_off;
+  {
+    const int s12 = row_slot(12, rl), s6 = row_slot(6, rl), s3 = row_slot(3, rl);
+    const uint32_t o12 = (uint32_t)(3 * ((s12 / 3 & 1) + (s12 / 6) * N) + s12 % 3) & 255u;
+    const uint32_t o6v = (uint32_t)s6 & 255u;  // 3 (s6 / 3) + s6 % 3
+    const uint32_t o6u = (uint32_t)(3 * (s6 / 3) * N + s6 % 3) & 255u;
+    tex_off = o12 | o6v << 8 | o6u << 16 | ((uint32_t)s3 & 255u) << 24;
+  }
 
   // the per-batch LDS sums start at zero; each batch's flush clears what it read
   // (the first barrier of the list loop orders these stores before any add)
-  for (int e = tid; e < B * TEXG; e += nthr) s_gtex[e] = 0.f;
-  for (int e = tid; e < B * kSums; e += nthr) s_sum[e] = 0.f;
+  for (int e = tid; e < B * TEXG; e += nthr) s_gtex[e] = 0.0;
+  for (int e = tid; e < B * kSums; e += nthr) s_sum[e] = 0.0;
+  int parity = 0;
 
 #pragma unroll 1
   for (int li = tile_open ? 0 : 1; li < 2; ++li) {
     const PairList L = li == 0 ? rest : first;
     const uint32_t* __restrict__ pair_vals = L.pair_vals;
     const uint32_t start = L.ranges[2 * tile];
+    uint32_t wave_last;  // one past the last pair that some pixel of the wave blended
     {
       const int64_t pix = pixel_index();
       ps.last = pix >= 0 ? L.n_last[pix] : start;
+      uint32_t m = ps.last;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t o = (uint32_t)__shfl_xor((int)m, d, 64);
+        m = o > m ? o : m;
+      }
+      wave_last = __builtin_amdgcn_readfirstlane(m);
     }
-
     __syncthreads();  // every thread has read the previous list's bound
     if (tid == 0) s_tile_last = start;
     __syncthreads();
-    atomicMax(&s_tile_last, ps.last);  // largest bound over the tile's pixels
+    if (lane == 0) atomicMax(&s_tile_last, wave_last);
     __syncthreads();
-    const uint32_t tile_last = s_tile_last;
+    const uint32_t tile_last = __builtin_amdgcn_readfirstlane(s_tile_last);
 
-    // One staging pass: the geometry of the AHEAD batches that end at pend, into slots
-    // [0, AHEAD B).
-    auto stage_geometry = [&](uint32_t pend) {
-      // thread c stages splat c mod B of batch h = c / (B n_waves) from this one (h = 0 is
-      // this batch; h < AHEAD since the workgroup has 64 n_waves threads) for wave block
-      // (c / B) mod n_waves (n_waves is 1, 2 or 4), geometry centred on that block, and tests
-      // whether it can reach the block
-      // (recomputed per pass from an opaque copy of the thread index: hoisted out of the
-      // loop, these indices would hold registers across the reverse walk)
-      int t = tid;
-      __asm__ volatile("" : "+v"(t));
-      const int j = t & (B - 1), b = (t / B) & (n_waves - 1),
-                h = (t / B) >> __builtin_ctz((unsigned)n_waves);
-      // batch h is [pend - min(rem, (h + 1) B), pend - min(rem, h B))
-      const uint32_t rem = pend - start;
-      const uint32_t o0 = (uint32_t)(h * B) < rem ? (uint32_t)(h * B) : rem;
-      const uint32_t o1 = (uint32_t)((h + 1) * B) < rem ? (uint32_t)((h + 1) * B) : rem;
-      const uint32_t hstart = pend - o1;
-      const int hnb = (int)(o1 - o0);
-      if (h < AHEAD && j < hnb) {
-        const int jj = h * B + j;
-        const uint32_t r = pair_vals[hstart + j];
-        const SplatRec R = rec[r];
-        const int kbx = tile_x0 + (b % waves_x) * 8, kby = tile_y0 + (b / waves_x) * 8;
-        const StagedGeo g = stage_geo(R, kbx + 4, kby + 4, tcx, tcy);
-        s_geo.store(b, jj, g);
-        s_reach[b][jj] = block_may_contribute(g, (float)(kbx + 4 - tcx),
-                                              (float)(kby + 4 - tcy), kbx, kby, p)
-                             ? 1
-                             : 0;
-        if (b == 0) {
-          s_splat[jj] = R.splat;
-          s_recid[jj] = r;
-          if (MIXED) {
-            const int n = grid_side<N>(p, r - rec_base);
-            s_gn[jj] = n;
-            s_gc[jj] = grid_consts(n, p.sigma);
-            s_toff[jj] = p.grid_at[r - rec_base];
-          }
+    for (uint32_t pend = tile_last; pend > start;) {
+      // a pass: entries [pbase, pend) of the list, one per lane
+      const uint32_t pbase = pend - start > (uint32_t)PE ? pend - (uint32_t)PE : start;
+      uint64_t mine = 0;
+      EntryGrid eg{0u, 1, 0.f, 0};
+      // wave 0 also stores what the blocks share of a splat's geometry
+      if (w == 0 || pbase < wave_last) {
+        bool may = false;
+        const int e = fresh_tid() & 63;
+        const uint32_t idx = pbase + (uint32_t)e;
+        if (idx < pend) {
+          const SplatRec R = rec[pair_vals[idx]];
+          const StagedGeo g = stage_geo(R, kbx + 4, kby + 4, tcx, tcy);
+          s_geo.store(w, e, g);
+          may = idx < wave_last && block_may_contribute(g, bcx, bcy, kbx, kby, p);
         }
+        mine = ballot(may);
       }
-    };
-    // Texels of the batch [bs, bs + n), whose geometry is in slot offset sof (staged by the
-    // pass's geometry launch, with a barrier between them).
-    auto stage_batch_texels = [&](uint32_t bs, int n, int sof) {
-      if constexpr (MIXED)
-        stage_texels_mixed<N, BF16, true>(textures, pair_vals + bs, rec_base, n, s_tex, p,
-                                          s_gn + sof, s_toff + sof);
-      else
-        stage_texels<N, BF16>(textures, pair_vals + bs, rec_base, n, s_tex, p.spec);
-    };
-    // The first batch's geometry pass and texels; later batches stage theirs while the batch
-    // before them flushes its sums (below).
-    if (tile_last > start) {
-      stage_geometry(tile_last);
-      if constexpr (MIXED) __syncthreads();  // sides and offsets of the batch's grids
-      const uint32_t bs = (tile_last - start) > (uint32_t)B ? tile_last - (uint32_t)B : start;
-      stage_batch_texels(bs, (int)(tile_last - bs), 0);
+      if constexpr (MIXED) {
+        const uint32_t idx = pbase + (uint32_t)lane;
+        if (idx < pend) eg = entry_grid<N>(p, pair_vals[idx], rec_base);
+      }
+      if (lane == 0) s_mask[parity][w] = mine;
       __syncthreads();
-    }
-    int slot = 0;  // slot of the batch's geometry: the batch's index in the list mod AHEAD
-    for (uint32_t bend = tile_last; bend > start;) {
-      const uint32_t bstart = (bend - start) > (uint32_t)B ? bend - (uint32_t)B : start;
-      const int nb = (int)(bend - bstart);
-      const int so = slot * B;
+      const PassVotes votes =
+          pass_votes<true>(mine, s_mask[parity], n_waves, lane, s_list);
+      parity ^= 1;
 
-      // splats of this batch that can reach the wave's block, walked back to front
-      const bool may = lane < nb && s_reach[w][so + lane] != 0;
-      uint64_t todo = ballot(may);
-      while (todo != 0) {
-        const int j = 63 - (int)__builtin_clzll(todo);
-        todo &= ~(1ull << j);
-        const uint32_t jg = bstart + (uint32_t)j;
-        if (ballot(jg < ps.last) == 0) continue;
-        const StagedGeo g = s_geo.load(w, so + j);
-        const float4* tex = s_tex + j * TexLayout<N>::kPerSplat;
-        const PixelEval e = eval_splat(g, lx, ly, lx + bcx, ly + bcy, p);
-        const bool act = (jg < ps.last) && e.hit;
-        const uint64_t pend = ballot(act);  // lanes that blended this splat
-        if (pend == 0) continue;            // no pixel of the wave blended it
-        PixOut po;
-        if constexpr (MIXED) {
-          const float4 gc = s_gc[so + j];
-          pixel_step<N, true>(g, tex, e, act, ps, p, po, gc);
-        } else {
-          pixel_step<N>(g, tex, e, act, ps, p, po);
-        }
+      auto stage_batch = [&](int b0) {
+        const int n = votes.total - b0 < B ? votes.total - b0 : B;
+        if constexpr (MIXED)
+          stage_texels_mixed<N, BF16>(textures, s_list + b0, n, s_tex, p.spec, eg);
+        else
+          stage_texels<N, BF16, true>(textures, pair_vals + pbase, s_list + b0, rec_base, n,
+                                      s_tex, p.spec);
+      };
+      if (votes.total > 0) {
+        stage_batch(0);
+        __syncthreads();
+      }
+      uint64_t ahead = ~0ull;  // entries that no batch has taken yet
+      for (int b0 = 0; b0 < votes.total; b0 += B) {
+        const int nb = votes.total - b0 < B ? votes.total - b0 : B;
+        const uint64_t batch =
+            ahead & (~0ull << __builtin_amdgcn_readfirstlane((int)s_list[b0 + nb - 1]));
+        ahead &= ~batch;
+        // the batch's splats that can reach the wave's block, walked back to front
+        uint64_t todo = votes.mine & batch;
+        while (todo != 0) {
+          const int j = 63 - (int)__builtin_clzll(todo);
+          todo &= ~(1ull << j);
+          const uint32_t jg = pbase + (uint32_t)j;
+          const uint64_t live = ballot(jg < ps.last);
+          const StagedGeo g = s_geo.load(w, j);
+          const PixelEval e = eval_splat(g, lx, ly, lx + bcx, ly + bcy, p);
+          // lanes that blended this splat (a vote per compare: each is a lane mask already)
+          const uint64_t pend_px = live & ballot(e.r2 != 0.0f) & ballot(e.alpha >= p.alpha_min);
+          if (pend_px == 0) continue;  // no pixel of the wave blended it
+          const bool act = __builtin_amdgcn_inverse_ballot_w64(pend_px);
+          // the splat's slot: taken slots of the pass after this entry's
+          const uint64_t after = votes.any >> 1 >> j;
+          const int slot = __builtin_popcount((uint32_t)after) +
+                           __builtin_popcount((uint32_t)(after >> 32)) - b0;
+          const float4* tex = s_tex + slot * TexLayout<N>::kPerSplat;
+          PixOut po;
+          int n_side = N;
+          float4 gc = make_float4(0.f, 0.f, 0.f, 0.f);
+          if constexpr (MIXED) {
+            n_side = __builtin_amdgcn_readlane(eg.n, j);
+            const float hi = (float)(n_side - 1);
+            gc = make_float4(
+                __int_as_float(__builtin_amdgcn_readlane(__float_as_int(eg.scale), j)), 0.5f * hi,
+                hi, __int_as_float(n_side > 2 ? n_side - 2 : 0));
+          }
+          const float inv = act ? e.inv : 0.f, u = act ? e.u : 0.f, v = act ? e.v : 0.f;
+          po.in_u = ballot(fabsf(u) < p.sigma);  // (-sigma, sigma): one compare with |u|
+          po.in_v = ballot(fabsf(v) < p.sigma);
+          const uint64_t low_pass = pend_px & ~ballot(e.uv_branch);
+          // Sums of the per-splat scalars; the owner lanes of a total add it to the splat's slot.
+          if (N > 1 && (low_pass & (po.in_u | po.in_v)) != 0) {
+            pixel_step<N, MIXED, true>(tex, e, inv, u, v, act, ps, p, po, gc);
+            lds_add<kOrderedOwners>(s_sum, kSums * slot, rec_slots >> 8, ordered_sums(po.sum));
+          } else {
+            pixel_step<N, MIXED, false>(tex, e, inv, u, v, act, ps, p, po, gc);
+            lds_add<row_owners(kSums)>(s_sum, kSums * slot, rec_slots & 255, row_sums(po.sum));
+          }
 
-        // Wave sums of the per-splat scalars; the one lane that owns each total adds it to the
-        // splat's LDS slot.
-        {
-          const float tot = wave_reduce_scatter<kSums>(po.sum);
-          if (rec_owner) atomicAdd(&s_sum[j * kSums + rec_slot], tot);
-        }
-
-        // Texel gradients, grouped by cell over all pixels of the wave. A wave step that blended
-        // few pixels (small or distant splats) adds each pixel's bilinear corners to LDS
-        // directly; up to kLaneAddMax lanes this costs less than group passes.
-        float* const gb = s_gtex + j * TEXG;
-        if (__builtin_popcountll(pend) <= kLaneAddMax) {
-          if (act) {
-            const int iu = cell_row<N>(po.cell), k00 = po.cell - iu;
+          // Texel gradients, grouped by cell over all pixels of the wave. A wave step that
+          // blended few pixels (small or distant splats) adds each pixel's bilinear corners to
+          // LDS directly; up to kLaneAddMax lanes this costs less than group passes.
+          const int base = TEXG * slot;
+          if constexpr (N == 1) {
+            float red[3] = {po.wgt * ps.g0, po.wgt * ps.g1, po.wgt * ps.g2};
+            const float tot = row_sums(red);
+            lds_add<row_owners(3)>(s_gtex, base, (int)(tex_off >> 24), tot);
+          } else if (__builtin_popcount((uint32_t)pend_px) +
+                         __builtin_popcount((uint32_t)(pend_px >> 32)) <=
+                     kLaneAddMax) {
+            if (act) {
+              double* const gb = s_gtex + base;
+              const int k00 = po.cell - cell_row<N>(po.cell);
+              float wc[4];
+              corner_weights(po.wgt, po.fu, po.fv, wc);
 #pragma unroll
-            for (int q = 0; q < KT / 3; ++q) {
-              const float wq = po.w[q];
-              if (wq != 0.f) {
-                float* dst = gb + 3 * (k00 + (q & 1) + (q >> 1) * N);
-                atomicAdd(dst + 0, wq * ps.g0);
-                atomicAdd(dst + 1, wq * ps.g1);
-                atomicAdd(dst + 2, wq * ps.g2);
+              for (int q = 0; q < 4; ++q) {
+                if (wc[q] != 0.f) {
+                  double* dst = gb + 3 * (k00 + (q & 1) + (q >> 1) * N);
+                  atomicAdd(dst + 0, (double)(wc[q] * ps.g0));
+                  atomicAdd(dst + 1, (double)(wc[q] * ps.g1));
+                  atomicAdd(dst + 2, (double)(wc[q] * ps.g2));
+                }
+              }
+            }
+          } else {
+            // A group is every pending lane of the first pending lane's cell, so the loop ends
+            // within 64 passes. Most groups lie where a coordinate is clamped to the grid's
+            // border (with sigma = 0.5 the grid covers only the splat's core): there the weights
+            // of the clamped axis are 0 and 1, the same for the whole group, and only two texels
+            // or one take a sum (at 1M splats and 1080p one texel in 25 % of the groups, two in
+            // 61 %). The clamped end follows from the cell when the axis has at least two
+            // cells. Other lanes contribute through a zero weight.
+            const uint64_t in_u = n_side > 2 ? po.in_u : ~0ull,
+                           in_v = n_side > 2 ? po.in_v : ~0ull;
+            const int key = act ? po.cell : -1;
+#pragma unroll 1
+            for (uint64_t left = pend_px; left != 0;) {
+              const int lead = __builtin_amdgcn_readlane(key, (int)__builtin_ctzll(left));
+              const uint64_t members = ballot(key == lead);
+              left &= ~members;
+              const float wm = __builtin_amdgcn_inverse_ballot_w64(members) ? po.wgt : 0.f;
+              const int lu = cell_row<N>(lead), lv = lead - lu * TexLayout<N>::kRow;
+              // the texel row and column of a clamped coordinate
+              const int bu = lu == 0 ? 0 : n_side - 1, bv = lv == 0 ? 0 : n_side - 1;
+              if ((members & in_v) == 0) {
+                if ((members & in_u) == 0) {
+                  float red[3] = {wm * ps.g0, wm * ps.g1, wm * ps.g2};
+                  const float tot = row_sums(red);
+                  lds_add<row_owners(3)>(s_gtex, base + 3 * (bu * N + bv), (int)(tex_off >> 24), tot);
+                } else {
+                  const float w1 = wm * po.fu, w0 = __builtin_fmaf(-wm, po.fu, wm);
+                  float red[6] = {w0 * ps.g0, w0 * ps.g1, w0 * ps.g2,
+                                  w1 * ps.g0, w1 * ps.g1, w1 * ps.g2};
+                  const float tot = row_sums(red);
+                  lds_add<row_owners(6)>(s_gtex, base + 3 * (lu * N + bv), (int)(tex_off >> 16 & 255u), tot);
+                }
+              } else if ((members & in_u) == 0) {
+                const float w1 = wm * po.fv, w0 = __builtin_fmaf(-wm, po.fv, wm);
+                float red[6] = {w0 * ps.g0, w0 * ps.g1, w0 * ps.g2,
+                                w1 * ps.g0, w1 * ps.g1, w1 * ps.g2};
+                const float tot = row_sums(red);
+                lds_add<row_owners(6)>(s_gtex, base + 3 * (bu * N + lv), (int)(tex_off >> 8 & 255u), tot);
+              } else {
+                float wc[4], red[12];
+                corner_weights(wm, po.fu, po.fv, wc);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                  red[3 * q] = wc[q] * ps.g0;
+                  red[3 * q + 1] = wc[q] * ps.g1;
+                  red[3 * q + 2] = wc[q] * ps.g2;
+                }
+                const float tot = row_sums(red);
+                lds_add<row_owners(12)>(s_gtex, base + 3 * (lu * N + lv), (int)(tex_off & 255u), tot);
               }
             }
           }
-        } else {
-          // Every group takes at least its lead lane, so the loop ends within 64 passes. A bound
-          // of four passes with per-lane LDS adds for the remaining lanes measured 1.80 ms at
-          // 1M splats and 1080p (10 % of wave steps have more than four cells), eight passes
-          // 1.73 ms: the per-lane adds, serialised on shared addresses, cost more than passes.
-          // Each pending lane carries its cell as the group key, -1 once its group is taken;
-          // non-members contribute through zeroed weights.
-          int key = act ? po.cell : -1;
-#pragma unroll 1
-          for (uint64_t left = pend; left != 0;) {
-            const int lead = __builtin_amdgcn_readlane(key, (int)__builtin_ctzll(left));
-            const bool in = key == lead;
-            key = in ? -1 : key;
-            left &= ~ballot(in);
-            // all corners and channels in one transposing wave reduction, so that one lane per
-            // value adds it to LDS: one add instruction per group
-            float red[KT];
-#pragma unroll
-            for (int q = 0; q < KT / 3; ++q) {
-              const float wq = in ? po.w[q] : 0.f;
-              red[3 * q] = wq * ps.g0;
-              red[3 * q + 1] = wq * ps.g1;
-              red[3 * q + 2] = wq * ps.g2;
+        }
+        __syncthreads();
+        // Flush: FL lanes take a slot, its sums go to global memory with one float atomic per
+        // non-zero sum (consecutive lanes, consecutive addresses) and are left zero for the
+        // next batch.
+        constexpr int FL = flush_lanes<N>(), PER = 64 / FL;
+        const int ft = fresh_tid() & 63, fl = ft & (FL - 1);
+        for (int j = w * PER + (PER > 1 ? ft / FL : 0); j < nb; j += n_waves * PER) {
+          int entry = (int)s_list[b0 + j];
+          if constexpr (PER == 1) entry = __builtin_amdgcn_readfirstlane(entry);
+          const uint32_t r = pair_vals[pbase + (uint32_t)entry];
+          double* const gs = s_gtex + j * TEXG;
+          if (p.d_spec) {
+            // the view-dependent colour of a record is added to every texel of its lookup, so
+            // its adjoint over the tile is the sum of the record's texel sums, one per channel
+            float sc[3] = {0.f, 0.f, 0.f};
+            for (int t = fl; t < N * N; t += FL) {
+              sc[0] += (float)gs[3 * t];
+              sc[1] += (float)gs[3 * t + 1];
+              sc[2] += (float)gs[3 * t + 2];
             }
-            const float tot = wave_reduce_scatter<KT>(red);
-            if (tex_owner) atomicAdd(gb + tex_off + 3 * (lead - cell_row<N>(lead)), tot);
+            if constexpr (PER == 1) wave_sum_all<3>(sc);
+            else row_sum_all<3>(sc);
+            const float x = fl == 0 ? sc[0] : fl == 1 ? sc[1] : sc[2];
+            if (fl < 3 && x != 0.f) atomicAdd(&p.d_spec[4 * (int64_t)r + fl], x);
           }
-        }
-      }
-      __syncthreads();
-      // the view-dependent colour of a record is added to every texel of its lookup, so its
-      // adjoint over the tile is the sum of the record's texel sums, one per channel: each
-      // wave sums the N^2 texels of a (splat, channel) pair at a time
-      if (p.d_spec) {
-        for (int jc = w; jc < 3 * nb; jc += nthr >> 6) {
-          const int j = jc / 3, c = jc - 3 * j;
-          float x = 0.f;
-          for (int t = lane; t < N * N; t += 64) x += s_gtex[j * TEXG + 3 * t + c];
-          x = wave_sum(x);
-          if (lane == 0 && x != 0.f) atomicAdd(&p.d_spec[4 * (int64_t)s_recid[so + j] + c], x);
-        }
-        __syncthreads();  // every texel sum has been read before the flush clears it
-      }
-      // flush the batch's sums, leaving them zero for the next batch
-      if constexpr (MIXED) {
-        // the N x N sums hold splat j's n x n grid in rows and columns [0, n): one wave per
-        // splat, lane i taking values i, i + 64, ... of the grid's 3 n^2
-        for (int j = w; j < nb; j += nthr >> 6) {
-          const int n = s_gn[so + j];
-          for (int i = lane; i < 3 * n * n; i += 64) {
-            const int t = i / 3, c = i - 3 * t, iu = div_side(t, n), iv = t - iu * n;
-            float* const sum = &s_gtex[j * TEXG + 3 * (iu * N + iv) + c];
-            const float x = *sum;
-            *sum = 0.f;
-            if (x != 0.f) atomicAdd(&d_tex[3 * s_toff[so + j] + i], x);
+          if constexpr (MIXED) {
+            // the N x N sums hold the splat's n x n grid in rows and columns [0, n): lane i takes
+            // values i, i + 64, ... of the grid's 3 n^2
+            const int n = __builtin_amdgcn_readlane(eg.n, entry);
+            float* const dst = d_tex + readlane64(eg.first, entry);
+            for (int i = fl; i < 3 * n * n; i += 64) {
+              const int t = i / 3, c = i - 3 * t, iu = div_side(t, n), iv = t - iu * n;
+              double* const sum = gs + 3 * (iu * N + iv) + c;
+              const double x = *sum;
+              if (x != 0.0) {
+                *sum = 0.0;
+                atomicAdd(dst + i, (float)x);
+              }
+            }
+          } else {
+            float* const dst = d_tex + (int64_t)(r - rec_base) * TEXG;
+            for (int k = 0; k < (TEXG + FL - 1) / FL; ++k) {
+              const int i = k * FL + fl;
+              const double x = i < TEXG ? gs[i] : 0.0;
+              if (x != 0.0) {
+                gs[i] = 0.0;
+                atomicAdd(dst + i, (float)x);
+              }
+            }
           }
+          // each lane reads the sums its record gradient needs, and only then are they cleared
+          const float x = fl < kRecGrad ? record_gradient(fl, &s_sum[j * kSums], s_geo.g1[entry],
+                                                          s_geo.g2[entry], p.lp_scale)
+                                        : 0.f;
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          if (fl < kSums) s_sum[j * kSums + fl] = 0.0;
+          if (x != 0.f) atomicAdd(&d_rec[(int64_t)r * kRecGrad + fl], x);
         }
-      } else if constexpr (TEXG % 4 == 0) {
-        // four sums per 16-byte LDS read; one global atomic per non-zero sum
-        constexpr int TEXG4 = TEXG / 4;
-        float4* g4 = reinterpret_cast<float4*>(s_gtex);
-        for (int e = tid; e < nb * TEXG4; e += nthr) {
-          const float4 x = g4[e];
-          g4[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (x.x != 0.f || x.y != 0.f || x.z != 0.f || x.w != 0.f) {
-            const int j = e / TEXG4, r = 4 * (e - j * TEXG4);
-            float* dst = d_tex + (int64_t)s_splat[so + j] * TEXG + r;
-            if (x.x != 0.f) atomicAdd(dst + 0, x.x);
-            if (x.y != 0.f) atomicAdd(dst + 1, x.y);
-            if (x.z != 0.f) atomicAdd(dst + 2, x.z);
-            if (x.w != 0.f) atomicAdd(dst + 3, x.w);
-          }
-        }
-      } else {
-        for (int e = tid; e < nb * TEXG; e += nthr) {
-          const float x = s_gtex[e];
-          s_gtex[e] = 0.f;
-          if (x != 0.f) {
-            const int j = e / TEXG, r = e - j * TEXG;
-            atomicAdd(&d_tex[(int64_t)s_splat[so + j] * TEXG + r], x);
-          }
-        }
+        // the next batch's texels load while the atomics above drain
+        if (b0 + B < votes.total) stage_batch(b0 + B);
+        __syncthreads();
       }
-      // sixteen lanes of one wave per splat: each reads the sums its record gradient needs, and
-      // only then are they cleared
-      for (int e = tid; e < 16 * nb; e += nthr) {
-        const int j = e >> 4, r = e & 15;
-        const float x = r < kRecGrad ? record_gradient(r, &s_sum[j * kSums], s_geo.g1[so + j],
-                                                       s_geo.g2[so + j], p.lp_scale)
-                                     : 0.f;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        if (r < kSums) s_sum[j * kSums + r] = 0.f;
-        if (x != 0.f) atomicAdd(&d_rec[(int64_t)s_recid[so + j] * kRecGrad + r], x);
-      }
-      // the next batch: its texels (and, when it starts a staging pass, the pass's geometry)
-      // load while the atomics above drain
-      const int nslot = slot + 1 < AHEAD ? slot + 1 : 0;
-      if (bstart > start) {
-        const uint32_t nbs = (bstart - start) > (uint32_t)B ? bstart - (uint32_t)B : start;
-        if (nslot == 0) {
-          __syncthreads();  // the flush above has read the pass's splat and record indices
-          stage_geometry(bstart);
-          if constexpr (MIXED) __syncthreads();  // sides and offsets of the batch's grids
-        }
-        stage_batch_texels(nbs, (int)(bstart - nbs), nslot * B);
-      }
-      __syncthreads();
-      bend = bstart;
-      slot = nslot;
+      pend = pbase;
     }
   }  // lists
 }
@@ -525,16 +597,12 @@ hipError_t launch_np(const Plan& pl, const gb_splats& sp, const BlendParams& bp,
   hipLaunchKernelGGL((blend_bwd_kernel<N, BF16, BB, MIXED>), grid, block, 0, s, views, rec, \
                      first, rest, open_bits, sp.textures, bp, T_final, d_rgb, d_rec, d_tex)
   if constexpr (N >= 16) {
-    // the only batch built for N = 16: at 8 splats of 16 x 16 texels (texels and their
-    // gradient sums) a workgroup held 67 KB of LDS, two per CU; at 4 the backward at 1M
-    // splats and 1080p took 2.58 ms against 3.87 (grids of sides {4, 8, 16}: 2.84 against
-    // 4.48); a batch of 2 took 2.47 and 3.25
-    GBB_BWD_B(4);
+    GBB_BWD_B(bwd_batch<N>(4));
   } else {
     switch (pl.batch_bwd) {
-      case 8: GBB_BWD_B(8); break;
-      case 32: GBB_BWD_B(32); break;
-      default: GBB_BWD_B(16); break;
+      case 8: GBB_BWD_B(bwd_batch<N>(8)); break;
+      case 32: GBB_BWD_B(bwd_batch<N>(32)); break;
+      default: GBB_BWD_B(bwd_batch<N>(16)); break;
     }
   }
 #undef GBB_BWD_B

@@ -25,6 +25,7 @@ struct BlendParams {
   float alpha_min, alpha_max, t_min;
   float cull_alpha;   // 0.99 alpha_min: the per-wave cull's margin below alpha_min
   float lp_scale;     // 1 / (2 lowpass_var)
+  float lp_scale2;    // 2 lp_scale
   float bg[3];
   int32_t tile_w, tile_h;
   int32_t n_views;
@@ -102,7 +103,7 @@ __device__ __forceinline__ StagedGeo stage_geo(const SplatRec& r, int cx, int cy
   return s;
 }
 
-// LDS copy of a batch's staged geometry for the (at most four) wave blocks of a tile: g1 and
+// LDS copy of a pass's staged geometry for the (at most four) wave blocks of a tile: g1 and
 // g2 once per splat, g0 once per (block, splat). 96 bytes per splat; reading one (block,
 // splat) takes three 16-byte loads.
 template <int B>
@@ -138,27 +139,81 @@ struct TexLayout {
   __device__ static int at(int iu, int iv) { return (int)__umul24((unsigned)iu, kRow) + iv; }
 };
 
-// Copies the texels of `nb` staged splats into LDS as float4 (RGB + pad) per texel. The j-th
-// splat is pairs[j] - rec_base: a tile's pairs all hold records of the tile's view, so the
-// splat follows from the pair list alone and the texel loads need not wait for the staged
+// A staged texel as one 16-byte LDS read (5.6 cycles of the CU's LDS for a wave). Left to the
+// compiler, which sees that the pad is unused, it becomes a 12-byte read, which takes 9.1.
+__device__ __forceinline__ float4 load_texel(const float4* t) {
+  const float4 x = *t;
+  __asm__ volatile("" : : "v"(x.w));
+  return x;
+}
+
+// Entries (consecutive pairs of the tile's list) whose geometry one staging pass prepares: one
+// per lane of each wave, which tests them against its own pixel block.
+constexpr int kPassEntries = 64;
+
+// The part of a staging pass that every wave works out alike from the waves' votes: `mine` marks
+// the entries that can reach this wave's block, `any` those that can reach some block of the
+// tile. Only the latter are given texel slots, in batches, so that a splat whose screen
+// rectangle touches the tile but whose footprint does not (about half of them) costs a geometry
+// test and nothing more. list[slot] is the entry of each slot, by falling (REVERSE) or rising
+// entry index; every wave writes the same list and reads only what it has written itself.
+struct PassVotes {
+  uint64_t mine, any;
+  int total;  // set bits of any
+};
+
+template <bool REVERSE>
+__device__ __forceinline__ PassVotes pass_votes(uint64_t mine, const uint64_t* s_mask, int n_waves,
+                                                int lane, uint8_t* s_list) {
+  uint64_t any = s_mask[0];
+  for (int k = 1; k < n_waves; ++k) any |= s_mask[k];
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)any),
+                 hi = __builtin_amdgcn_readfirstlane((uint32_t)(any >> 32));
+  PassVotes v;
+  v.mine = mine;
+  v.any = (uint64_t)hi << 32 | lo;
+  v.total = __builtin_popcount(lo) + __builtin_popcount(hi);
+  if (__builtin_amdgcn_inverse_ballot_w64(v.any)) {
+    const int below = (int)mbcnt(v.any);
+    s_list[REVERSE ? v.total - 1 - below : below] = (uint8_t)lane;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  return v;
+}
+
+// The thread index as a value the compiler takes to be new: what a staging or flush phase
+// derives from it is then computed in that phase, and does not sit in registers through the
+// splat loop.
+__device__ __forceinline__ int fresh_tid() {
+  int t = (int)threadIdx.x;
+  __asm__ volatile("" : "+v"(t));
+  return t;
+}
+
+// Copies the texels of a batch of `nb` splats into LDS as float4 (RGB + pad) per texel. The
+// splat of slot j is pairs[list[j]] - rec_base: a tile's pairs all hold records of the tile's
+// view, so the splat follows from the pair list alone and the texel loads need not wait for the
 // records. For even N a splat's 3 N^2 channel values split into groups of 12 (four texels):
 // each thread moves whole groups, three 16-byte (float32) or 8-byte (bfloat16) loads in, four
 // LDS stores out.
-// With spec != null each texel also gets the record's view-dependent colour spec[pairs[j]]
+// With spec != null each texel also gets the record's view-dependent colour spec[record]
 // (the bilinear weights sum to one, so this adds that colour to the lookup).
-template <int N, bool BF16>
+// FRESH: the thread index through fresh_tid (the backward, which is short of registers).
+template <int N, bool BF16, bool FRESH>
 __device__ __forceinline__ void stage_texels(const void* __restrict__ textures,
                                              const uint32_t* __restrict__ pairs,
-                                             uint32_t rec_base, int nb, float4* s_tex,
-                                             const float4* __restrict__ spec) {
+                                             const uint8_t* list, uint32_t rec_base, int nb,
+                                             float4* s_tex, const float4* __restrict__ spec) {
   constexpr int per = 3 * N * N;  // channel values per splat
-  const int tid = threadIdx.x, nthr = blockDim.x;
+  const int tid = FRESH ? fresh_tid() : (int)threadIdx.x, nthr = blockDim.x;
   if constexpr ((per % 12) == 0) {
     constexpr int groups = per / 12;  // = N^2 / 4
     for (int gi = tid; gi < nb * groups; gi += nthr) {
       const int j = gi / groups, a = gi - j * groups;
-      const int64_t src = ((int64_t)(pairs[j] - rec_base) * groups + a) * 3;
-      const float4 sc = spec ? spec[pairs[j]] : make_float4(0.f, 0.f, 0.f, 0.f);
+      const uint32_t r = pairs[list[j]];
+      const int64_t src = ((int64_t)(r - rec_base) * groups + a) * 3;
+      const float4 sc = spec ? spec[r] : make_float4(0.f, 0.f, 0.f, 0.f);
       float v[12];
       if constexpr (BF16) {
         const uint2* t = reinterpret_cast<const uint2*>(textures) + src;
@@ -193,14 +248,15 @@ __device__ __forceinline__ void stage_texels(const void* __restrict__ textures,
   } else {
     for (int e = tid; e < nb * per; e += nthr) {
       const int j = e / per, r = e - j * per;
-      const int64_t k = (int64_t)(pairs[j] - rec_base);
+      const uint32_t id = pairs[list[j]];
+      const int64_t k = (int64_t)(id - rec_base);
       float x;
       if constexpr (BF16)
         x = bf16_to_f32(reinterpret_cast<const uint16_t*>(textures)[k * per + r]);
       else
         x = reinterpret_cast<const float*>(textures)[k * per + r];
       if (spec) {
-        const float4 sc = spec[pairs[j]];
+        const float4 sc = spec[id];
         x += (r % 3) == 0 ? sc.x : (r % 3) == 1 ? sc.y : sc.z;
       }
       const int t = r / 3, iu = t / N, iv = t - iu * N;
@@ -221,56 +277,58 @@ __device__ __forceinline__ int grid_side(const BlendParams& p, uint32_t k) {
   return min(max(p.grid_n[k], 1), N);
 }
 
-// Copies the texels of `nb` staged splats whose grids have sides of their own (at most N) into
-// the N x N LDS layout: splat j's n x n texels go to rows and columns [0, n). Wave w takes
-// splats w, w + nw, ...; lane q of the wave first loads the side, first value and
-// view-dependent colour (spec, nullable, added to each texel as in stage_texels) of the wave's
-// q-th splat, so that these loads of all the wave's splats are in flight together; then, splat
-// by splat, lane i moves texels i, i + 64, ... of the grid (three channel values in, one
-// 16-byte LDS store out: a third of the index arithmetic of moving single values). A
-// one-texel grid is also copied to (0, 1), (1, 0) and (1, 1), so that the bilinear lookup,
-// which reads the four corners of cell (0, 0) with weights (1, 0, 0, 0) there, reads finite
-// values.
-// FROM_LDS: each grid's side and first texel come from the staged copies s_gn / s_toff (the
-// backward, whose geometry pass staged them well before); otherwise they are read from
-// p.grid_n / p.grid_at for record pairs[j] - rec_base, so that the forward need not wait at a
-// barrier for the copies staged in the same phase.
-template <int N, bool BF16, bool FROM_LDS>
+// What each lane holds of its entry of the pass in a call with grids of several sides: the
+// record, the grid's side, its uv -> grid slope and its first value in the texture array. The
+// waves read an entry's values back with readlane (the entry is uniform over the wave).
+struct EntryGrid {
+  uint32_t rec;
+  int n;
+  float scale;
+  int64_t first;
+};
+
+// Slope of the uv -> grid map of an n-texel side, formed as the host forms it for a uniform
+// side (a call whose sides all equal N then matches the uniform path bit for bit).
+__device__ __forceinline__ float grid_scale(int n, float sigma) {
+  return (float)(n - 1) / (2.0f * sigma);
+}
+
+template <int N>
+__device__ __forceinline__ EntryGrid entry_grid(const BlendParams& p, uint32_t r,
+                                                uint32_t rec_base) {
+  EntryGrid g;
+  g.rec = r;
+  g.n = grid_side<N>(p, r - rec_base);
+  g.scale = grid_scale(g.n, p.sigma);
+  g.first = 3 * p.grid_at[r - rec_base];
+  return g;
+}
+
+__device__ __forceinline__ int64_t readlane64(int64_t x, int lane) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)x, lane),
+                 hi = (uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), lane);
+  return (int64_t)((uint64_t)hi << 32 | lo);
+}
+
+// Copies the texels of a batch of `nb` splats whose grids have sides of their own (at most N)
+// into the N x N LDS layout: a splat's n x n texels go to rows and columns [0, n). Wave w takes
+// slots w, w + nw, ...; lane i moves texels i, i + 64, ... of the grid (three channel values in,
+// one 16-byte LDS store out: a third of the index arithmetic of moving single values), with the
+// record's view-dependent colour (spec, nullable) added as in stage_texels. A one-texel grid is
+// also copied to (0, 1), (1, 0) and (1, 1), so that the bilinear lookup, which reads the four
+// corners of cell (0, 0) with weights (1, 0, 0, 0) there, reads finite values.
+template <int N, bool BF16>
 __device__ __forceinline__ void stage_texels_mixed(const void* __restrict__ textures,
-                                                   const uint32_t* __restrict__ pairs,
-                                                   uint32_t rec_base, int nb, float4* s_tex,
-                                                   const BlendParams& p, const int32_t* s_gn,
-                                                   const int64_t* s_toff) {
-  const int lane = threadIdx.x & 63, w = (int)(threadIdx.x >> 6), nw = (int)(blockDim.x >> 6);
-  const float4* __restrict__ spec = p.spec;
-  // lane q: the wave's q-th splat (nb <= 64 nw, so one lane per splat suffices)
-  int my_n = 1;
-  int64_t my_base = 0;
-  float4 my_sc = make_float4(0.f, 0.f, 0.f, 0.f);
-  const int jq = w + lane * nw;
-  if (jq < nb) {
-    const uint32_t r = pairs[jq];
-    if constexpr (FROM_LDS) {
-      my_n = s_gn[jq];
-      my_base = 3 * s_toff[jq];
-    } else {
-      my_n = grid_side<N>(p, r - rec_base);
-      my_base = 3 * p.grid_at[r - rec_base];
-    }
-    if (spec) my_sc = spec[r];
-  }
-  for (int q = 0; w + q * nw < nb; ++q) {
-    const int j = w + q * nw;
-    const int n = __builtin_amdgcn_readlane(my_n, q);
-    const int64_t base =
-        (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(my_base >> 32), q) << 32) |
-                  (uint32_t)__builtin_amdgcn_readlane((int)my_base, q));
-    float4 sc = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (spec)
-      sc = make_float4(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_sc.x), q)),
-                       __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_sc.y), q)),
-                       __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_sc.z), q)),
-                       0.f);
+                                                   const uint8_t* list, int nb, float4* s_tex,
+                                                   const float4* __restrict__ spec,
+                                                   const EntryGrid& eg) {
+  const int tid = fresh_tid(), lane = tid & 63, nw = (int)(blockDim.x >> 6);
+  for (int j = __builtin_amdgcn_readfirstlane(tid >> 6); j < nb; j += nw) {
+    const int e = __builtin_amdgcn_readfirstlane((int)list[j]);
+    const int n = __builtin_amdgcn_readlane(eg.n, e);
+    const int64_t base = readlane64(eg.first, e);
+    const float4 sc = spec ? spec[(uint32_t)__builtin_amdgcn_readlane((int)eg.rec, e)]
+                           : make_float4(0.f, 0.f, 0.f, 0.f);
     float4* dst = s_tex + j * TexLayout<N>::kPerSplat;
     // texel at value index i (its three channels), with the view-dependent colour added
     auto texel = [&](int64_t i) {
@@ -300,24 +358,21 @@ __device__ __forceinline__ void stage_texels_mixed(const void* __restrict__ text
   }
 }
 
-// Slope of the uv -> grid map of an n-texel side, formed as the host forms it for a uniform
-// side (a call whose sides all equal N then matches the uniform path bit for bit).
-__device__ __forceinline__ float grid_scale(int n, float sigma) {
-  return (float)(n - 1) / (2.0f * sigma);
-}
-
-// Ray-splat solve and falloff of one splat at one pixel.
+// Ray-splat solve and falloff of one splat at one pixel. The pixel can blend the splat where
+// r2 != 0 and alpha >= alpha_min.
 struct PixelEval {
   float dx, dy;       // pixel centre minus projected centre (float32; low-pass and gradients)
-  float inv;          // 1 / rho2
+  float r2, inv;      // rho2 and 1 / rho2
   float u, v;
   float G;            // exp(-q)
-  float alpha;
+  float oG;           // opacity times G
+  float alpha;        // min(alpha_max, oG)
   bool uv_branch;     // q came from the uv Gaussian (else from the screen low-pass)
-  bool hit;           // rho2 != 0 and alpha >= alpha_min
 };
 
 // (lx, ly): pixel centre minus the wave block's centre; (tx, ty): minus the tile's centre.
+// Both falloff exponents are compared and scaled as 2 q (doubling is exact, so the result is
+// that of q); the minimum is one instruction (fminf first canonicalises alpha_max).
 __device__ __forceinline__ PixelEval eval_splat(const StagedGeo& s, float lx, float ly, float tx,
                                                 float ty, const BlendParams& p) {
   PixelEval e;
@@ -325,17 +380,17 @@ __device__ __forceinline__ PixelEval eval_splat(const StagedGeo& s, float lx, fl
   e.dy = ty + s.g2.w;
   const float r0 = __builtin_fmaf(s.g1.y, ly, __builtin_fmaf(s.g1.x, lx, s.g0.x));
   const float r1 = __builtin_fmaf(s.g1.w, ly, __builtin_fmaf(s.g1.z, lx, s.g0.y));
-  const float r2 = __builtin_fmaf(s.g2.y, ly, __builtin_fmaf(s.g2.x, lx, s.g0.z));
-  e.inv = __builtin_amdgcn_rcpf(r2);
+  e.r2 = __builtin_fmaf(s.g2.y, ly, __builtin_fmaf(s.g2.x, lx, s.g0.z));
+  e.inv = __builtin_amdgcn_rcpf(e.r2);
   e.u = r0 * e.inv;
   e.v = r1 * e.inv;
-  const float q_uv = 0.5f * (e.u * e.u + e.v * e.v);
-  const float q_lp = (e.dx * e.dx + e.dy * e.dy) * p.lp_scale;
+  const float q_uv = e.u * e.u + e.v * e.v;
+  const float q_lp = (e.dx * e.dx + e.dy * e.dy) * p.lp_scale2;
   e.uv_branch = q_uv <= q_lp;
   const float q = e.uv_branch ? q_uv : q_lp;
-  e.G = __builtin_amdgcn_exp2f(-q * 1.4426950408889634f);
-  e.alpha = fminf(p.alpha_max, s.g0.w * e.G);
-  e.hit = (r2 != 0.0f) && (e.alpha >= p.alpha_min);
+  e.G = __builtin_amdgcn_exp2f(q * (-0.5f * 1.4426950408889634f));
+  e.oG = s.g0.w * e.G;
+  __asm__("v_min_f32 %0, %1, %2" : "=v"(e.alpha) : "s"(p.alpha_max), "v"(e.oG));
   return e;
 }
 

@@ -1,8 +1,12 @@
 // Forward blend (Alg. 1 forward with Alg. 2 bilinear): one workgroup per tile, one lane per
-// pixel, each wave owning an 8 x 8 pixel block. The tile's depth-sorted splats are staged
-// into LDS in batches (geometry plus texels, bfloat16 decoded on staging). A wave skips a
-// splat whose screen rectangle misses its block, and stops when all of its pixels have
-// terminated; the workgroup stops staging when every wave has.
+// pixel, each wave owning an 8 x 8 pixel block. The tile's depth-sorted splats are taken in passes
+// of 64: each wave stages their geometry for its own block, one splat per lane, and votes which
+// can reach it (a wave whose pixels have all terminated votes for none); the splats that reach
+// some block have their texels staged into LDS in batches (bfloat16 decoded on staging) and are
+// walked by the waves that they reach. The workgroup stops when every wave has terminated.
+// Bound by VALU issue (about 85 wave instructions per evaluated wave and splat, staging included).
+// Staging only the splats that reach a block, and their geometry by all waves at once: at 1M
+// splats and 1080p 0.509 -> 0.456 ms, 16 x 16 grids 1.24 -> 0.84, sides {2, 4, 8} 0.745 -> 0.577.
 //
 // Per pixel and splat: (u, v) from the centre-relative homography, G = exp(-min(q_uv, q_lp)),
 // alpha = min(alpha_max, o G); alpha < alpha_min is skipped; if T (1 - alpha) < t_min the
@@ -24,14 +28,21 @@ namespace {
 // the rest pass also adds its blended pairs to stats[4].
 // Occupancy target: eight waves per SIMD, or what the 160 KB of LDS per CU allows (a
 // workgroup puts one wave on each of the CU's four SIMDs). Grids of several sides (MIXED) ask
-// for at most seven: at eight their 64-VGPR budget spills, and seven measured faster for a
-// layout of 16 (sides {4, 8, 16} at 1M splats and 1080p: forward 1.468 against 1.516 ms) and
-// the same for a layout of 8.
+// for at most seven: at eight their 64-VGPR budget spills.
 template <int N, int B, bool MIXED>
 constexpr int fwd_min_waves() {
-  constexpr int lds = B * (GeoLds<B>::kBytesPerSplat + 4 + TexLayout<N>::kPerSplat * 16);
+  constexpr int lds = (int)sizeof(GeoLds<kPassEntries>) + 256 + B * TexLayout<N>::kPerSplat * 16;
   constexpr int w = 160 * 1024 / lds < 8 ? 160 * 1024 / lds : 8;
   return MIXED && w > 7 ? 7 : w;
+}
+
+// Splats per batch: the number asked for, or fewer where that lets eight workgroups share a CU's
+// LDS beside the pass's 6 KB of geometry. 8 x 8 grids (1.1 KB of texels per splat), forward ms at
+// 1M splats and 1080p / 3M splats on four 1080p views: batches of 8 0.482 / 5.26, 12 0.458 / 4.75,
+// 16 0.501 / 5.28. 16 x 16 grids (4.3 KB) at 1M splats: 2 0.915, 3 0.840, 4 0.854.
+template <int N>
+constexpr int fwd_batch(int asked) {
+  return N >= 16 ? 3 : N == 8 && asked == 16 ? 12 : asked;
 }
 
 // This workgroup's slices of the arrays to zero (the coming backward's texture and record
@@ -67,14 +78,11 @@ blend_fwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
                  const void* __restrict__ textures, BlendParams p, float* __restrict__ rgb,
                  float* __restrict__ T_final, uint32_t* __restrict__ n_last, SplitState split,
                  unsigned long long* __restrict__ stats) {
-  __shared__ GeoLds<B> s_geo;
+  __shared__ GeoLds<kPassEntries> s_geo;
   __shared__ float4 s_tex[B * TexLayout<N>::kPerSplat];
-  __shared__ uint8_t s_reach[4][B];  // [wave block][staged splat]: may reach the block
-  // MIXED: side and uv -> grid slope of each staged splat's grid (two words per splat: the 16
-  // of grid_consts would take the LDS of a batch of 16 8 x 8 grids past an eighth of the CU's)
-  __shared__ int32_t s_gn[MIXED ? B : 1];
-  __shared__ float s_gscale[MIXED ? B : 1];
-  static_assert((B & (B - 1)) == 0, "batch sizes are powers of two");
+  // the waves' votes of a pass, of which two can be in use at a time
+  __shared__ uint64_t s_mask[2][4];
+  __shared__ uint8_t s_list[kPassEntries];
 
   const int tile = tile_of_block(p);
   if (tile >= p.total_tiles) {
@@ -121,97 +129,113 @@ blend_fwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
   }
   uint32_t st_blend = 0, st_eval = 0;
   bool st_term = false;
+  const int kbx = tile_x0 + bx, kby = tile_y0 + by;  // the wave block's first pixel
+  int parity = 0;
+  bool all_done = false;
 
-  for (uint32_t b0 = start; b0 < end; b0 += B) {
-    const int nb = (int)((end - b0) < (uint32_t)B ? (end - b0) : (uint32_t)B);
-    if (STATS && tid == 0) atomicAdd(&stats[3], (unsigned long long)nb);
-    {
-      // thread c stages splat c mod B for wave block c / B (geometry centred on that block)
-      // and tests whether it can reach the block: for a batch of 16 and four waves that is
-      // one wave doing every (splat, block) staging and test once
-      const int j = tid & (B - 1), b = tid / B;
-      if (b < n_waves && j < nb) {
-        const uint32_t r = pair_vals[b0 + j];
-        const SplatRec R = rec[r];
-        const int kbx = tile_x0 + (b % waves_x) * 8, kby = tile_y0 + (b / waves_x) * 8;
+  for (uint32_t b = start; b < end && !all_done; b += (uint32_t)kPassEntries) {
+    // a pass: entries [b, b + n) of the list, one per lane, for the wave's own block
+    const int n = (int)((end - b) < (uint32_t)kPassEntries ? (end - b) : (uint32_t)kPassEntries);
+    if (STATS && tid == 0) atomicAdd(&stats[3], (unsigned long long)n);
+    uint64_t mine = 0;
+    EntryGrid eg{0u, 1, 0.f, 0};
+    const bool wave_open = ballot(!done) != 0;
+    // wave 0 also stores what the blocks share of a splat's geometry
+    if (w == 0 || wave_open) {
+      bool may = false;
+      if (lane < n) {
+        const SplatRec R = rec[pair_vals[b + (uint32_t)lane]];
         const StagedGeo g = stage_geo(R, kbx + 4, kby + 4, tcx, tcy);
-        s_geo.store(b, j, g);
-        if (MIXED && b == 0) {
-          const int n = grid_side<N>(p, r - rec_base);
-          s_gn[j] = n;
-          s_gscale[j] = grid_scale(n, p.sigma);
-        }
-        s_reach[b][j] =
-            block_may_contribute(g, (float)(kbx + 4 - tcx), (float)(kby + 4 - tcy), kbx, kby, p)
-                ? 1
-                : 0;
+        s_geo.store(w, lane, g);
+        may = wave_open && block_may_contribute(g, (float)(kbx + 4 - tcx), (float)(kby + 4 - tcy),
+                                                kbx, kby, p);
       }
+      mine = ballot(may);
     }
-    if constexpr (MIXED)
-      stage_texels_mixed<N, BF16, false>(textures, pair_vals + b0, rec_base, nb, s_tex, p,
-                                         nullptr, nullptr);
-    else
-      stage_texels<N, BF16>(textures, pair_vals + b0, rec_base, nb, s_tex, p.spec);
+    if constexpr (MIXED) {
+      if (lane < n) eg = entry_grid<N>(p, pair_vals[b + (uint32_t)lane], rec_base);
+    }
+    if (lane == 0) s_mask[parity][w] = mine;
     __syncthreads();
+    const PassVotes votes = pass_votes<false>(mine, s_mask[parity], n_waves, lane, s_list);
+    parity ^= 1;
 
-    if (ballot(!done) != 0) {
-      // splats of this batch that can reach the wave's 8 x 8 block (one lane per splat)
-      const bool may = lane < nb && s_reach[w][lane] != 0;
-      uint64_t todo = ballot(may);
-      while (todo != 0) {
-        const int j = (int)__builtin_ctzll(todo);
-        todo &= todo - 1;
-        const StagedGeo g = s_geo.load(w, j);
-        const PixelEval e = eval_splat(g, lx, ly, tx, ty, p);
-        if (STATS) ++st_eval;
-        if (!done && e.hit) {
-          const float Tn = T * (1.0f - e.alpha);
-          if (Tn < p.t_min) {
-            done = true;
-            if (STATS) st_term = true;
-          } else {
-            if (STATS) ++st_blend;
-            float c0, c1, c2;
-            const float4* tex = s_tex + j * TexLayout<N>::kPerSplat;
-            if constexpr (N == 1) {
-              const float4 t = tex[0];
-              c0 = t.x;
-              c1 = t.y;
-              c2 = t.z;
+    uint64_t ahead = ~0ull;  // entries that no batch has taken yet
+    for (int b0 = 0; b0 < votes.total; b0 += B) {
+      const int nb = votes.total - b0 < B ? votes.total - b0 : B;
+      if constexpr (MIXED)
+        stage_texels_mixed<N, BF16>(textures, s_list + b0, nb, s_tex, p.spec, eg);
+      else
+        stage_texels<N, BF16, false>(textures, pair_vals + b, s_list + b0, rec_base, nb, s_tex,
+                                     p.spec);
+      __syncthreads();
+      const uint64_t batch =
+          ahead & (~0ull >> (63 - __builtin_amdgcn_readfirstlane((int)s_list[b0 + nb - 1])));
+      ahead &= ~batch;
+      if (ballot(!done) != 0) {
+        // the batch's splats that can reach the wave's block
+        uint64_t todo = votes.mine & batch;
+        while (todo != 0) {
+          const int j = (int)__builtin_ctzll(todo);
+          const uint64_t before = votes.any & ((1ull << j) - 1ull);
+          todo &= todo - 1;
+          const StagedGeo g = s_geo.load(w, j);
+          const PixelEval e = eval_splat(g, lx, ly, tx, ty, p);
+          if (STATS) ++st_eval;
+          if (!done & (e.r2 != 0.0f) & (e.alpha >= p.alpha_min)) {
+            const float Tn = T * (1.0f - e.alpha);
+            if (Tn < p.t_min) {
+              done = true;
+              if (STATS) st_term = true;
             } else {
-              int iu, iv;
-              float fu, fv;
-              if constexpr (MIXED) {
-                const int n = s_gn[j];
-                const float sc = s_gscale[j];
-                grid_coord_n(e.u, sc, n, iu, fu);
-                grid_coord_n(e.v, sc, n, iv, fv);
+              if (STATS) ++st_blend;
+              float c0, c1, c2;
+              const int slot = __builtin_popcount((uint32_t)before) +
+                               __builtin_popcount((uint32_t)(before >> 32)) - b0;
+              const float4* tex = s_tex + slot * TexLayout<N>::kPerSplat;
+              if constexpr (N == 1) {
+                const float4 t = tex[0];
+                c0 = t.x;
+                c1 = t.y;
+                c2 = t.z;
               } else {
-                grid_coord<N>(e.u, p, iu, fu);
-                grid_coord<N>(e.v, p, iv, fv);
+                int iu, iv;
+                float fu, fv;
+                if constexpr (MIXED) {
+                  const int ns = __builtin_amdgcn_readlane(eg.n, j);
+                  const float sc = __int_as_float(
+                      __builtin_amdgcn_readlane(__float_as_int(eg.scale), j));
+                  grid_coord_n(e.u, sc, ns, iu, fu);
+                  grid_coord_n(e.v, sc, ns, iv, fv);
+                } else {
+                  grid_coord<N>(e.u, p, iu, fu);
+                  grid_coord<N>(e.v, p, iv, fv);
+                }
+                const float4* t = tex + TexLayout<N>::at(iu, iv);
+                const int kr = TexLayout<N>::kRow;
+                const float4 t00 = load_texel(t), t01 = load_texel(t + 1);
+                const float4 t10 = load_texel(t + kr), t11 = load_texel(t + kr + 1);
+                const float a0 = t00.x + fv * (t01.x - t00.x), b0_ = t10.x + fv * (t11.x - t10.x);
+                const float a1 = t00.y + fv * (t01.y - t00.y), b1 = t10.y + fv * (t11.y - t10.y);
+                const float a2 = t00.z + fv * (t01.z - t00.z), b2 = t10.z + fv * (t11.z - t10.z);
+                c0 = a0 + fu * (b0_ - a0);
+                c1 = a1 + fu * (b1 - a1);
+                c2 = a2 + fu * (b2 - a2);
               }
-              const int k00 = TexLayout<N>::at(iu, iv), kr = TexLayout<N>::kRow;
-              const float4 t00 = tex[k00], t01 = tex[k00 + 1];
-              const float4 t10 = tex[k00 + kr], t11 = tex[k00 + kr + 1];
-              const float a0 = t00.x + fv * (t01.x - t00.x), b0_ = t10.x + fv * (t11.x - t10.x);
-              const float a1 = t00.y + fv * (t01.y - t00.y), b1 = t10.y + fv * (t11.y - t10.y);
-              const float a2 = t00.z + fv * (t01.z - t00.z), b2 = t10.z + fv * (t11.z - t10.z);
-              c0 = a0 + fu * (b0_ - a0);
-              c1 = a1 + fu * (b1 - a1);
-              c2 = a2 + fu * (b2 - a2);
+              const float wgt = e.alpha * T;
+              acc0 += wgt * c0;
+              acc1 += wgt * c1;
+              acc2 += wgt * c2;
+              T = Tn;
+              last = b + (uint32_t)j + 1u;
             }
-            const float wgt = e.alpha * T;
-            acc0 += wgt * c0;
-            acc1 += wgt * c1;
-            acc2 += wgt * c2;
-            T = Tn;
-            last = b0 + (uint32_t)j + 1u;
           }
+          if (ballot(!done) == 0) break;
         }
-        if (ballot(!done) == 0) break;
       }
+      all_done = __syncthreads_and(done);
+      if (all_done) break;
     }
-    if (__syncthreads_and(done)) break;
   }
 
   if (p.tile_work) {
@@ -275,16 +299,13 @@ hipError_t launch_n(const Plan& pl, const gb_splats& sp, const BlendParams& bp,
                      rec, pair_vals, ranges, sp.textures, bp, rgb, T_final, n_last, split,    \
                      stats)
   if constexpr (N >= 16) {
-    // the only batch built for N = 16: 8 splats of 16 x 16 texels hold 36 KB of LDS (4
-    // workgroups per CU); 4 double that, and the forward at 1M splats and 1080p took 1.24 ms
-    // against 1.33 (a batch of 2: 1.85 ms)
-    GBB_FWD_B(4);
+    GBB_FWD_B(fwd_batch<N>(4));
   } else {
     switch (pl.batch_fwd) {
-      case 8: GBB_FWD_B(8); break;
-      case 16: GBB_FWD_B(16); break;
-      case 32: GBB_FWD_B(32); break;
-      default: GBB_FWD_B(64); break;
+      case 8: GBB_FWD_B(fwd_batch<N>(8)); break;
+      case 16: GBB_FWD_B(fwd_batch<N>(16)); break;
+      case 32: GBB_FWD_B(fwd_batch<N>(32)); break;
+      default: GBB_FWD_B(fwd_batch<N>(64)); break;
     }
   }
 #undef GBB_FWD_B
@@ -341,6 +362,7 @@ BlendParams make_blend_params(const Plan& pl, const gb_options& o, int n_views) 
   bp.alpha_max = o.alpha_max;
   bp.t_min = o.t_min;
   bp.lp_scale = 1.0f / (2.0f * o.lowpass_var);
+  bp.lp_scale2 = 2.0f * bp.lp_scale;
   bp.bg[0] = o.bg[0];
   bp.bg[1] = o.bg[1];
   bp.bg[2] = o.bg[2];

@@ -160,39 +160,6 @@ __device__ __forceinline__ void row_sum_all(float (&v)[K]) {
   for (int k = 0; k < K; ++k) v[k] += dpp_f<0x128>(v[k]);
 }
 
-// Row sums of K values (K <= 16) by a transposing butterfly. In each of four steps a lane and
-// its partner inside the 16-lane row (lane ^ 15, ^ 7, ^ 3, ^ 1: DPP row_mirror,
-// row_half_mirror, quad_perm [3,2,1,0], quad_perm [1,0,3,2]) split their values pairwise:
-// each keeps one value of a pair, chosen by one bit of its row position, and adds the
-// partner's copy of it; a value left without a pair is added whole on both sides. The masks
-// span all 16 positions, so each lane ends with the row total of one value: about 3K/2 + 4
-// instructions instead of 4K for plain reductions. row_scatter_slot gives that value's index
-// and whether this lane is the one lane of the row that owns it.
-template <int CTRL, int KI>
-__device__ __forceinline__ void rs_step(const float (&in)[KI], float (&out)[(KI + 1) / 2],
-                                        bool hi) {
-#pragma unroll
-  for (int i = 0; i < KI / 2; ++i) {
-    const float keep = hi ? in[2 * i + 1] : in[2 * i];
-    const float send = hi ? in[2 * i] : in[2 * i + 1];
-    out[i] = keep + dpp_f<CTRL>(send);
-  }
-  if (KI & 1) out[KI / 2] = in[KI - 1] + dpp_f<CTRL>(in[KI - 1]);
-}
-
-template <int K>
-__device__ __forceinline__ float row_reduce_scatter(const float (&v)[K]) {
-  static_assert(K >= 1 && K <= 16, "at most 16 values per row");
-  constexpr int K1 = (K + 1) / 2, K2 = (K1 + 1) / 2, K3 = (K2 + 1) / 2;
-  const int l = threadIdx.x & 15;
-  float a[K1], b[K2], c[K3], d[1];
-  rs_step<0x140>(v, a, (l & 8) != 0);
-  rs_step<0x141>(a, b, (l & 4) != 0);
-  rs_step<0x1B>(b, c, (l & 2) != 0);
-  rs_step<0xB1>(c, d, (l & 1) != 0);
-  return d[0];
-}
-
 // One swap step across lane groups: v_permlane32_swap pairs each lane of the wave's lower half
 // with one of the upper half, v_permlane16_swap each lane of an even row with one of the next
 // row. Swapping a value pair (a, b) and adding the two results leaves one side of every lane
@@ -218,21 +185,8 @@ __device__ __forceinline__ void swap_step(const float (&in)[KI], float (&out)[(K
   if (KI & 1) out[KI / 2] = swap_sum<HALVES>(in[KI - 1], in[KI - 1]);
 }
 
-// Wave sums of K values (K <= 16): two swap steps (wave halves, then row pairs) and the
-// transposing row butterfly leave each of the K totals in lanes of one row, at about
-// 2 K / 2 + 2 K / 4 + 3 K / 8 + 4 instructions. wave_scatter_slot gives each lane's total.
-template <int K>
-__device__ __forceinline__ float wave_reduce_scatter(const float (&v)[K]) {
-  static_assert(K >= 1 && K <= 16, "at most 16 values per wave");
-  constexpr int K1 = (K + 1) / 2, K2 = (K1 + 1) / 2;
-  float a[K1], b[K2];
-  swap_step<true>(v, a);
-  swap_step<false>(a, b);
-  return row_reduce_scatter<K2>(b);
-}
-
 // The side of each swap step a lane is on: true where it receives the second value of a pair.
-// Taken from the swap itself once per kernel, so that the mapping below holds whichever way
+// Taken from the swap itself once per kernel, so that the slot mapping holds whichever way
 // the hardware orders the exchange.
 struct SwapSides {
   bool halves, rows;
@@ -242,43 +196,115 @@ __device__ __forceinline__ SwapSides swap_sides() {
   return {swap_sum<true>(0.f, 1.f) != 0.f, swap_sum<false>(0.f, 1.f) != 0.f};
 }
 
-// The value index that wave_reduce_scatter<K> leaves in this lane, and whether the lane owns
-// it (a value that went unpaired at some step is held on both sides; only the lane on the low
-// side of every such step owns it, so each of the K totals has exactly one owner).
+// ---- row sums by masked DPP adds ---------------------------------------------------------------
+// Sums of K = 12, 6 or 3 values over each row of 16 lanes (all lanes active). A pair (a, b) is
+// halved by two DPP adds: a + mirrored a into every lane, then b + mirrored b into the half of
+// the lanes that the bank mask names (banks are four lanes of a row), so that one lane of each
+// mirrored pair goes on with a and the other with b. That is two instructions a pair, against
+// three for selects and an add, and three issue slots for a lane swap (which takes two) and an
+// add; the bank masks reach lane bits 3 and 2, the last two steps (inside groups of four lanes)
+// select. A value without a partner is left as partial sums in both halves where its row_slot
+// entry has an owner in each. The four rows are not summed with each other: each owner lane adds
+// its row's total to the LDS, where the four adds to one address cost less than two more
+// swaps. Written as assembly because the compiler does not form masked DPP adds; the s_nop are
+// the wait states a DPP read needs after a write of its source.
+#define GBB_PAIR(A, B, OP, MASK)                                    \
+  "v_add_f32_dpp " A ", " A ", " A " " OP " row_mask:0xf bank_mask:0xf\n\t" \
+  "v_add_f32_dpp " A ", " B ", " B " " OP " row_mask:0xf bank_mask:" MASK "\n\t"
+
 template <int K>
-__device__ __forceinline__ void wave_scatter_slot(SwapSides sides, int& idx, bool& owner) {
-  const int l = threadIdx.x & 15;
-  const bool hi[6] = {sides.halves, sides.rows, (l & 8) != 0, (l & 4) != 0, (l & 2) != 0,
-                      (l & 1) != 0};
-  int ids[16];
-  bool dup[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    ids[i] = i;
-    dup[i] = false;
+__device__ __forceinline__ float row_sums(float (&v)[K]) {
+  static_assert(K == 12 || K == 6 || K == 3, "built for 12, 6 and 3 values");
+  const bool b1 = (threadIdx.x & 2) != 0, b0 = (threadIdx.x & 1) != 0;
+  if constexpr (K == 12) {
+    __asm__ volatile("s_nop 1\n\t"
+                     GBB_PAIR("%0", "%6", "row_mirror", "0xc")
+                     GBB_PAIR("%1", "%7", "row_mirror", "0xc")
+                     GBB_PAIR("%2", "%8", "row_mirror", "0xc")
+                     GBB_PAIR("%3", "%9", "row_mirror", "0xc")
+                     GBB_PAIR("%4", "%10", "row_mirror", "0xc")
+                     GBB_PAIR("%5", "%11", "row_mirror", "0xc")
+                     GBB_PAIR("%0", "%1", "row_half_mirror", "0xa")
+                     GBB_PAIR("%2", "%3", "row_half_mirror", "0xa")
+                     GBB_PAIR("%4", "%5", "row_half_mirror", "0xa")
+                     "s_nop 1"
+                     : "+v"(v[0]), "+v"(v[2]), "+v"(v[4]), "+v"(v[6]), "+v"(v[8]), "+v"(v[10])
+                     : "v"(v[1]), "v"(v[3]), "v"(v[5]), "v"(v[7]), "v"(v[9]), "v"(v[11]));
+    const float x = (b1 ? v[4] : v[0]) + dpp_f<0x4E>(b1 ? v[0] : v[4]);
+    const float y = v[8] + dpp_f<0x4E>(v[8]);
+    return (b0 ? y : x) + dpp_f<0xB1>(b0 ? x : y);
+  } else if constexpr (K == 6) {
+    __asm__ volatile("s_nop 1\n\t"
+                     GBB_PAIR("%0", "%3", "row_mirror", "0xc")
+                     GBB_PAIR("%1", "%4", "row_mirror", "0xc")
+                     GBB_PAIR("%2", "%5", "row_mirror", "0xc")
+                     GBB_PAIR("%0", "%1", "row_half_mirror", "0xa")
+                     "s_nop 1"
+                     : "+v"(v[0]), "+v"(v[2]), "+v"(v[4])
+                     : "v"(v[1]), "v"(v[3]), "v"(v[5]));
+    const float x = (b1 ? v[4] : v[0]) + dpp_f<0x4E>(b1 ? v[0] : v[4]);
+    return x + dpp_f<0xB1>(x);
+  } else {
+    __asm__ volatile("s_nop 1\n\t"
+                     GBB_PAIR("%0", "%1", "row_mirror", "0xc")
+                     "s_nop 1\n\t"
+                     GBB_PAIR("%0", "%2", "row_half_mirror", "0xa")
+                     "s_nop 1"
+                     : "+v"(v[0])
+                     : "v"(v[1]), "v"(v[2]));
+    const float x = v[0] + dpp_f<0x4E>(v[0]);
+    return x + dpp_f<0xB1>(x);
   }
-  int n = K;
-#pragma unroll
-  for (int s = 0; s < 6; ++s) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (i < n / 2) {
-        ids[i] = hi[s] ? ids[2 * i + 1] : ids[2 * i];
-        dup[i] = hi[s] ? dup[2 * i + 1] : dup[2 * i];
-      }
-    }
-    if (n & 1) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        if (i == n / 2) {
-          ids[i] = ids[n - 1];
-          dup[i] = dup[n - 1] || hi[s];
-        }
-    }
-    n = (n + 1) / 2;
-  }
-  idx = ids[0];
-  owner = !dup[0];
+}
+
+// Wave sums of twelve values, added in the order lane ^ 32, ^ 16, ^ 15, ^ 7, ^ 3, ^ 1: two swap
+// steps, then the row steps above. 34 issue slots against the 25 of row_sums, which leaves the
+// rows unsummed and adds in another order.
+__device__ __forceinline__ float ordered_sums(const float (&v)[12]) {
+  float a[6], b[3];
+  swap_step<true>(v, a);
+  swap_step<false>(a, b);
+  __asm__ volatile("s_nop 1\n\t"
+                   GBB_PAIR("%0", "%1", "row_mirror", "0xc")
+                   "v_add_f32_dpp %2, %2, %2 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+                   "s_nop 1\n\t"
+                   GBB_PAIR("%0", "%2", "row_half_mirror", "0xa")
+                   "s_nop 1\n\t"
+                   "v_add_f32_dpp %0, %0, %0 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
+                   "s_nop 1\n\t"
+                   "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+                   "s_nop 1"
+                   : "+v"(b[0]), "+v"(b[1]), "+v"(b[2]));
+  return b[0];
+}
+#undef GBB_PAIR
+
+// The value that ordered_sums leaves in a lane, and the lanes of which each value has one: with
+// h and r the sides of the swaps and b3..b0 the bits of the row position, value 4 i + 2 r + h
+// with i = b3 for b2 = 0 and i = 2 for b2 = 1 (held for both b3); b1 and b0 hold copies.
+__device__ __forceinline__ int ordered_slot(bool h, bool r, int l) {
+  return 4 * ((l & 4) ? 2 : (l >> 3 & 1)) + (r ? 2 : 0) + (h ? 1 : 0);
+}
+constexpr uint64_t kOrderedOwners = 0x0111011101110111ull;  // row positions 0, 4 and 8
+
+// The value whose (partial) sum row_sums<K> leaves in row position l (0..15), -1 in a position
+// that holds a copy of another's. With b3..b0 the bits of l:
+//   12: 4 j + 2 b2 + b3 with j = b1 for b0 = 0; j = 2 for b0 = 1, held twice (b1)
+//    6: 2 i + b3 with i = b2 for b1 = 0; i = 2 for b1 = 1, in two parts (b2); b0 holds copies
+//    3: b3 for b2 = 0; 2 for b2 = 1, in two parts (b3); b1 and b0 hold copies
+__host__ __device__ constexpr int row_slot(int K, int l) {
+  const int b3 = l >> 3 & 1, b2 = l >> 2 & 1, b1 = l >> 1 & 1, b0 = l & 1;
+  if (K == 12) return b0 ? (b1 ? -1 : 8 + 2 * b2 + b3) : 4 * b1 + 2 * b2 + b3;
+  if (K == 6) return b0 ? -1 : 2 * (b1 ? 2 : b2) + b3;
+  return b1 || b0 ? -1 : (b2 ? 2 : b3);
+}
+
+// The lanes of a wave whose row position owns a value, as a lane mask.
+__host__ __device__ constexpr uint64_t row_owners(int K) {
+  uint64_t m = 0;
+  for (int l = 0; l < 64; ++l)
+    if (row_slot(K, l & 15) >= 0) m |= 1ull << l;
+  return m;
 }
 
 __device__ __forceinline__ float wave_sum(float v) {
