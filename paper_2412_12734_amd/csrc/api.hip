@@ -129,16 +129,12 @@ gb_status make_plan(int32_t P, int32_t N, const gb_view* views, int32_t n_views,
   pl->capacity = capacity;
   pl->tile_w = o->tile_w == 0 ? 16 : o->tile_w;
   pl->tile_h = o->tile_h == 0 ? 16 : o->tile_h;
-  // defaults: at N = 8 the smaller batches measured faster on the 1M-splat 1080p workload
-  // (forward 16 vs 32: 0.50 vs 0.60 ms; backward 8 vs 16: 2.21 vs 2.31 ms), because less LDS
-  // per block lets more blocks share a CU; at N = 4 a forward batch of 32 beat 64 and 16 (1M
-  // splats at 1080p, forward + backward: 2.06 vs 2.13 ms) and a backward batch of 32 beat
-  // 16 and 8 (2.13 vs 2.19 and 2.28 ms)
+  // defaults: the largest batches that the kernels' own limits leave worth while (fwd_batch and
+  // bwd_batch, which may take fewer and say what each measured)
   pl->batch_fwd = o->batch != 0 ? o->batch : (N >= 16 ? 4 : N >= 8 ? 16 : N >= 4 ? 32 : 64);
   pl->batch_bwd = o->batch_bwd != 0 ? o->batch_bwd : (N >= 16 ? 4 : N >= 8 ? 8 : 32);
-  // N = 16: 4.3 KB of staged texels per splat; batches of 4 keep the backward's LDS (texels,
-  // their gradient sums and a ring of 4 batches' geometry) near 32 KB per workgroup, five per
-  // CU. Batches of 4 are built for N = 16 only, and N = 16 only with them.
+  // N = 16 holds 10.6 KB of texels and sums per splat: batches of 4 are built for it only, and it
+  // only with them
   if (N >= 16 && (pl->batch_fwd != 4 || pl->batch_bwd != 4)) {
     g_last_error = "N = 16 takes batch and batch_bwd 4 (or 0)";
     return GB_ERR_UNSUPPORTED;

@@ -15,17 +15,19 @@
 // for the sums over pixels. Per splat and wave, twelve sums are taken by masked DPP adds inside
 // the rows of 16 lanes; texel gradients are grouped by grid cell (with sigma = 0.5 the grid covers
 // only the splat's core, so most blended pixels are border-clamped and share a few cells), one
-// group after another, over the corners that the group weights (a step that blended at most
-// kLaneAddMax pixels adds each pixel's corners directly instead). After each batch the non-zero
-// sums go to global memory with one float atomic each, while the next batch's texels are staged.
+// group after another, over the corners that the group weights, until at most kLaneAddMax pixels
+// are left, each of which adds its corners directly. After each batch the non-zero sums go to global
+// memory with one float atomic each, and the next batch's texels are staged.
 //
 // The sums are 64-bit in LDS: ds_add_f64 serves 64 lanes with distinct addresses in 8.7 cycles of
 // the CU's LDS (12 lanes 6.5, and 3 per lane on one address), where ds_add_f32 takes 3 cycles for
 // every lane whatever the addresses (12 lanes 38, 64 lanes 193), which had made the LDS the
-// limit. What bounds the kernel now is VALU issue (1M splats at 1080p: 88 % of the cycles; 0.65 G
-// wave instructions, about 228 per wave step). At 1M splats and 1080p 1.35 -> 1.05 ms, 3M splats
-// on four 1080p views 14.5 -> 13.2, 16 uneven views with 4 x 4 grids 8.28 -> 6.53, 16 x 16 grids
-// 2.33 -> 1.87, sides {2, 4, 8} 1.53 -> 1.10.
+// limit. What bounds the kernel now is VALU issue where tiles fill the chip (1M splats at 1080p:
+// 88 % of the cycles; 0.65 G wave instructions, about 228 per wave step), and the latency of a
+// wave's step where a few tiles hold the work. At 1M splats and 1080p 1.35 -> 1.02 ms, 3M splats on
+// four 1080p views 14.5 -> 10.9, 16 uneven views with 4 x 4 grids 8.28 -> 6.2, 16 x 16 grids 2.33 ->
+// 1.66, sides {2, 4, 8} 1.53 -> 1.13, 100k splats at 800 x 800 0.73 -> 0.53, 372k small splats on
+// 462 tiles 1.10 -> 1.11.
 #include "blend_common.h"
 
 namespace gbb {
@@ -97,11 +99,10 @@ __device__ __forceinline__ void pixel_step(const float4* tex, const PixelEval& e
     }
     o.fu = fu;
     o.fv = fv;
-    const int kr = TexLayout<N>::kRow;
     o.cell = TexLayout<N>::at(iu, iv);
     const float4* t = tex + o.cell;
-    const float4 t00 = load_texel(t), t01 = load_texel(t + 1);
-    const float4 t10 = load_texel(t + kr), t11 = load_texel(t + kr + 1);
+    float4 t00, t01, t10, t11;
+    load_corners<TexLayout<N>::kRow>(t, t00, t01, t10, t11);
     const float tsc = MIXED ? gc.x : p.tex_scale;
     // fractional-position adjoints (Alg. 2), zero where the coordinate is clamped
     if constexpr (CHANNELS) {
@@ -183,6 +184,20 @@ __device__ __forceinline__ int cell_row(int cell) {
   return (int)((unsigned)cell / (unsigned)TexLayout<N>::kRow);
 }
 
+// Fields of a lane's packed places: first bit and width (a lane that owns no value of a kind holds
+// bits that are never used).
+struct PlaceField {
+  int at, bits;
+};
+constexpr PlaceField kRow{0, 4}, kOrd{4, 4}, kT12{8, 6}, kT6v{14, 3}, kT6u{17, 6}, kT3{23, 2};
+
+__device__ __forceinline__ uint32_t place(PlaceField f, int x) {
+  return ((uint32_t)x & ((1u << f.bits) - 1u)) << f.at;
+}
+__device__ __forceinline__ int place_of(PlaceField f, uint32_t places) {
+  return (int)((places >> f.at) & ((1u << f.bits) - 1u));
+}
+
 // Adds the total that row_sums or ordered_sums left in each owner lane to an LDS array at index
 // base + offset (base uniform over the wave).
 template <uint64_t OWNERS>
@@ -195,48 +210,64 @@ __device__ __forceinline__ void lds_add(double* array, int base, int offset, flo
 // Record gradient r (in the order of kRecGrad) from a splat's sums x and its staged H.
 __device__ __forceinline__ float record_gradient(int r, const double* x, const float4& g1,
                                                  const float4& g2, float lp_scale) {
-  if (r < 7) return (float)x[r];
-  if (r == 9) return (float)x[11];
-  // d c2: minus the low-pass term's and rho's adjoints of the offset
+  // every lane reads what the two lanes of d c2 need: the reads then need no branch
   const bool y = r == 8;
-  const float lp = 2.f * lp_scale * (float)x[y ? 10 : 9];
-  return -lp - (float)x[7] * (y ? g1.y : g1.x) - (float)x[8] * (y ? g1.w : g1.z) -
-         (float)x[6] * (y ? g2.y : g2.x);
+  const float own = (float)x[r < 7 ? r : 11], lp = 2.f * lp_scale * (float)x[y ? 10 : 9];
+  // d c2: minus the low-pass term's and rho's adjoints of the offset
+  const float dc = -lp - (float)x[7] * (y ? g1.y : g1.x) - (float)x[8] * (y ? g1.w : g1.z) -
+                   (float)x[6] * (y ? g2.y : g2.x);
+  return r < 7 || r == 9 ? own : dc;
 }
 
-// Wave steps that blended at most this many pixels skip the cell grouping. Backward ms for
-// thresholds 8 / 16 / 20 / 28 / 40: 1M splats at 1080p 1.037 / 1.032 / 1.031 / 1.043 / 1.066, 3M
-// splats at 4 x 1080p 13.65 / 13.23 / 13.15 / 12.89 / 12.64, 100k splats at 800x800 0.673 /
-// 0.652 / 0.640 / 0.629 / 0.623.
-constexpr int kLaneAddMax = 24;
+// Pixels left to a wave step's cell grouping that are added one by one. Backward ms for 16 / 20 / 24
+// / 32: 1M splats at 1080p 1.033 / 1.018 / 1.041 / 1.18, 3M splats at 4 x 1080p 11.9 / 10.9 / 10.8 /
+// 11.6, 16 uneven views with 4 x 4 grids 6.00 / 6.17 / 6.28 / 6.92, 100k splats at 800 x 800 0.575 /
+// 0.526 / 0.518 / 0.543. (Grouping every pixel of a step with more than 24: 3M splats 13.2, 100k
+// 0.64.)
+constexpr int kLaneAddMax = 20;
 
-// Occupancy target: 7 waves per SIMD (at most 72 VGPRs; the kernels take 71-73 without scratch),
-// which the LDS also allows, see bwd_batch; 8 (64 VGPRs) spilled: 1M splats at 1080p 1.10 against
-// 1.03 ms, 3M splats at 4 x 1080p 14.7 against 13.2.
+// Splats per batch: a whole pass for one-texel grids; else the number asked for while the call's
+// tiles all run at once (few_tiles), and fewer where that lets another workgroup share a CU's 160
+// KB of LDS. Backward times:
+//  8 x 8 grids hold 2.8 KB per splat (texels and 64-bit sums) beside the pass's geometry: seven
+//  splats and passes of 32 entries (3 KB) are 22.7 KB, seven workgroups. 6 of 64 / 7 of 32 / 8 of
+//  64: 1.063 / 1.045 / 1.101 ms at 1M splats and 1080p, 11.4 / 10.8 / 11.9 at 3M splats on four
+//  1080p views, but 324 / 323 / 286 us at 120k small splats on 999 tiles.
+//  4 x 4 grids, 16 / 24 / 32 splats: 16 uneven views of 1M splats 6.22 / 6.25 / 7.54 ms, 47k splats
+//  on three uneven views 0.558 / 0.529 / -, 372k splats on 462 tiles 1.27 / - / 1.11.
+//  16 x 16 grids, 1 / 2 / 3 splats: 2.81 / 2.10 / 2.16 ms at 1M splats and 1080p, two in passes of
+//  32 entries (six workgroups per CU instead of five) 1.66. With sides {4, 8, 16} a grid is mostly
+//  smaller than its slot: 2 / 3 / 4 splats 3.88 / 3.11 / 2.59 ms at 202k splats on three views.
+template <int N, bool MIXED>
+constexpr int bwd_batch(int asked, bool few_tiles) {
+  return N == 1                                ? kPassEntries
+         : few_tiles || (N >= 16 && MIXED)     ? asked
+         : N >= 16                             ? 2
+         : N == 8 && asked == 8                ? 7
+         : N == 4 && asked == 32               ? 24
+                                               : asked;
+}
+template <int N, int B>
+constexpr int bwd_pass_entries() {
+  return (N == 8 && B == 7) || (N >= 16 && B == 2) ? 32 : kPassEntries;
+}
+
+// Occupancy target: what the LDS allows (see above), at most 7 waves per SIMD (72 VGPRs): 8 (64
+// VGPRs) spilled: 1M splats at 1080p 1.10 against 1.03 ms, 3M splats at 4 x 1080p 14.7 against
+// 13.2.
 template <int N, int B>
 constexpr int bwd_min_waves() {
-  return N <= 2 || (N == 4 && B <= 16) || (N == 8 && B <= 6) ? 7 : N == 4 ? 5 : 1;
+  return N <= 2 || (N == 4 && B <= 16) || (N == 8 && B <= 7)         ? 7
+         : (N == 4 && B == 24) || (N == 16 && B == 2)                ? 6
+         : N == 4 || (N == 8 && B == 8)                              ? 5
+                                                                     : 1;
 }
 
-// Splats per batch: the number asked for, or fewer where that lets another workgroup share a
-// CU's 160 KB of LDS. 8 x 8 grids hold 2.8 KB per splat (texels and 64-bit sums) beside the
-// pass's 6 KB of geometry: six splats are 22.5 KB, seven workgroups; 4 / 6 / 8 splats took 1.047 /
-// 1.040 / 1.132 ms at 1M splats and 1080p and 13.20 / 12.76 / 14.27 at 3M splats on four 1080p
-// views. 4 x 4 grids, 16 uneven views of 1M splats: 8 / 12 / 16 / 32 splats 6.64 / 7.51 / 6.41 /
-// 7.26 ms. 16 x 16 grids: 1 / 2 / 3 splats 2.81 / 2.10 / 2.16 ms.
-template <int N>
-constexpr int bwd_batch(int asked) {
-  return N >= 16 ? 2 : N == 8 && asked == 8 ? 6 : N == 4 && asked == 32 ? 16 : asked;
-}
-
-// Entries per pass: half a pass for 16 x 16 grids, whose 3 KB less of geometry lets six workgroups
-// share a CU instead of five (backward at 1M splats and 1080p 2.10 -> 1.83 ms).
-template <int N>
-constexpr int bwd_pass_entries() { return N >= 16 ? 32 : kPassEntries; }
-
-// Lanes that flush one splat's sums: a whole wave, or sixteen lanes where the grid is small.
-template <int N>
-constexpr int flush_lanes() { return N >= 4 ? 64 : 16; }
+// Lanes that flush one splat's sums: as few as keep the number of reads per lane small, so that a
+// wave flushes several splats side by side (one after another, each a chain of LDS reads, the
+// flush was what bound tiles of many small splats).
+template <int N, bool MIXED>
+constexpr int flush_lanes() { return MIXED || N >= 16 ? 64 : N == 8 ? 32 : 16; }
 
 // Depth-prefix split: on a tile that the prefix left open the block first walks the rest
 // pass's list (the later splats) and then, with each pixel's T and S carried over in
@@ -251,7 +282,7 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
                  const float* __restrict__ T_final, const float* __restrict__ d_rgb,
                  float* __restrict__ d_rec, float* __restrict__ d_tex) {
   constexpr int TEXG = 3 * N * N;
-  constexpr int PE = bwd_pass_entries<N>();
+  constexpr int PE = bwd_pass_entries<N, B>();
   __shared__ GeoLds<PE> s_geo;
   __shared__ float4 s_tex[B * TexLayout<N>::kPerSplat];
   __shared__ __attribute__((aligned(16))) double s_gtex[B * TEXG];  // per slot
@@ -259,7 +290,7 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
   // the waves' votes of a pass, of which two can be in use at a time (a wave may vote on the
   // next pass while another still reads this one's)
   __shared__ uint64_t s_mask[2][4];
-  __shared__ uint8_t s_list[PE];
+  __shared__ SlotList<PE> s_list;
   __shared__ uint32_t s_tile_last;
 
   const int tile = tile_of_block(p);
@@ -302,29 +333,28 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
     }
     ps.Sg = ps.T * (ps.g0 * p.bg[0] + ps.g1 * p.bg[1] + ps.g2 * p.bg[2]);
   }
-  // the sum that row_sums leaves in this lane: its place among a splat's record sums, and its
-  // offset from the first texel's first channel in the three kinds of texel group (four corners;
-  // two texels along v, or along u; one texel), one byte each
-  const int rl = lane & 15;
-  // (the record sums' places: after row_sums, and after ordered_sums in the second byte)
-  int rec_slots;
+  // the sum that this lane owns after the reductions: its place among a splat's record sums (after
+  // row_sums, and after ordered_sums), and its offset from the first texel's first channel in the
+  // three kinds of texel group (four corners; two texels along v, or along u; one texel), in one
+  // register: fields kRow, kOrd, kT12, kT6v, kT6u, kT3 of lane_places
+  uint32_t places;
   {
-    const SwapSides sides = swap_sides();
-    rec_slots = (row_slot(kSums, rl) & 255) | ordered_slot(sides.halves, sides.rows, rl) << 8;
-  }
-  uint32_t tex_off;
-  {
+    const int rl = lane & 15;
     const int s12 = row_slot(12, rl), s6 = row_slot(6, rl), s3 = row_slot(3, rl);
-    const uint32_t o12 = (uint32_t)(3 * ((s12 / 3 & 1) + (s12 / 6) * N) + s12 % 3) & 255u;
-    const uint32_t o6v = (uint32_t)s6 & 255u;  // 3 (s6 / 3) + s6 % 3
-    const uint32_t o6u = (uint32_t)(3 * (s6 / 3) * N + s6 % 3) & 255u;
-    tex_off = o12 | o6v << 8 | o6u << 16 | ((uint32_t)s3 & 255u) << 24;
+    const SwapSides sides = swap_sides();
+    places = place(kRow, row_slot(kSums, rl)) |
+             place(kOrd, ordered_slot(sides.halves, sides.rows, rl)) |
+             place(kT12, 3 * ((s12 / 3 & 1) + (s12 / 6) * N) + s12 % 3) |
+             place(kT6v, s6) |  // 3 (s6 / 3) + s6 % 3
+             place(kT6u, 3 * (s6 / 3) * N + s6 % 3) | place(kT3, s3);
   }
 
   // the per-batch LDS sums start at zero; each batch's flush clears what it read
   // (the first barrier of the list loop orders these stores before any add)
   for (int e = tid; e < B * TEXG; e += nthr) s_gtex[e] = 0.0;
   for (int e = tid; e < B * kSums; e += nthr) s_sum[e] = 0.0;
+  // votes of waves that the workgroup does not have
+  if (tid < 8 && (tid & 3) >= n_waves) s_mask[tid >> 2][tid & 3] = 0;
   int parity = 0;
 
 #pragma unroll 1
@@ -351,51 +381,64 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
     __syncthreads();
     const uint32_t tile_last = __builtin_amdgcn_readfirstlane(s_tile_last);
 
+    // the record of the lane's entry of the pass that ends at `end`
+    auto load_rec = [&](uint32_t end) {
+      const uint32_t at = (end - start > (uint32_t)PE ? end - (uint32_t)PE : start) + (uint32_t)lane;
+      return at < end ? pair_vals[at] : rec_base;
+    };
+    uint32_t my_rec = load_rec(tile_last);  // loaded a pass ahead
     for (uint32_t pend = tile_last; pend > start;) {
       // a pass: entries [pbase, pend) of the list, one per lane
       const uint32_t pbase = pend - start > (uint32_t)PE ? pend - (uint32_t)PE : start;
       uint64_t mine = 0;
-      EntryGrid eg{0u, 1, 0.f, 0};
+      EntryGrid eg{1, 0.f, 0};
       // wave 0 also stores what the blocks share of a splat's geometry
       if (w == 0 || pbase < wave_last) {
         bool may = false;
         const int e = fresh_tid() & 63;
         const uint32_t idx = pbase + (uint32_t)e;
         if (idx < pend) {
-          const SplatRec R = rec[pair_vals[idx]];
+          const SplatRec R = rec[my_rec];
           const StagedGeo g = stage_geo(R, kbx + 4, kby + 4, tcx, tcy);
           s_geo.store(w, e, g);
+          if constexpr (N == 1) {
+            if (w == 0) s_tex[e] = one_texel<BF16>(textures, my_rec, rec_base, p.spec);
+          }
           may = idx < wave_last && block_may_contribute(g, bcx, bcy, kbx, kby, p);
         }
         mine = ballot(may);
       }
       if constexpr (MIXED) {
         const uint32_t idx = pbase + (uint32_t)lane;
-        if (idx < pend) eg = entry_grid<N>(p, pair_vals[idx], rec_base);
+        if (idx < pend) eg = entry_grid<N>(p, my_rec, rec_base);
       }
       if (lane == 0) s_mask[parity][w] = mine;
       __syncthreads();
       const PassVotes votes =
-          pass_votes<true>(mine, s_mask[parity], n_waves, lane, s_list);
+          pass_votes<true>(mine, s_mask[parity], lane, my_rec, s_list);
+      my_rec = load_rec(pbase);
       parity ^= 1;
 
+      auto batch_size = [&](int b0) { return votes.total - b0 < B ? votes.total - b0 : B; };
       auto stage_batch = [&](int b0) {
-        const int n = votes.total - b0 < B ? votes.total - b0 : B;
-        if constexpr (MIXED)
-          stage_texels_mixed<N, BF16>(textures, s_list + b0, n, s_tex, p.spec, eg);
+        if constexpr (N == 1)
+          ;  // staged with the geometry
+        else if constexpr (MIXED)
+          stage_texels_mixed<N, BF16>(textures, s_list.entry + b0, s_list.rec + b0,
+                                      batch_size(b0), s_tex, p.spec, eg);
         else
-          stage_texels<N, BF16, true>(textures, pair_vals + pbase, s_list + b0, rec_base, n,
-                                      s_tex, p.spec);
+          stage_texels<N, BF16>(textures, s_list.rec + b0, rec_base, batch_size(b0), s_tex,
+                                p.spec, fresh_tid());
       };
-      if (votes.total > 0) {
+      if (N > 1 && votes.total > 0) {
         stage_batch(0);
         __syncthreads();
       }
       uint64_t ahead = ~0ull;  // entries that no batch has taken yet
       for (int b0 = 0; b0 < votes.total; b0 += B) {
-        const int nb = votes.total - b0 < B ? votes.total - b0 : B;
+        const int nb = batch_size(b0);
         const uint64_t batch =
-            ahead & (~0ull << __builtin_amdgcn_readfirstlane((int)s_list[b0 + nb - 1]));
+            ahead & (~0ull << __builtin_amdgcn_readfirstlane((int)s_list.entry[b0 + nb - 1]));
         ahead &= ~batch;
         // the batch's splats that can reach the wave's block, walked back to front
         uint64_t todo = votes.mine & batch;
@@ -412,9 +455,8 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
           const bool act = __builtin_amdgcn_inverse_ballot_w64(pend_px);
           // the splat's slot: taken slots of the pass after this entry's
           const uint64_t after = votes.any >> 1 >> j;
-          const int slot = __builtin_popcount((uint32_t)after) +
-                           __builtin_popcount((uint32_t)(after >> 32)) - b0;
-          const float4* tex = s_tex + slot * TexLayout<N>::kPerSplat;
+          const int slot = popcount64(after) - b0;
+          const float4* tex = s_tex + (N == 1 ? j : slot) * TexLayout<N>::kPerSplat;
           PixOut po;
           int n_side = N;
           float4 gc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -432,10 +474,10 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
           // Sums of the per-splat scalars; the owner lanes of a total add it to the splat's slot.
           if (N > 1 && (low_pass & (po.in_u | po.in_v)) != 0) {
             pixel_step<N, MIXED, true>(tex, e, inv, u, v, act, ps, p, po, gc);
-            lds_add<kOrderedOwners>(s_sum, kSums * slot, rec_slots >> 8, ordered_sums(po.sum));
+            lds_add<kOrderedOwners>(s_sum, kSums * slot, place_of(kOrd, places), ordered_sums(po.sum));
           } else {
             pixel_step<N, MIXED, false>(tex, e, inv, u, v, act, ps, p, po, gc);
-            lds_add<row_owners(kSums)>(s_sum, kSums * slot, rec_slots & 255, row_sums(po.sum));
+            lds_add<row_owners(kSums)>(s_sum, kSums * slot, place_of(kRow, places), row_sums(po.sum));
           }
 
           // Texel gradients, grouped by cell over all pixels of the wave. A wave step that
@@ -445,25 +487,7 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
           if constexpr (N == 1) {
             float red[3] = {po.wgt * ps.g0, po.wgt * ps.g1, po.wgt * ps.g2};
             const float tot = row_sums(red);
-            lds_add<row_owners(3)>(s_gtex, base, (int)(tex_off >> 24), tot);
-          } else if (__builtin_popcount((uint32_t)pend_px) +
-                         __builtin_popcount((uint32_t)(pend_px >> 32)) <=
-                     kLaneAddMax) {
-            if (act) {
-              double* const gb = s_gtex + base;
-              const int k00 = po.cell - cell_row<N>(po.cell);
-              float wc[4];
-              corner_weights(po.wgt, po.fu, po.fv, wc);
-#pragma unroll
-              for (int q = 0; q < 4; ++q) {
-                if (wc[q] != 0.f) {
-                  double* dst = gb + 3 * (k00 + (q & 1) + (q >> 1) * N);
-                  atomicAdd(dst + 0, (double)(wc[q] * ps.g0));
-                  atomicAdd(dst + 1, (double)(wc[q] * ps.g1));
-                  atomicAdd(dst + 2, (double)(wc[q] * ps.g2));
-                }
-              }
-            }
+            lds_add<row_owners(3)>(s_gtex, base, place_of(kT3, places), tot);
           } else {
             // A group is every pending lane of the first pending lane's cell, so the loop ends
             // within 64 passes. Most groups lie where a coordinate is clamped to the grid's
@@ -477,6 +501,24 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
             const int key = act ? po.cell : -1;
 #pragma unroll 1
             for (uint64_t left = pend_px; left != 0;) {
+              if (popcount64(left) <= kLaneAddMax) {
+                if (__builtin_amdgcn_inverse_ballot_w64(left)) {
+                  double* const gb = s_gtex + base;
+                  const int k00 = po.cell - cell_row<N>(po.cell);
+                  float wc[4];
+                  corner_weights(po.wgt, po.fu, po.fv, wc);
+#pragma unroll
+                  for (int q = 0; q < 4; ++q) {
+                    if (wc[q] != 0.f) {
+                      double* dst = gb + 3 * (k00 + (q & 1) + (q >> 1) * N);
+                      atomicAdd(dst + 0, (double)(wc[q] * ps.g0));
+                      atomicAdd(dst + 1, (double)(wc[q] * ps.g1));
+                      atomicAdd(dst + 2, (double)(wc[q] * ps.g2));
+                    }
+                  }
+                }
+                break;
+              }
               const int lead = __builtin_amdgcn_readlane(key, (int)__builtin_ctzll(left));
               const uint64_t members = ballot(key == lead);
               left &= ~members;
@@ -488,20 +530,20 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
                 if ((members & in_u) == 0) {
                   float red[3] = {wm * ps.g0, wm * ps.g1, wm * ps.g2};
                   const float tot = row_sums(red);
-                  lds_add<row_owners(3)>(s_gtex, base + 3 * (bu * N + bv), (int)(tex_off >> 24), tot);
+                  lds_add<row_owners(3)>(s_gtex, base + 3 * (bu * N + bv), place_of(kT3, places), tot);
                 } else {
                   const float w1 = wm * po.fu, w0 = __builtin_fmaf(-wm, po.fu, wm);
                   float red[6] = {w0 * ps.g0, w0 * ps.g1, w0 * ps.g2,
                                   w1 * ps.g0, w1 * ps.g1, w1 * ps.g2};
                   const float tot = row_sums(red);
-                  lds_add<row_owners(6)>(s_gtex, base + 3 * (lu * N + bv), (int)(tex_off >> 16 & 255u), tot);
+                  lds_add<row_owners(6)>(s_gtex, base + 3 * (lu * N + bv), place_of(kT6u, places), tot);
                 }
               } else if ((members & in_u) == 0) {
                 const float w1 = wm * po.fv, w0 = __builtin_fmaf(-wm, po.fv, wm);
                 float red[6] = {w0 * ps.g0, w0 * ps.g1, w0 * ps.g2,
                                 w1 * ps.g0, w1 * ps.g1, w1 * ps.g2};
                 const float tot = row_sums(red);
-                lds_add<row_owners(6)>(s_gtex, base + 3 * (bu * N + lv), (int)(tex_off >> 8 & 255u), tot);
+                lds_add<row_owners(6)>(s_gtex, base + 3 * (bu * N + lv), place_of(kT6v, places), tot);
               } else {
                 float wc[4], red[12];
                 corner_weights(wm, po.fu, po.fv, wc);
@@ -512,7 +554,7 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
                   red[3 * q + 2] = wc[q] * ps.g2;
                 }
                 const float tot = row_sums(red);
-                lds_add<row_owners(12)>(s_gtex, base + 3 * (lu * N + lv), (int)(tex_off & 255u), tot);
+                lds_add<row_owners(12)>(s_gtex, base + 3 * (lu * N + lv), place_of(kT12, places), tot);
               }
             }
           }
@@ -521,13 +563,19 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
         // Flush: FL lanes take a slot, its sums go to global memory with one float atomic per
         // non-zero sum (consecutive lanes, consecutive addresses) and are left zero for the
         // next batch.
-        constexpr int FL = flush_lanes<N>(), PER = 64 / FL;
+        constexpr int FL = flush_lanes<N, MIXED>(), PER = 64 / FL;
         const int ft = fresh_tid() & 63, fl = ft & (FL - 1);
         for (int j = w * PER + (PER > 1 ? ft / FL : 0); j < nb; j += n_waves * PER) {
-          int entry = (int)s_list[b0 + j];
-          if constexpr (PER == 1) entry = __builtin_amdgcn_readfirstlane(entry);
-          const uint32_t r = pair_vals[pbase + (uint32_t)entry];
+          int entry = (int)s_list.entry[b0 + j];
+          uint32_t r = s_list.rec[b0 + j];
+          if constexpr (PER == 1) {
+            entry = __builtin_amdgcn_readfirstlane(entry);
+            r = __builtin_amdgcn_readfirstlane(r);
+          }
           double* const gs = s_gtex + j * TEXG;
+          // each lane reads the sums its record gradient needs, and only then are they cleared
+          const float rg = record_gradient(fl, &s_sum[j * kSums], s_geo.g1[entry],
+                                           s_geo.g2[entry], p.lp_scale);
           if (p.d_spec) {
             // the view-dependent colour of a record is added to every texel of its lookup, so
             // its adjoint over the tile is the sum of the record's texel sums, one per channel
@@ -539,6 +587,9 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
             }
             if constexpr (PER == 1) wave_sum_all<3>(sc);
             else row_sum_all<3>(sc);
+            if constexpr (FL == 32) {
+              for (float& x : sc) x += __shfl_xor(x, 16, 64);
+            }
             const float x = fl == 0 ? sc[0] : fl == 1 ? sc[1] : sc[2];
             if (fl < 3 && x != 0.f) atomicAdd(&p.d_spec[4 * (int64_t)r + fl], x);
           }
@@ -547,34 +598,50 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
             // values i, i + 64, ... of the grid's 3 n^2
             const int n = __builtin_amdgcn_readlane(eg.n, entry);
             float* const dst = d_tex + readlane64(eg.first, entry);
-            for (int i = fl; i < 3 * n * n; i += 64) {
-              const int t = i / 3, c = i - 3 * t, iu = div_side(t, n), iv = t - iu * n;
-              double* const sum = gs + 3 * (iu * N + iv) + c;
-              const double x = *sum;
-              if (x != 0.0) {
-                *sum = 0.0;
-                atomicAdd(dst + i, (float)x);
+            for (int i0 = fl; i0 < 3 * n * n; i0 += 3 * 64) {  // three reads at a time
+              double x[3];
+              int at[3];
+#pragma unroll
+              for (int k = 0; k < 3; ++k) {
+                const int i = min(i0 + 64 * k, 3 * n * n - 1);
+                const int t = i / 3, c = i - 3 * t, iu = div_side(t, n), iv = t - iu * n;
+                at[k] = 3 * (iu * N + iv) + c;
+                x[k] = gs[at[k]];
+              }
+#pragma unroll
+              for (int k = 0; k < 3; ++k) {
+                const int i = i0 + 64 * k;
+                if (i < 3 * n * n && x[k] != 0.0) {
+                  gs[at[k]] = 0.0;
+                  atomicAdd(dst + i, (float)x[k]);
+                }
               }
             }
           } else {
             float* const dst = d_tex + (int64_t)(r - rec_base) * TEXG;
-            for (int k = 0; k < (TEXG + FL - 1) / FL; ++k) {
-              const int i = k * FL + fl;
-              const double x = i < TEXG ? gs[i] : 0.0;
-              if (x != 0.0) {
-                gs[i] = 0.0;
-                atomicAdd(dst + i, (float)x);
+            // (three reads at a time)
+            constexpr int K = (TEXG + FL - 1) / FL, KU = K < 3 ? K : 3;
+            for (int k0 = 0; k0 < K; k0 += KU) {
+              double x[KU];
+#pragma unroll
+              for (int k = 0; k < KU; ++k) {
+                const int i = (k0 + k) * FL + fl;
+                x[k] = (TEXG % FL == 0 && K % KU == 0) || i < TEXG ? gs[i] : 0.0;
+              }
+#pragma unroll
+              for (int k = 0; k < KU; ++k) {
+                const int i = (k0 + k) * FL + fl;
+                if (x[k] != 0.0) {
+                  gs[i] = 0.0;
+                  atomicAdd(dst + i, (float)x[k]);
+                }
               }
             }
           }
-          // each lane reads the sums its record gradient needs, and only then are they cleared
-          const float x = fl < kRecGrad ? record_gradient(fl, &s_sum[j * kSums], s_geo.g1[entry],
-                                                          s_geo.g2[entry], p.lp_scale)
-                                        : 0.f;
           __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
           __builtin_amdgcn_wave_barrier();
           if (fl < kSums) s_sum[j * kSums + fl] = 0.0;
-          if (x != 0.f) atomicAdd(&d_rec[(int64_t)r * kRecGrad + fl], x);
+          if (fl < kRecGrad && rg != 0.f) atomicAdd(&d_rec[(int64_t)r * kRecGrad + fl], rg);
         }
         // the next batch's texels load while the atomics above drain
         if (b0 + B < votes.total) stage_batch(b0 + B);
@@ -585,6 +652,13 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
   }  // lists
 }
 
+// Whether the tiles of a call all find room at once with the larger batches: then the LDS limits
+// nothing and a larger batch only means fewer barriers and flushes.
+template <int N>
+bool few_tiles(int64_t tiles) {
+  return tiles <= 256 * (N >= 16 ? 3 : 5);  // CUs times workgroups per CU
+}
+
 template <int N, bool BF16, bool MIXED = false>
 hipError_t launch_np(const Plan& pl, const gb_splats& sp, const BlendParams& bp,
                      const ViewDev* views, const SplatRec* rec, const PairList& first,
@@ -593,16 +667,25 @@ hipError_t launch_np(const Plan& pl, const gb_splats& sp, const BlendParams& bp,
   const dim3 grid((unsigned)(bp.tile_order ? (int64_t)bp.total_tiles
                                            : 8 * (int64_t)bp.tiles_per_xcd));
   const dim3 block((unsigned)(pl.tile_w * pl.tile_h));
-#define GBB_BWD_B(BB)                                                                         \
-  hipLaunchKernelGGL((blend_bwd_kernel<N, BF16, BB, MIXED>), grid, block, 0, s, views, rec, \
-                     first, rest, open_bits, sp.textures, bp, T_final, d_rgb, d_rec, d_tex)
+#define GBB_BWD_B(ASKED, FEW)                                                                  \
+  hipLaunchKernelGGL((blend_bwd_kernel<N, BF16, bwd_batch<N, MIXED>(ASKED, FEW), MIXED>), grid,  \
+                     block, 0, s, views, rec, first, rest, open_bits, sp.textures, bp, T_final,  \
+                     d_rgb, d_rec, d_tex)
+  const bool few = few_tiles<N>(bp.total_tiles);
   if constexpr (N >= 16) {
-    GBB_BWD_B(bwd_batch<N>(4));
+    if (few) GBB_BWD_B(4, true);
+    else GBB_BWD_B(4, false);
   } else {
     switch (pl.batch_bwd) {
-      case 8: GBB_BWD_B(bwd_batch<N>(8)); break;
-      case 32: GBB_BWD_B(bwd_batch<N>(32)); break;
-      default: GBB_BWD_B(bwd_batch<N>(16)); break;
+      case 8:
+        if (few) GBB_BWD_B(8, true);
+        else GBB_BWD_B(8, false);
+        break;
+      case 32:
+        if (few) GBB_BWD_B(32, true);
+        else GBB_BWD_B(32, false);
+        break;
+      default: GBB_BWD_B(16, true); break;
     }
   }
 #undef GBB_BWD_B

@@ -134,17 +134,35 @@ struct GeoLds {
 template <int N>
 struct TexLayout {
   static constexpr int kRow = N + 1;
-  static constexpr int kPerSplat = N * (N + 1);
+  static constexpr int kPerSplat = N == 1 ? 1 : N * (N + 1);
   // a 24-bit multiply (full rate; a 32-bit integer multiply is quarter rate): iu < N
   __device__ static int at(int iu, int iv) { return (int)__umul24((unsigned)iu, kRow) + iv; }
 };
 
-// A staged texel as one 16-byte LDS read (5.6 cycles of the CU's LDS for a wave). Left to the
-// compiler, which sees that the pad is unused, it becomes a 12-byte read, which takes 9.1.
-__device__ __forceinline__ float4 load_texel(const float4* t) {
-  const float4 x = *t;
-  __asm__ volatile("" : : "v"(x.w));
-  return x;
+// The four corner texels of a cell, each as one 16-byte LDS read (5.6 cycles of the CU's LDS for a
+// wave). Left to the compiler, which sees that the pad is unused, they become 12-byte reads, which
+// take 9.1. (All four are asked for before the one point that uses the pads: a use after each read
+// had put four LDS latencies one after another into every wave step.)
+template <int ROW>
+__device__ __forceinline__ void load_corners(const float4* t, float4& t00, float4& t01,
+                                             float4& t10, float4& t11) {
+  t00 = t[0];
+  t01 = t[1];
+  t10 = t[ROW];
+  t11 = t[ROW + 1];
+  __asm__ volatile("" : : "v"(t00.w), "v"(t01.w), "v"(t10.w), "v"(t11.w));
+}
+
+// Set bits of a uniform mask (two scalar counts).
+__device__ __forceinline__ int popcount64(uint64_t x) {
+  return __builtin_popcount((uint32_t)x) + __builtin_popcount((uint32_t)(x >> 32));
+}
+
+// A lane mask that is the same in every lane, kept in scalar registers.
+__device__ __forceinline__ uint64_t uniform64(uint64_t x) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x),
+                 hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
+  return (uint64_t)hi << 32 | lo;
 }
 
 // Entries (consecutive pairs of the tile's list) whose geometry one staging pass prepares: one
@@ -155,27 +173,31 @@ constexpr int kPassEntries = 64;
 // the entries that can reach this wave's block, `any` those that can reach some block of the
 // tile. Only the latter are given texel slots, in batches, so that a splat whose screen
 // rectangle touches the tile but whose footprint does not (about half of them) costs a geometry
-// test and nothing more. list[slot] is the entry of each slot, by falling (REVERSE) or rising
-// entry index; every wave writes the same list and reads only what it has written itself.
+// test and nothing more. list.entry[slot] is the entry of each slot, by falling (REVERSE) or rising
+// entry index, and list.rec[slot] its record (my_rec: the record of the lane's entry); every wave
+// writes the same list and reads only what it has written itself.
+template <int PE>
+struct SlotList {
+  uint32_t rec[PE];
+  uint8_t entry[PE];
+};
+
 struct PassVotes {
   uint64_t mine, any;
   int total;  // set bits of any
 };
 
-template <bool REVERSE>
-__device__ __forceinline__ PassVotes pass_votes(uint64_t mine, const uint64_t* s_mask, int n_waves,
-                                                int lane, uint8_t* s_list) {
-  uint64_t any = s_mask[0];
-  for (int k = 1; k < n_waves; ++k) any |= s_mask[k];
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)any),
-                 hi = __builtin_amdgcn_readfirstlane((uint32_t)(any >> 32));
+template <bool REVERSE, int PE>
+__device__ __forceinline__ PassVotes pass_votes(uint64_t mine, const uint64_t* s_mask, int lane, uint32_t my_rec, SlotList<PE>& list) {
   PassVotes v;
   v.mine = mine;
-  v.any = (uint64_t)hi << 32 | lo;
-  v.total = __builtin_popcount(lo) + __builtin_popcount(hi);
+  v.any = uniform64((s_mask[0] | s_mask[1]) | (s_mask[2] | s_mask[3]));
+  v.total = popcount64(v.any);
   if (__builtin_amdgcn_inverse_ballot_w64(v.any)) {
     const int below = (int)mbcnt(v.any);
-    s_list[REVERSE ? v.total - 1 - below : below] = (uint8_t)lane;
+    const int slot = REVERSE ? v.total - 1 - below : below;
+    list.entry[slot] = (uint8_t)lane;
+    list.rec[slot] = my_rec;
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -191,78 +213,84 @@ __device__ __forceinline__ int fresh_tid() {
   return t;
 }
 
-// Copies the texels of a batch of `nb` splats into LDS as float4 (RGB + pad) per texel. The
-// splat of slot j is pairs[list[j]] - rec_base: a tile's pairs all hold records of the tile's
-// view, so the splat follows from the pair list alone and the texel loads need not wait for the
-// records. For even N a splat's 3 N^2 channel values split into groups of 12 (four texels):
-// each thread moves whole groups, three 16-byte (float32) or 8-byte (bfloat16) loads in, four
-// LDS stores out.
+// Copies the texels of a batch of `nb` splats (even N) into LDS as float4 (RGB + pad) per texel.
+// Slot j holds the splat of record recs[j] (a tile's records are all of the tile's view, so the
+// splat is the record minus rec_base). A splat's 3 N^2 channel values split into groups of 12
+// (four texels): each thread moves whole groups, three 16-byte (float32) or 8-byte (bfloat16)
+// loads in, four LDS stores out.
 // With spec != null each texel also gets the record's view-dependent colour spec[record]
 // (the bilinear weights sum to one, so this adds that colour to the lookup).
-// FRESH: the thread index through fresh_tid (the backward, which is short of registers).
-template <int N, bool BF16, bool FRESH>
+template <int N, bool BF16>
 __device__ __forceinline__ void stage_texels(const void* __restrict__ textures,
-                                             const uint32_t* __restrict__ pairs,
-                                             const uint8_t* list, uint32_t rec_base, int nb,
-                                             float4* s_tex, const float4* __restrict__ spec) {
-  constexpr int per = 3 * N * N;  // channel values per splat
-  const int tid = FRESH ? fresh_tid() : (int)threadIdx.x, nthr = blockDim.x;
-  if constexpr ((per % 12) == 0) {
-    constexpr int groups = per / 12;  // = N^2 / 4
-    for (int gi = tid; gi < nb * groups; gi += nthr) {
-      const int j = gi / groups, a = gi - j * groups;
-      const uint32_t r = pairs[list[j]];
-      const int64_t src = ((int64_t)(r - rec_base) * groups + a) * 3;
-      const float4 sc = spec ? spec[r] : make_float4(0.f, 0.f, 0.f, 0.f);
-      float v[12];
-      if constexpr (BF16) {
-        const uint2* t = reinterpret_cast<const uint2*>(textures) + src;
+                                             const uint32_t* recs, uint32_t rec_base, int nb,
+                                             float4* s_tex, const float4* __restrict__ spec,
+                                             int tid) {
+  constexpr int groups = 3 * N * N / 12;
+#pragma unroll 1
+  for (int gi = tid; gi < nb * groups; gi += (int)blockDim.x) {
+    const int j = gi / groups, a = gi - j * groups;
+    const uint32_t r = recs[j];
+    const int64_t src = ((int64_t)(r - rec_base) * groups + a) * 3;
+    const float4 sc = spec ? spec[r] : make_float4(0.f, 0.f, 0.f, 0.f);
+    float v[12];
+    if constexpr (BF16) {
+      const uint2* t = reinterpret_cast<const uint2*>(textures) + src;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          const uint2 x = t[k];
-          v[4 * k + 0] = __uint_as_float(x.x << 16);
-          v[4 * k + 1] = __uint_as_float(x.x & 0xffff0000u);
-          v[4 * k + 2] = __uint_as_float(x.y << 16);
-          v[4 * k + 3] = __uint_as_float(x.y & 0xffff0000u);
-        }
-      } else {
-        const float4* t = reinterpret_cast<const float4*>(textures) + src;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          const float4 x = t[k];
-          v[4 * k + 0] = x.x;
-          v[4 * k + 1] = x.y;
-          v[4 * k + 2] = x.z;
-          v[4 * k + 3] = x.w;
-        }
+      for (int k = 0; k < 3; ++k) {
+        const uint2 x = t[k];
+        v[4 * k + 0] = __uint_as_float(x.x << 16);
+        v[4 * k + 1] = __uint_as_float(x.x & 0xffff0000u);
+        v[4 * k + 2] = __uint_as_float(x.y << 16);
+        v[4 * k + 3] = __uint_as_float(x.y & 0xffff0000u);
       }
-      float4* dst = s_tex + j * TexLayout<N>::kPerSplat;
+    } else {
+      const float4* t = reinterpret_cast<const float4*>(textures) + src;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int t = 4 * a + k, iu = t / N, iv = t - iu * N;
-        dst[TexLayout<N>::at(iu, iv)] =
-            spec ? make_float4(v[3 * k] + sc.x, v[3 * k + 1] + sc.y, v[3 * k + 2] + sc.z, 0.f)
-                 : make_float4(v[3 * k], v[3 * k + 1], v[3 * k + 2], 0.f);
+      for (int k = 0; k < 3; ++k) {
+        const float4 x = t[k];
+        v[4 * k + 0] = x.x;
+        v[4 * k + 1] = x.y;
+        v[4 * k + 2] = x.z;
+        v[4 * k + 3] = x.w;
       }
     }
-  } else {
-    for (int e = tid; e < nb * per; e += nthr) {
-      const int j = e / per, r = e - j * per;
-      const uint32_t id = pairs[list[j]];
-      const int64_t k = (int64_t)(id - rec_base);
-      float x;
-      if constexpr (BF16)
-        x = bf16_to_f32(reinterpret_cast<const uint16_t*>(textures)[k * per + r]);
-      else
-        x = reinterpret_cast<const float*>(textures)[k * per + r];
-      if (spec) {
-        const float4 sc = spec[id];
-        x += (r % 3) == 0 ? sc.x : (r % 3) == 1 ? sc.y : sc.z;
-      }
-      const int t = r / 3, iu = t / N, iv = t - iu * N;
-      reinterpret_cast<float*>(s_tex + j * TexLayout<N>::kPerSplat + TexLayout<N>::at(iu, iv))[r % 3] = x;
+    float4* dst = s_tex + j * TexLayout<N>::kPerSplat;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int t = 4 * a + k, iu = t / N, iv = t - iu * N;
+      dst[TexLayout<N>::at(iu, iv)] =
+          spec ? make_float4(v[3 * k] + sc.x, v[3 * k + 1] + sc.y, v[3 * k + 2] + sc.z, 0.f)
+               : make_float4(v[3 * k], v[3 * k + 1], v[3 * k + 2], 0.f);
     }
   }
+}
+
+// The texel of record r's splat where grids have one texel (N = 1), with the view-dependent colour
+// as above. Such texels are staged with the pass's geometry, one per entry: they cost less than the
+// second trip to memory that texels of chosen entries wait for.
+template <bool BF16>
+__device__ __forceinline__ float4 one_texel(const void* __restrict__ textures, uint32_t r,
+                                            uint32_t rec_base, const float4* __restrict__ spec) {
+  const int64_t i = 3 * (int64_t)(r - rec_base);
+  float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+  if constexpr (BF16) {
+    const uint16_t* t = reinterpret_cast<const uint16_t*>(textures) + i;
+    x.x = bf16_to_f32(t[0]);
+    x.y = bf16_to_f32(t[1]);
+    x.z = bf16_to_f32(t[2]);
+  } else {
+    const float* t = reinterpret_cast<const float*>(textures) + i;
+    x.x = t[0];
+    x.y = t[1];
+    x.z = t[2];
+  }
+  if (spec) {
+    const float4 sc = spec[r];
+    x.x += sc.x;
+    x.y += sc.y;
+    x.z += sc.z;
+  }
+  return x;
 }
 
 // Row and column of texel t (< 256) of an n-texel side (n <= 16): t / n as a multiply by
@@ -278,10 +306,9 @@ __device__ __forceinline__ int grid_side(const BlendParams& p, uint32_t k) {
 }
 
 // What each lane holds of its entry of the pass in a call with grids of several sides: the
-// record, the grid's side, its uv -> grid slope and its first value in the texture array. The
+// grid's side, its uv -> grid slope and its first value in the texture array. The
 // waves read an entry's values back with readlane (the entry is uniform over the wave).
 struct EntryGrid {
-  uint32_t rec;
   int n;
   float scale;
   int64_t first;
@@ -297,7 +324,6 @@ template <int N>
 __device__ __forceinline__ EntryGrid entry_grid(const BlendParams& p, uint32_t r,
                                                 uint32_t rec_base) {
   EntryGrid g;
-  g.rec = r;
   g.n = grid_side<N>(p, r - rec_base);
   g.scale = grid_scale(g.n, p.sigma);
   g.first = 3 * p.grid_at[r - rec_base];
@@ -319,7 +345,8 @@ __device__ __forceinline__ int64_t readlane64(int64_t x, int lane) {
 // corners of cell (0, 0) with weights (1, 0, 0, 0) there, reads finite values.
 template <int N, bool BF16>
 __device__ __forceinline__ void stage_texels_mixed(const void* __restrict__ textures,
-                                                   const uint8_t* list, int nb, float4* s_tex,
+                                                   const uint8_t* list, const uint32_t* recs,
+                                                   int nb, float4* s_tex,
                                                    const float4* __restrict__ spec,
                                                    const EntryGrid& eg) {
   const int tid = fresh_tid(), lane = tid & 63, nw = (int)(blockDim.x >> 6);
@@ -327,8 +354,7 @@ __device__ __forceinline__ void stage_texels_mixed(const void* __restrict__ text
     const int e = __builtin_amdgcn_readfirstlane((int)list[j]);
     const int n = __builtin_amdgcn_readlane(eg.n, e);
     const int64_t base = readlane64(eg.first, e);
-    const float4 sc = spec ? spec[(uint32_t)__builtin_amdgcn_readlane((int)eg.rec, e)]
-                           : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 sc = spec ? spec[recs[j]] : make_float4(0.f, 0.f, 0.f, 0.f);
     float4* dst = s_tex + j * TexLayout<N>::kPerSplat;
     // texel at value index i (its three channels), with the view-dependent colour added
     auto texel = [&](int64_t i) {

@@ -4,9 +4,12 @@
 // can reach it (a wave whose pixels have all terminated votes for none); the splats that reach
 // some block have their texels staged into LDS in batches (bfloat16 decoded on staging) and are
 // walked by the waves that they reach. The workgroup stops when every wave has terminated.
-// Bound by VALU issue (about 85 wave instructions per evaluated wave and splat, staging included).
-// Staging only the splats that reach a block, and their geometry by all waves at once: at 1M
-// splats and 1080p 0.509 -> 0.456 ms, 16 x 16 grids 1.24 -> 0.84, sides {2, 4, 8} 0.745 -> 0.577.
+// Bound by VALU issue where tiles fill the chip, and by the latency of a wave's step (two LDS
+// round trips) where they do not. Staging only the splats that reach a block and their geometry by
+// all waves at once, the four corner texels in flight together, and the open pixels as a scalar
+// lane mask (a flag per lane cost copies of the pixel's state around every branch): at 1M splats
+// and 1080p 0.509 -> 0.382 ms, 16 x 16 grids 1.24 -> 0.80, sides {2, 4, 8} 0.745 -> 0.490, 3M splats
+// on four 1080p views 4.91 -> 3.85, 350k small splats on 135 tiles 0.363 -> 0.312.
 //
 // Per pixel and splat: (u, v) from the centre-relative homography, G = exp(-min(q_uv, q_lp)),
 // alpha = min(alpha_max, o G); alpha < alpha_min is skipped; if T (1 - alpha) < t_min the
@@ -27,22 +30,21 @@ namespace {
 // by t_min, lane evaluations (64 per wave and evaluated splat) and staged (tile, splat) pairs;
 // the rest pass also adds its blended pairs to stats[4].
 // Occupancy target: eight waves per SIMD, or what the 160 KB of LDS per CU allows (a
-// workgroup puts one wave on each of the CU's four SIMDs). Grids of several sides (MIXED) ask
-// for at most seven: at eight their 64-VGPR budget spills.
-template <int N, int B, bool MIXED>
+// workgroup puts one wave on each of the CU's four SIMDs).
+template <int N, int B>
 constexpr int fwd_min_waves() {
-  constexpr int lds = (int)sizeof(GeoLds<kPassEntries>) + 256 + B * TexLayout<N>::kPerSplat * 16;
-  constexpr int w = 160 * 1024 / lds < 8 ? 160 * 1024 / lds : 8;
-  return MIXED && w > 7 ? 7 : w;
+  constexpr int lds = (int)sizeof(GeoLds<kPassEntries>) + 512 + B * TexLayout<N>::kPerSplat * 16;
+  return 160 * 1024 / lds < 8 ? 160 * 1024 / lds : 8;
 }
 
 // Splats per batch: the number asked for, or fewer where that lets eight workgroups share a CU's
-// LDS beside the pass's 6 KB of geometry. 8 x 8 grids (1.1 KB of texels per splat), forward ms at
-// 1M splats and 1080p / 3M splats on four 1080p views: batches of 8 0.482 / 5.26, 12 0.458 / 4.75,
-// 16 0.501 / 5.28. 16 x 16 grids (4.3 KB) at 1M splats: 2 0.915, 3 0.840, 4 0.854.
+// LDS beside the pass's 6 KB of geometry. 8 x 8 grids (1.1 KB of texels per splat), when a step
+// still took 0.458 ms at 1M splats and 1080p, there and at 3M splats on four 1080p views: batches
+// of 8 0.482 / 5.26, 12 0.458 / 4.75, 16 0.501 / 5.28. 16 x 16 grids (4.3 KB) at 1M splats: 2 0.915,
+// 3 0.840, 4 0.854. One-texel grids stage their texels with the geometry, a whole pass at once.
 template <int N>
 constexpr int fwd_batch(int asked) {
-  return N >= 16 ? 3 : N == 8 && asked == 16 ? 12 : asked;
+  return N == 1 ? kPassEntries : N >= 16 ? 3 : N == 8 && asked == 16 ? 12 : asked;
 }
 
 // This workgroup's slices of the arrays to zero (the coming backward's texture and record
@@ -72,7 +74,7 @@ __device__ __forceinline__ void zero_slice(const BlendParams& p) {
 
 // MIXED: each splat has a grid side of its own (at most N), read from p.grid_n.
 template <int N, bool BF16, int B, bool STATS, bool REST, bool MIXED>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fwd_min_waves<N, B, MIXED>())))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fwd_min_waves<N, B>())))
 blend_fwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__ rec,
                  const uint32_t* __restrict__ pair_vals, const uint32_t* __restrict__ ranges,
                  const void* __restrict__ textures, BlendParams p, float* __restrict__ rgb,
@@ -82,7 +84,8 @@ blend_fwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
   __shared__ float4 s_tex[B * TexLayout<N>::kPerSplat];
   // the waves' votes of a pass, of which two can be in use at a time
   __shared__ uint64_t s_mask[2][4];
-  __shared__ uint8_t s_list[kPassEntries];
+  __shared__ SlotList<kPassEntries> s_list;
+  __shared__ uint64_t s_open[2][4];  // the waves' open pixels, likewise
 
   const int tile = tile_of_block(p);
   if (tile >= p.total_tiles) {
@@ -118,7 +121,7 @@ blend_fwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
   float T = 1.0f;
   float acc0 = 0.f, acc1 = 0.f, acc2 = 0.f;
   uint32_t last = start;
-  bool done = !inside;
+  bool done = !inside;  // before the list
   if (REST && inside) {
     const float4 sv = split.fwd_state[pix];
     acc0 = sv.x;
@@ -127,113 +130,137 @@ blend_fwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
     done = sv.w != 0.f;
     T = T_final[pix];
   }
+  // pixels still open, as a lane mask in scalar registers
+  uint64_t open = ballot(!done);
   uint32_t st_blend = 0, st_eval = 0;
   bool st_term = false;
   const int kbx = tile_x0 + bx, kby = tile_y0 + by;  // the wave block's first pixel
-  int parity = 0;
+  int parity = 0, open_set = 0;
   bool all_done = false;
+  // whether some pixel of the tile is open; a barrier of the tile (two sets of masks: a wave may
+  // set the next call's while another still reads this one's)
+  auto tile_open = [&]() {
+    uint64_t* const m = s_open[open_set];
+    open_set ^= 1;
+    if (lane == 0) m[w] = open;
+    __syncthreads();
+    return uniform64((m[0] | m[1]) | (m[2] | m[3])) != 0;
+  };
+  // entries of waves that the workgroup does not have
+  if (tid < 8 && (tid & 3) >= n_waves) s_mask[tid >> 2][tid & 3] = s_open[tid >> 2][tid & 3] = 0;
+
+  // the record of the lane's entry, loaded a pass ahead
+  uint32_t my_rec = start + (uint32_t)lane < end ? pair_vals[start + (uint32_t)lane] : rec_base;
 
   for (uint32_t b = start; b < end && !all_done; b += (uint32_t)kPassEntries) {
     // a pass: entries [b, b + n) of the list, one per lane, for the wave's own block
     const int n = (int)((end - b) < (uint32_t)kPassEntries ? (end - b) : (uint32_t)kPassEntries);
     if (STATS && tid == 0) atomicAdd(&stats[3], (unsigned long long)n);
     uint64_t mine = 0;
-    EntryGrid eg{0u, 1, 0.f, 0};
-    const bool wave_open = ballot(!done) != 0;
+    EntryGrid eg{1, 0.f, 0};
+    const bool wave_open = open != 0;
     // wave 0 also stores what the blocks share of a splat's geometry
     if (w == 0 || wave_open) {
       bool may = false;
       if (lane < n) {
-        const SplatRec R = rec[pair_vals[b + (uint32_t)lane]];
+        const SplatRec R = rec[my_rec];
         const StagedGeo g = stage_geo(R, kbx + 4, kby + 4, tcx, tcy);
         s_geo.store(w, lane, g);
+        if constexpr (N == 1) {
+          if (w == 0) s_tex[lane] = one_texel<BF16>(textures, my_rec, rec_base, p.spec);
+        }
         may = wave_open && block_may_contribute(g, (float)(kbx + 4 - tcx), (float)(kby + 4 - tcy),
                                                 kbx, kby, p);
       }
       mine = ballot(may);
     }
     if constexpr (MIXED) {
-      if (lane < n) eg = entry_grid<N>(p, pair_vals[b + (uint32_t)lane], rec_base);
+      if (lane < n) eg = entry_grid<N>(p, my_rec, rec_base);
     }
     if (lane == 0) s_mask[parity][w] = mine;
     __syncthreads();
-    const PassVotes votes = pass_votes<false>(mine, s_mask[parity], n_waves, lane, s_list);
+    const PassVotes votes =
+        pass_votes<false>(mine, s_mask[parity], lane, my_rec, s_list);
+    {
+      const uint32_t next = b + (uint32_t)(kPassEntries + lane);
+      if (next < end) my_rec = pair_vals[next];
+    }
     parity ^= 1;
 
     uint64_t ahead = ~0ull;  // entries that no batch has taken yet
     for (int b0 = 0; b0 < votes.total; b0 += B) {
       const int nb = votes.total - b0 < B ? votes.total - b0 : B;
-      if constexpr (MIXED)
-        stage_texels_mixed<N, BF16>(textures, s_list + b0, nb, s_tex, p.spec, eg);
+      if constexpr (N == 1)
+        ;  // staged with the geometry
+      else if constexpr (MIXED)
+        stage_texels_mixed<N, BF16>(textures, s_list.entry + b0, s_list.rec + b0, nb, s_tex,
+                                    p.spec, eg);
       else
-        stage_texels<N, BF16, false>(textures, pair_vals + b, s_list + b0, rec_base, nb, s_tex,
-                                     p.spec);
-      __syncthreads();
+        stage_texels<N, BF16>(textures, s_list.rec + b0, rec_base, nb, s_tex, p.spec, tid);
+      if constexpr (N > 1) __syncthreads();
       const uint64_t batch =
-          ahead & (~0ull >> (63 - __builtin_amdgcn_readfirstlane((int)s_list[b0 + nb - 1])));
+          ahead & (~0ull >> (63 - __builtin_amdgcn_readfirstlane((int)s_list.entry[b0 + nb - 1])));
       ahead &= ~batch;
-      if (ballot(!done) != 0) {
+      if (open != 0) {
         // the batch's splats that can reach the wave's block
         uint64_t todo = votes.mine & batch;
         while (todo != 0) {
           const int j = (int)__builtin_ctzll(todo);
-          const uint64_t before = votes.any & ((1ull << j) - 1ull);
           todo &= todo - 1;
           const StagedGeo g = s_geo.load(w, j);
           const PixelEval e = eval_splat(g, lx, ly, tx, ty, p);
           if (STATS) ++st_eval;
-          if (!done & (e.r2 != 0.0f) & (e.alpha >= p.alpha_min)) {
-            const float Tn = T * (1.0f - e.alpha);
-            if (Tn < p.t_min) {
-              done = true;
-              if (STATS) st_term = true;
+          // pixels that the splat stops, and those that blend it
+          const uint64_t hit = open & ballot(e.r2 != 0.0f) & ballot(e.alpha >= p.alpha_min);
+          const float Tn = T * (1.0f - e.alpha);
+          const uint64_t stop = hit & ballot(Tn < p.t_min);
+          open = uniform64(open & ~stop);
+          const uint64_t blend = hit & ~stop;
+          if (STATS && __builtin_amdgcn_inverse_ballot_w64(stop)) st_term = true;
+          if (__builtin_amdgcn_inverse_ballot_w64(blend)) {
+            if (STATS) ++st_blend;
+            float c0, c1, c2;
+            // the splat's slot: taken slots of the pass before this entry's
+            const int slot = popcount64(votes.any & ((1ull << j) - 1ull)) - b0;
+            const float4* tex = s_tex + (N == 1 ? j : slot) * TexLayout<N>::kPerSplat;
+            if constexpr (N == 1) {
+              const float4 t = tex[0];
+              c0 = t.x;
+              c1 = t.y;
+              c2 = t.z;
             } else {
-              if (STATS) ++st_blend;
-              float c0, c1, c2;
-              const int slot = __builtin_popcount((uint32_t)before) +
-                               __builtin_popcount((uint32_t)(before >> 32)) - b0;
-              const float4* tex = s_tex + slot * TexLayout<N>::kPerSplat;
-              if constexpr (N == 1) {
-                const float4 t = tex[0];
-                c0 = t.x;
-                c1 = t.y;
-                c2 = t.z;
+              int iu, iv;
+              float fu, fv;
+              if constexpr (MIXED) {
+                const int ns = __builtin_amdgcn_readlane(eg.n, j);
+                const float sc = __int_as_float(
+                    __builtin_amdgcn_readlane(__float_as_int(eg.scale), j));
+                grid_coord_n(e.u, sc, ns, iu, fu);
+                grid_coord_n(e.v, sc, ns, iv, fv);
               } else {
-                int iu, iv;
-                float fu, fv;
-                if constexpr (MIXED) {
-                  const int ns = __builtin_amdgcn_readlane(eg.n, j);
-                  const float sc = __int_as_float(
-                      __builtin_amdgcn_readlane(__float_as_int(eg.scale), j));
-                  grid_coord_n(e.u, sc, ns, iu, fu);
-                  grid_coord_n(e.v, sc, ns, iv, fv);
-                } else {
-                  grid_coord<N>(e.u, p, iu, fu);
-                  grid_coord<N>(e.v, p, iv, fv);
-                }
-                const float4* t = tex + TexLayout<N>::at(iu, iv);
-                const int kr = TexLayout<N>::kRow;
-                const float4 t00 = load_texel(t), t01 = load_texel(t + 1);
-                const float4 t10 = load_texel(t + kr), t11 = load_texel(t + kr + 1);
-                const float a0 = t00.x + fv * (t01.x - t00.x), b0_ = t10.x + fv * (t11.x - t10.x);
-                const float a1 = t00.y + fv * (t01.y - t00.y), b1 = t10.y + fv * (t11.y - t10.y);
-                const float a2 = t00.z + fv * (t01.z - t00.z), b2 = t10.z + fv * (t11.z - t10.z);
-                c0 = a0 + fu * (b0_ - a0);
-                c1 = a1 + fu * (b1 - a1);
-                c2 = a2 + fu * (b2 - a2);
+                grid_coord<N>(e.u, p, iu, fu);
+                grid_coord<N>(e.v, p, iv, fv);
               }
-              const float wgt = e.alpha * T;
-              acc0 += wgt * c0;
-              acc1 += wgt * c1;
-              acc2 += wgt * c2;
-              T = Tn;
-              last = b + (uint32_t)j + 1u;
+              float4 t00, t01, t10, t11;
+              load_corners<TexLayout<N>::kRow>(tex + TexLayout<N>::at(iu, iv), t00, t01, t10, t11);
+              const float a0 = t00.x + fv * (t01.x - t00.x), b0_ = t10.x + fv * (t11.x - t10.x);
+              const float a1 = t00.y + fv * (t01.y - t00.y), b1 = t10.y + fv * (t11.y - t10.y);
+              const float a2 = t00.z + fv * (t01.z - t00.z), b2 = t10.z + fv * (t11.z - t10.z);
+              c0 = a0 + fu * (b0_ - a0);
+              c1 = a1 + fu * (b1 - a1);
+              c2 = a2 + fu * (b2 - a2);
             }
+            const float wgt = e.alpha * T;
+            acc0 += wgt * c0;
+            acc1 += wgt * c1;
+            acc2 += wgt * c2;
+            T = Tn;
+            last = b + (uint32_t)j + 1u;
           }
-          if (ballot(!done) == 0) break;
+          if (open == 0) break;
         }
       }
-      all_done = __syncthreads_and(done);
+      all_done = !tile_open();
       if (all_done) break;
     }
   }
@@ -263,12 +290,14 @@ blend_fwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
   }
   if (!REST && split.mode == kPrefixPass) {
     // a tile with an open pixel takes part in the rest pass
-    if (!__syncthreads_and(done)) {
+    if (tile_open()) {
       if (tid == 0) {
         atomicOr(&split.open_bits[tile >> 5], 1u << (tile & 31));
         atomicOr(split.any_open, 1u);
       }
-      if (inside) split.fwd_state[pix] = make_float4(acc0, acc1, acc2, done ? 1.f : 0.f);
+      if (inside)
+        split.fwd_state[pix] = make_float4(
+            acc0, acc1, acc2, __builtin_amdgcn_inverse_ballot_w64(open) ? 0.f : 1.f);
     }
   }
   if (STATS) {

@@ -26,6 +26,14 @@ def test_lists_at_the_edges_of_a_pass(gb, N, P):  # noqa: F811
     check_grads(gb, scene, view, opts, (0, 0, 37, 29), seed=P)
 
 
+@pytest.mark.parametrize("N", [4, 8, 16])
+def test_batches_of_a_call_with_many_tiles(gb, N):  # noqa: F811
+    # 41 x 37 tiles: more than run at once with the larger batches, so that smaller ones are taken
+    scene = sg.make_scene(17, 150, -0.1, 0.1, 0.002, 0.1, N, op_lo=0.02, op_hi=0.2)
+    view = sg.look_at_view((0.05, 0.02, -2.0), 656, 592)
+    check_grads(gb, scene, view, O.Options(), (304, 276, 48, 40), seed=N)
+
+
 @pytest.mark.parametrize("layout,sides", [(8, (1, 2, 3, 8)), (16, (1, 2, 5, 16))])
 def test_thin_splats_with_grids_of_several_sides(gb, layout, sides):  # noqa: F811
     scene = sg.make_scene(7, 200, -0.5, 0.5, 0.001, 0.4, 2)
