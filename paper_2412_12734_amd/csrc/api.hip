@@ -164,6 +164,9 @@ gb_status make_plan(int32_t P, int32_t N, const gb_view* views, int32_t n_views,
   // tiles stay open after a smaller prefix
   const int64_t per_tile = o->prefix_pairs_per_tile > 0 ? o->prefix_pairs_per_tile : 1024;
   pl->prefix_cap = pl->split ? align_up_i64(per_tile * tiles, 1024) : 0;
+  // pairs that all fit the prefix pass leave nothing for a rest pass (14 launches, 45 to 60 us
+  // however little they find)
+  pl->rest = pl->split && capacity > pl->prefix_cap;
   if (capacity + pl->prefix_cap > (int64_t)0xFFFFFFF0)
     return arg_fail("pair capacity plus the prefix pass's slots exceed 2^32-16");
   pl->ordered = o->tile_order >= 0 && tiles <= kMaxOrderedTiles;
@@ -751,28 +754,40 @@ static gb_status render_fwd_impl(const gb_splats* s, const gb_view* views, int32
   SplatRec* rec = at<SplatRec>(ws, pl.off_rec);
   unsigned long long* d_stats = at<unsigned long long>(ws, pl.off_stats);
 
-  // depth order of all records: sort the key copy written by the preprocess, carrying
-  // record indices (the offsets array is free until the scan and serves as ping-pong space)
+  // depth order of all records: few by counting ranks, else by sorting the key copy written by the
+  // preprocess, carrying record indices (the offsets array is free until the scan and serves as
+  // ping-pong space)
   GBB_TRY(stage_mark(kStDepthSort, 0, hs), "timing");
-  GBB_TRY(launch_radix_sort(dk_a, order, offsets, order_alt, nullptr, pl.VP, 32, hist, digit_tot,
-                            hs),
-          "depth sort");
+  if (pl.VP <= kRankMax)
+    GBB_TRY(launch_rank_order(at<uint32_t>(ws, pl.off_depth_key), pl.VP, order, hs), "depth order");
+  else
+    GBB_TRY(launch_radix_sort(dk_a, order, offsets, order_alt, nullptr, pl.VP, 32, hist, digit_tot,
+                              nullptr, nullptr, hs),
+            "depth sort");
   GBB_TRY(stage_mark(kStDepthSort, 1, hs), "timing");
   // tile counts in depth order -> pair offsets and K; with the split, the prefix cut
   GBB_TRY(stage_mark(kStPairScan, 0, hs), "timing");
   uint32_t* chunk_owner = at<uint32_t>(ws, pl.off_chunk_owner);
   unsigned long long* partials64 = at<unsigned long long>(ws, pl.off_partials64);
-  GBB_TRY(launch_scan_u32(count, order, offsets, pl.VP, partials, &d_st->K, &d_st->K64,
-                          partials64, hs, chunk_owner, pl.n_chunks),
-          "pair scan");
   const StatusEcho echo{(uint32_t)n_views, (uint32_t)pl.P, (unsigned long long)pl.off_count,
                         (unsigned long long)pl.off_view_pairs};
-  GBB_TRY(launch_finalize_count(offsets, pl.VP, d_st, pl.capacity, echo, m_dev, overflow_flag,
-                                pl.split ? pl.prefix_cap : 0, chunk_owner, hs),
-          "finalize count");
+  const int64_t budget = pl.split ? pl.prefix_cap : 0;
+  if (pl.VP <= kSmallScan) {
+    GBB_TRY(launch_scan_finalize(count, order, pl.VP, offsets, chunk_owner, pl.n_chunks, d_st,
+                                 pl.capacity, echo, m_dev, overflow_flag, budget, hs),
+            "pair scan");
+  } else {
+    GBB_TRY(launch_scan_u32(count, order, offsets, pl.VP, partials, &d_st->K, &d_st->K64,
+                            partials64, hs, chunk_owner, pl.n_chunks),
+            "pair scan");
+    GBB_TRY(launch_finalize_count(offsets, pl.VP, d_st, pl.capacity, echo, m_dev, overflow_flag,
+                                  budget, chunk_owner, hs),
+            "finalize count");
+  }
   GBB_TRY(stage_mark(kStPairScan, 1, hs), "timing");
   // first (or only) pass: pairs of the depth prefix, sorted by tile, ranges, blend
-  const int64_t cap_a = pl.split ? pl.prefix_cap : pl.capacity;
+  const int64_t cap_a = pl.rest ? pl.prefix_cap : pl.capacity;
+  const bool odd = (radix_passes(pl.tile_bits) & 1) != 0;  // where the sort takes its input
   GBB_TRY(stage_mark(kStDuplicate, 0, hs), "timing");
   // the duplicate launch also zeroes the tile ranges and, with the split, the open-tile bitmap
   ClearList clear_a;
@@ -783,23 +798,24 @@ static gb_status render_fwd_impl(const gb_splats* s, const gb_view* views, int32
     clear_a.n[1] = (pl.total_tiles + 31) / 32;
   }
   GBB_TRY(launch_duplicate(order, count, offsets, chunk_owner, rec, d_views, pl.tile_w, pl.tile_h,
-                           d_st, cap_a, pk, pv, clear_a, hs),
+                           d_st, cap_a, odd ? pk_a : pk, odd ? pv_a : pv, clear_a, hs),
           "duplicate");
   GBB_TRY(stage_mark(kStDuplicate, 1, hs), "timing");
   GBB_TRY(stage_mark(kStTileSort, 0, hs), "timing");
+  bool have_ranges = false;
   GBB_TRY(launch_radix_sort(pk, pv, pk_a, pv_a, &d_st->n_sorted, cap_a, pl.tile_bits, hist,
-                            digit_tot, hs),
+                            digit_tot, ranges, &have_ranges, hs),
           "tile sort");
   GBB_TRY(stage_mark(kStTileSort, 1, hs), "timing");
   GBB_TRY(stage_mark(kStRanges, 0, hs), "timing");
-  GBB_TRY(launch_ranges(pk, &d_st->n_sorted, cap_a, ranges, hs), "ranges");
+  if (!have_ranges) GBB_TRY(launch_ranges(pk, &d_st->n_sorted, cap_a, ranges, hs), "ranges");
   GBB_TRY(stage_mark(kStRanges, 1, hs), "timing");
   // per-tile blended spans for the backward's work order
   uint32_t* tile_work = pl.ordered ? at<uint32_t>(ws, pl.off_tile_work) : nullptr;
   if (stats)
     GBB_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(d_stats), 0u, 16, hs), "clear stats");
   SplitState split{kSinglePass, nullptr, nullptr, nullptr};
-  if (pl.split) {
+  if (pl.rest) {
     split.mode = kPrefixPass;
     split.open_bits = at<uint32_t>(ws, pl.off_open_bits);
     split.fwd_state = at<float4>(ws, pl.off_fwd_state);
@@ -818,7 +834,7 @@ static gb_status render_fwd_impl(const gb_splats* s, const gb_view* views, int32
   GBB_TRY(stage_mark(kStBlendFwd, 1, hs), "timing");
   if (zero_tex) zeroed_set(ws, kZeroTex, zero_tex, zero_n);
   zeroed_set(ws, kZeroRec, d_rec, rec_n);
-  if (!pl.split) return GB_OK;
+  if (!pl.rest) return GB_OK;
 
   // rest pass: the remaining records, paired with the tiles the prefix left open
   uint32_t* count_rest = at<uint32_t>(ws, pl.off_count_rest);
@@ -843,12 +859,13 @@ static gb_status render_fwd_impl(const gb_splats* s, const gb_view* views, int32
   clear_r.n[0] = 2 * pl.total_tiles;
   GBB_TRY(launch_duplicate_rest(order, count_rest, offsets_rest, chunk_owner, rec, d_views,
                                 pl.tile_w, pl.tile_h, d_st, split.open_bits, sat, pl.capacity,
-                                pk_r, pv_r, clear_r, hs),
+                                odd ? pk_ra : pk_r, odd ? pv_ra : pv_r, clear_r, hs),
           "rest duplicate");
   GBB_TRY(launch_radix_sort(pk_r, pv_r, pk_ra, pv_ra, &d_st->n_rest, pl.capacity, pl.tile_bits,
-                            hist, at<uint32_t>(ws, pl.off_digit_tot), hs),
+                            hist, digit_tot, ranges_rest, &have_ranges, hs),
           "rest tile sort");
-  GBB_TRY(launch_ranges(pk_r, &d_st->n_rest, pl.capacity, ranges_rest, hs), "rest ranges");
+  if (!have_ranges)
+    GBB_TRY(launch_ranges(pk_r, &d_st->n_rest, pl.capacity, ranges_rest, hs), "rest ranges");
   GBB_TRY(stage_mark(kStRestTiles, 1, hs), "timing");
   split.mode = kRestPass;
   GBB_TRY(stage_mark(kStBlendFwdRest, 0, hs), "timing");
@@ -961,7 +978,7 @@ gb_status gb_render_bwd(const gb_splats* s, const gb_view* views, int32_t n_view
   const PairList first{pv, at<uint32_t>(ws, pl.off_ranges), at<uint32_t>(ws, pl.off_n_last)};
   PairList rest{nullptr, nullptr, nullptr};
   const uint32_t* open_bits = nullptr;
-  if (pl.split) {
+  if (pl.rest) {
     rest = PairList{pv + pl.prefix_cap, at<uint32_t>(ws, pl.off_ranges_rest),
                     at<uint32_t>(ws, pl.off_n_last_rest)};
     open_bits = at<uint32_t>(ws, pl.off_open_bits);

@@ -322,12 +322,14 @@ radix_offsets_kernel(const uint32_t* __restrict__ d_n, int64_t n_cap,
   }
 }
 
+// Places one tile's elements (from `base`, up to n): gstart is the output index of the tile's first
+// element of digit threadIdx.x (< the number of digits). All 256 threads take part.
 template <int NBITS>
-__global__ void __launch_bounds__(kRadixThreads)
-radix_scatter_kernel(const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
-                     uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out,
-                     const uint32_t* __restrict__ d_n, int64_t n_cap, int shift,
-                     const uint32_t* __restrict__ hist_scanned, uint32_t* __restrict__ digit_tot) {
+__device__ __forceinline__ void scatter_tile(const uint32_t* __restrict__ keys_in,
+                                             const uint32_t* __restrict__ vals_in,
+                                             uint32_t* __restrict__ keys_out,
+                                             uint32_t* __restrict__ vals_out, int64_t n,
+                                             int64_t base, int shift, uint32_t gstart) {
   constexpr int kBins = 1 << NBITS;
   constexpr uint32_t kMask = (uint32_t)kBins - 1u;
   constexpr int kWaves = kRadixThreads / 64;
@@ -338,95 +340,168 @@ radix_scatter_kernel(const uint32_t* __restrict__ keys_in, const uint32_t* __res
   __shared__ uint32_t s_start[256];
   __shared__ uint32_t s_gofs[kBins];  // output index of the tile's element 0 of each digit
   __shared__ uint32_t wave_tot[4];
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const int nvalid = (int)((n - base) < kRadixTile ? (n - base) : kRadixTile);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) s_cnt[w][lane + 64 * k] = 0;
+  __builtin_amdgcn_wave_barrier();
+  // Each wave ranks its own contiguous quarter of the tile in rounds of 64 elements; program
+  // order inside the wave keeps equal digits in index order.
+  uint32_t key_r[kRadixItems], val_r[kRadixItems], rank_r[kRadixItems];
+  // all loads first (memory-level parallelism)
+#pragma unroll
+  for (int r = 0; r < kRadixItems; ++r) {
+    const int i = w * kPerWave + r * 64 + lane;
+    const bool valid = i < nvalid;
+    key_r[r] = valid ? keys_in[base + i] : 0u;
+    val_r[r] = valid ? vals_in[base + i] : 0u;
+  }
+#pragma unroll
+  for (int r = 0; r < kRadixItems; ++r) {
+    const int i = w * kPerWave + r * 64 + lane;
+    const bool valid = i < nvalid;
+    const uint32_t d = (key_r[r] >> shift) & kMask;
+    // lanes holding the same digit: one ballot per digit bit
+    uint64_t m = ballot(valid);
+#pragma unroll
+    for (int bit = 0; bit < NBITS; ++bit) {
+      const bool set = (d >> bit) & 1u;
+      const uint64_t b = ballot(set);
+      m &= set ? b : ~b;
+    }
+    const uint32_t below = mbcnt(m);
+    const uint32_t cnt = s_cnt[w][d];
+    __builtin_amdgcn_wave_barrier();
+    if (valid && below == 0) s_cnt[w][d] = cnt + popc64(m);
+    __builtin_amdgcn_wave_barrier();
+    rank_r[r] = cnt + below;
+  }
+  __syncthreads();
+  // digit totals of the tile, offsets of each wave inside a digit, digit starts
+  uint32_t tot = 0;
+#pragma unroll
+  for (int ww = 0; ww < kWaves; ++ww) {
+    const uint32_t c = s_cnt[ww][tid];
+    s_cnt[ww][tid] = tot;
+    tot += c;
+  }
+  uint32_t total;
+  const uint32_t incl = block_inclusive_scan(tot, wave_tot, &total);
+  s_start[tid] = incl - tot;
+  // element counts fit in 32 bits, so output indices do too
+  if (tid < kBins) s_gofs[tid] = gstart - (incl - tot);
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kRadixItems; ++r) {
+    const int i = w * kPerWave + r * 64 + lane;
+    if (i < nvalid) {
+      const uint32_t d = (key_r[r] >> shift) & kMask;
+      const uint32_t pos = s_start[d] + s_cnt[w][d] + rank_r[r];
+      s_keys[pos] = key_r[r];
+      s_vals[pos] = val_r[r];
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < nvalid; i += kRadixThreads) {
+    const uint32_t key = s_keys[i];
+    const uint32_t gpos = s_gofs[(key >> shift) & kMask] + (uint32_t)i;
+    keys_out[gpos] = key;
+    vals_out[gpos] = s_vals[i];
+  }
+  __syncthreads();  // the next tile reuses the LDS
+}
+
+template <int NBITS>
+__global__ void __launch_bounds__(kRadixThreads)
+radix_scatter_kernel(const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
+                     uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out,
+                     const uint32_t* __restrict__ d_n, int64_t n_cap, int shift,
+                     const uint32_t* __restrict__ hist_scanned, uint32_t* __restrict__ digit_tot) {
   const int64_t n = sort_count(d_n, n_cap);
   const int64_t nb = (n + kRadixTile - 1) / kRadixTile;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x;
   // the offsets launch has read this pass's digit totals: leave them zero for the next sort
   for (int c = blockIdx.x; c < kTotCopies; c += gridDim.x) digit_tot[c * 256 + tid] = 0u;
   for (int64_t tile = blockIdx.x; tile < nb; tile += gridDim.x) {
-    const int64_t base = tile * kRadixTile;
-    const int nvalid = (int)((n - base) < kRadixTile ? (n - base) : kRadixTile);
     // where each digit of this tile starts in the output (loaded early, used at the end)
-    const uint32_t gstart = tid < kBins ? hist_scanned[(int64_t)tid * nb + tile] : 0u;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) s_cnt[w][lane + 64 * k] = 0;
-    __builtin_amdgcn_wave_barrier();
-    // Each wave ranks its own contiguous quarter of the tile in rounds of 64 elements; program
-    // order inside the wave keeps equal digits in index order.
-    uint32_t key_r[kRadixItems], val_r[kRadixItems], rank_r[kRadixItems];
-    // all loads first (memory-level parallelism)
-#pragma unroll
-    for (int r = 0; r < kRadixItems; ++r) {
-      const int i = w * kPerWave + r * 64 + lane;
-      const bool valid = i < nvalid;
-      key_r[r] = valid ? keys_in[base + i] : 0u;
-      val_r[r] = valid ? vals_in[base + i] : 0u;
-    }
-#pragma unroll
-    for (int r = 0; r < kRadixItems; ++r) {
-      const int i = w * kPerWave + r * 64 + lane;
-      const bool valid = i < nvalid;
-      const uint32_t d = (key_r[r] >> shift) & kMask;
-      // lanes holding the same digit: one ballot per digit bit
-      uint64_t m = ballot(valid);
-#pragma unroll
-      for (int bit = 0; bit < NBITS; ++bit) {
-        const bool set = (d >> bit) & 1u;
-        const uint64_t b = ballot(set);
-        m &= set ? b : ~b;
-      }
-      const uint32_t below = mbcnt(m);
-      const uint32_t cnt = s_cnt[w][d];
-      __builtin_amdgcn_wave_barrier();
-      if (valid && below == 0) s_cnt[w][d] = cnt + popc64(m);
-      __builtin_amdgcn_wave_barrier();
-      rank_r[r] = cnt + below;
-    }
-    __syncthreads();
-    // digit totals of the tile, offsets of each wave inside a digit, digit starts
-    uint32_t tot = 0;
-#pragma unroll
-    for (int ww = 0; ww < kWaves; ++ww) {
-      const uint32_t c = s_cnt[ww][tid];
-      s_cnt[ww][tid] = tot;
-      tot += c;
-    }
-    uint32_t total;
-    const uint32_t incl = block_inclusive_scan(tot, wave_tot, &total);
-    s_start[tid] = incl - tot;
-    // element counts fit in 32 bits, so output indices do too
-    if (tid < kBins) s_gofs[tid] = gstart - (incl - tot);
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < kRadixItems; ++r) {
-      const int i = w * kPerWave + r * 64 + lane;
-      if (i < nvalid) {
-        const uint32_t d = (key_r[r] >> shift) & kMask;
-        const uint32_t pos = s_start[d] + s_cnt[w][d] + rank_r[r];
-        s_keys[pos] = key_r[r];
-        s_vals[pos] = val_r[r];
-      }
-    }
-    __syncthreads();
-    for (int i = tid; i < nvalid; i += kRadixThreads) {
-      const uint32_t key = s_keys[i];
-      const uint32_t gpos = s_gofs[(key >> shift) & kMask] + (uint32_t)i;
-      keys_out[gpos] = key;
-      vals_out[gpos] = s_vals[i];
-    }
-    __syncthreads();  // the next tile reuses the LDS
+    const uint32_t gstart = tid < (1 << NBITS) ? hist_scanned[(int64_t)tid * nb + tile] : 0u;
+    scatter_tile<NBITS>(keys_in, vals_in, keys_out, vals_out, n, tile * kRadixTile, shift, gstart);
   }
 }
 
-__global__ void copy_pairs_kernel(const uint32_t* __restrict__ ka, const uint32_t* __restrict__ va,
-                                  uint32_t* __restrict__ kb, uint32_t* __restrict__ vb,
-                                  const uint32_t* __restrict__ d_n, int64_t n_cap) {
-  const int64_t n = sort_count(d_n, n_cap);
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    kb[i] = ka[i];
-    vb[i] = va[i];
+// One pass of a short sort (at most kDirectTiles radix tiles) in one launch: instead of a histogram
+// launch and an offsets launch, every workgroup counts the digits of all elements itself, those of
+// the tiles before its own apart from the rest. With `ranges` (a sort of one pass: a digit is a
+// tile of the image) the first workgroup also writes each digit's run as [first, end). Bound by
+// launches, which each cost 4 to 5 us whatever they do: 5000 pairs in 64 tiles of an image, sort
+// and ranges 28 -> 9 us.
+template <int NBITS>
+__global__ void __launch_bounds__(kRadixThreads)
+radix_direct_kernel(const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
+                    uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out,
+                    const uint32_t* __restrict__ d_n, int64_t n_cap, int shift,
+                    uint32_t* __restrict__ ranges) {
+  constexpr int kBins = 1 << NBITS;
+  constexpr uint32_t kMask = (uint32_t)kBins - 1u;
+  __shared__ uint32_t s_before[256], s_after[256];
+  __shared__ uint32_t wave_tot[4];
+  const int n = (int)sort_count(d_n, n_cap);
+  const int tid = threadIdx.x;
+  const int base = (int)blockIdx.x * kRadixTile;
+  if (base >= n) return;
+  s_before[tid] = 0u;
+  s_after[tid] = 0u;
+  __syncthreads();
+#pragma unroll 4
+  for (int i = tid; i < n; i += kRadixThreads)
+    atomicAdd(&(i < base ? s_before : s_after)[(keys_in[i] >> shift) & kMask], 1u);
+  __syncthreads();
+  const uint32_t before = s_before[tid], all = before + s_after[tid];
+  uint32_t total;
+  const uint32_t first = block_inclusive_scan(all, wave_tot, &total) - all;
+  if (ranges && blockIdx.x == 0 && all != 0u) {
+    ranges[2 * tid] = first;
+    ranges[2 * tid + 1] = first + all;
   }
+  scatter_tile<NBITS>(keys_in, vals_in, keys_out, vals_out, n, base, shift, first + before);
+}
+
+// Depth order of few records in one launch: the rank of a record is the number of records with a
+// smaller key, or an equal one and a smaller index. A workgroup ranks 64 records, one per lane;
+// its 16 waves count over every 16th chunk of 64 keys each, read through the scalar cache (two
+// vector instructions per key and wave). The work grows with n^2, the launches of a radix sort
+// (12, 70 us) do not shrink with n.
+constexpr int kRankThreads = 1024;
+
+__global__ void __launch_bounds__(kRankThreads)
+rank_order_kernel(const uint32_t* __restrict__ keys, int n, uint32_t* __restrict__ order) {
+  __shared__ uint32_t s_rank[64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int own = (int)blockIdx.x, i = own * 64 + lane;
+  const uint32_t key = i < n ? keys[i] : 0xffffffffu;
+  if (tid < 64) s_rank[tid] = 0u;
+  __syncthreads();
+  uint32_t below = 0;
+  const int chunks = (n + 63) / 64;
+  for (int c = w; c < chunks; c += kRankThreads / 64) {
+    const uint32_t* __restrict__ k = keys + c * 64;
+    const int m = n - c * 64 < 64 ? n - c * 64 : 64;
+    if (c == own) {
+      for (int j = 0; j < m; ++j) below += (k[j] < key || (k[j] == key && j < lane)) ? 1u : 0u;
+    } else if (c < own) {
+#pragma unroll
+      for (int j = 0; j < 64; ++j) below += k[j] <= key ? 1u : 0u;
+    } else if (m == 64) {
+#pragma unroll
+      for (int j = 0; j < 64; ++j) below += k[j] < key ? 1u : 0u;
+    } else {
+      for (int j = 0; j < m; ++j) below += k[j] < key ? 1u : 0u;
+    }
+  }
+  atomicAdd(&s_rank[lane], below);
+  __syncthreads();
+  if (tid < 64 && i < n) order[s_rank[tid]] = (uint32_t)i;
 }
 
 __global__ void fill_u32_kernel(uint32_t* __restrict__ p, uint32_t value, int64_t n) {
@@ -491,10 +566,19 @@ hipError_t launch_scan_u32(const uint32_t* in, const uint32_t* gather, uint32_t*
   return hipGetLastError();
 }
 
+// Radix tiles of a sort whose passes are one launch each: a workgroup reads every key, which costs
+// about 1 us per tile and pass, against 4 to 5 for each of the two launches saved.
+constexpr int64_t kDirectTiles = 4;
+
 template <int NBITS>
 hipError_t radix_pass(const uint32_t* ki, const uint32_t* vi, uint32_t* ko, uint32_t* vo,
                       const uint32_t* d_n, int64_t n_cap, int shift, int64_t nb, uint32_t* hist,
-                      uint32_t* digit_tot, hipStream_t s) {
+                      uint32_t* digit_tot, uint32_t* ranges, hipStream_t s) {
+  if (nb <= kDirectTiles) {
+    hipLaunchKernelGGL(radix_direct_kernel<NBITS>, dim3((unsigned)nb), dim3(kRadixThreads), 0, s,
+                       ki, vi, ko, vo, d_n, n_cap, shift, ranges);
+    return hipGetLastError();
+  }
   const unsigned grid = (unsigned)(nb < kRadixGrid ? nb : kRadixGrid);
   hipLaunchKernelGGL(radix_hist_kernel<NBITS>, dim3(grid), dim3(kRadixThreads), 0, s, ki, d_n,
                      n_cap, shift, hist, digit_tot);
@@ -505,30 +589,45 @@ hipError_t radix_pass(const uint32_t* ki, const uint32_t* vi, uint32_t* ko, uint
   return hipGetLastError();
 }
 
+// The fewest 8-bit-or-narrower passes (the key bits are spread evenly over them).
+int radix_passes(int bits) { return (bits + 7) / 8; }
+
 hipError_t launch_radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt,
                              uint32_t* vals_alt, const uint32_t* d_n, int64_t n_cap, int bits,
-                             uint32_t* hist, uint32_t* digit_tot, hipStream_t s) {
+                             uint32_t* hist, uint32_t* digit_tot, uint32_t* ranges,
+                             bool* ranges_written, hipStream_t s) {
   const int64_t nb = (n_cap + kRadixTile - 1) / kRadixTile;
+  if (ranges_written) *ranges_written = false;
   if (nb == 0 || bits <= 0) return hipSuccess;
   if (bits > 32) return hipErrorInvalidValue;
-  // the fewest 8-bit-or-narrower passes, with the key bits spread evenly over them
-  const int passes = (bits + 7) / 8;
+  const int passes = radix_passes(bits);
+  if (passes != 1 || nb > kDirectTiles) ranges = nullptr;
+  if (ranges_written) *ranges_written = ranges != nullptr;
   hipError_t e = hipSuccess;
   uint32_t *ki = keys, *vi = vals, *ko = keys_alt, *vo = vals_alt;
+  if (passes & 1) {  // the input is in the alternate arrays
+    ki = keys_alt;
+    vi = vals_alt;
+    ko = keys;
+    vo = vals;
+  }
   int shift = 0;
   for (int p = 0; p < passes; ++p) {
     const int nbits = bits / passes + (p < bits % passes ? 1 : 0);
     uint32_t* const tot = digit_tot + (int64_t)kTotCopies * 256 * p;
+#define GBB_PASS(B) \
+  e = radix_pass<B>(ki, vi, ko, vo, d_n, n_cap, shift, nb, hist, tot, ranges, s)
     switch (nbits) {
-      case 1: e = radix_pass<1>(ki, vi, ko, vo, d_n, n_cap, shift, nb, hist, tot, s); break;
-      case 2: e = radix_pass<2>(ki, vi, ko, vo, d_n, n_cap, shift, nb, hist, tot, s); break;
-      case 3: e = radix_pass<3>(ki, vi, ko, vo, d_n, n_cap, shift, nb, hist, tot, s); break;
-      case 4: e = radix_pass<4>(ki, vi, ko, vo, d_n, n_cap, shift, nb, hist, tot, s); break;
-      case 5: e = radix_pass<5>(ki, vi, ko, vo, d_n, n_cap, shift, nb, hist, tot, s); break;
-      case 6: e = radix_pass<6>(ki, vi, ko, vo, d_n, n_cap, shift, nb, hist, tot, s); break;
-      case 7: e = radix_pass<7>(ki, vi, ko, vo, d_n, n_cap, shift, nb, hist, tot, s); break;
-      default: e = radix_pass<8>(ki, vi, ko, vo, d_n, n_cap, shift, nb, hist, tot, s); break;
+      case 1: GBB_PASS(1); break;
+      case 2: GBB_PASS(2); break;
+      case 3: GBB_PASS(3); break;
+      case 4: GBB_PASS(4); break;
+      case 5: GBB_PASS(5); break;
+      case 6: GBB_PASS(6); break;
+      case 7: GBB_PASS(7); break;
+      default: GBB_PASS(8); break;
     }
+#undef GBB_PASS
     if (e != hipSuccess) return e;
     shift += nbits;
     uint32_t* t = ki;
@@ -538,10 +637,14 @@ hipError_t launch_radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt,
     vi = vo;
     vo = t;
   }
-  if (ki != keys) {
-    hipLaunchKernelGGL(copy_pairs_kernel, dim3(grid_for(n_cap, 256)), dim3(256), 0, s, ki, vi,
-                       keys, vals, d_n, n_cap);
-  }
+  return hipGetLastError();
+}
+
+hipError_t launch_rank_order(const uint32_t* keys, int64_t n, uint32_t* order, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  if (n > kRankMax) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(rank_order_kernel, dim3((unsigned)((n + 63) / 64)), dim3(kRankThreads), 0, s,
+                     keys, (int)n, order);
   return hipGetLastError();
 }
 

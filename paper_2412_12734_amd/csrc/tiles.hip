@@ -59,6 +59,31 @@ __device__ int64_t wave_slot_owner(const uint32_t* __restrict__ offsets, int64_t
   return lo;
 }
 
+// What a forward's pair count leaves in the status (one thread): n pairs of the first pass, ending
+// at depth rank `cut`, the last of them owned by rank `last`. The rest pass starts out empty.
+__device__ __forceinline__ void store_status(Status* st, unsigned long long K, bool over,
+                                             uint32_t n, uint32_t cut, uint32_t last,
+                                             const StatusEcho& echo, unsigned long long* mirror,
+                                             uint32_t* overflow_flag) {
+  st->overflow = over ? 1u : 0u;
+  st->sticky_overflow |= over ? 1u : 0u;
+  st->n_views = echo.n_views;
+  st->P = echo.P;
+  st->off_count = echo.off_count;
+  st->off_view_pairs = echo.off_view_pairs;
+  // one aligned 8-byte store, so that the host never reads a torn value
+  if (mirror) *reinterpret_cast<volatile unsigned long long*>(mirror) = (over ? 1ull << 63 : 0ull) | K;
+  if (overflow_flag && over) *overflow_flag = 1u;
+  st->any_open = 0u;
+  st->cut = cut;
+  st->n_sorted = n;
+  st->last_first = last;
+  st->n_rest = 0u;
+  st->K_rest = 0u;
+  st->K_rest64 = 0u;
+  st->last_rest = 0u;
+}
+
 // One wave.
 __global__ void finalize_count_kernel(const uint32_t* __restrict__ offsets, int64_t VP,
                                       Status* st, int64_t capacity, StatusEcho echo,
@@ -81,20 +106,118 @@ __global__ void finalize_count_kernel(const uint32_t* __restrict__ offsets, int6
   }
   const uint32_t last = n > 0 ? (uint32_t)wave_slot_owner(offsets, VP, chunk_owner, K, n - 1)
                               : 0u;
-  if (threadIdx.x == 0) {
-    st->overflow = over ? 1u : 0u;
-    st->sticky_overflow |= over ? 1u : 0u;
-    st->n_views = echo.n_views;
-    st->P = echo.P;
-    st->off_count = echo.off_count;
-    st->off_view_pairs = echo.off_view_pairs;
-    // one aligned 8-byte store, so that the host never reads a torn value
-    if (mirror) *reinterpret_cast<volatile unsigned long long*>(mirror) = (over ? 1ull << 63 : 0ull) | K;
-    if (overflow_flag && over) *overflow_flag = 1u;
-    st->any_open = 0u;
-    st->cut = cut;
-    st->n_sorted = n;
-    st->last_first = last;
+  if (threadIdx.x == 0)
+    store_status(st, K, over, n, cut, last, echo, mirror, overflow_flag);
+}
+
+// Scan and finalisation for at most kSmallScan records, one workgroup: thread t holds the counts of
+// ranks t, t + 1024, ... in registers (all loads in flight at once), each wave scans its 64, and one
+// wave scans the waves' totals.
+constexpr int kScanThreads = 1024;
+constexpr int kScanRounds = (int)(kSmallScan / kScanThreads);
+static_assert(kScanRounds * (kScanThreads / 64) <= 256, "four wave totals per lane");
+
+__global__ void __launch_bounds__(kScanThreads)
+scan_finalize_kernel(const uint32_t* __restrict__ count, const uint32_t* __restrict__ order,
+                     int VP, uint32_t* __restrict__ offsets, uint32_t* __restrict__ chunk_owner,
+                     int64_t n_chunks, Status* st, int64_t capacity, StatusEcho echo,
+                     unsigned long long* mirror, uint32_t* overflow_flag, int64_t budget) {
+  constexpr int kWaves = kScanThreads / 64;
+  __shared__ uint32_t s_tot[256];  // [round][wave]
+  __shared__ unsigned long long s_tot64[kWaves];
+  __shared__ uint32_t s_cut, s_n, s_last;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  uint32_t x[kScanRounds], incl[kScanRounds];
+#pragma unroll
+  for (int k = 0; k < kScanRounds; ++k) {
+    const int r = k * kScanThreads + tid;
+    x[k] = r < VP ? order[r] : 0u;
+  }
+#pragma unroll
+  for (int k = 0; k < kScanRounds; ++k)
+    x[k] = k * kScanThreads + tid < VP ? count[x[k]] : 0u;
+  unsigned long long sum = 0;
+#pragma unroll
+  for (int k = 0; k < kScanRounds; ++k) {
+    sum += x[k];
+    uint32_t v = x[k];
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t t = __shfl_up(v, d, 64);
+      if (lane >= d) v += t;
+    }
+    incl[k] = v;
+    if (lane == 63) s_tot[k * kWaves + w] = v;
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
+  if (lane == 0) s_tot64[w] = sum;
+  if (tid == 0) {
+    s_cut = (uint32_t)VP;
+    s_last = 0u;
+  }
+  __syncthreads();
+  unsigned long long K = 0;
+  for (int i = 0; i < kWaves; ++i) K += s_tot64[i];
+  if (w == 0) {  // exclusive scan of the (round, wave) totals, four per lane
+    uint32_t v[4], s = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int at = 4 * lane + i;
+      v[i] = at < kScanRounds * kWaves ? s_tot[at] : 0u;
+      s += v[i];
+    }
+    uint32_t run = s;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t t = __shfl_up(run, d, 64);
+      if (lane >= d) run += t;
+    }
+    run -= s;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s_tot[4 * lane + i] = run;
+      run += v[i];
+    }
+  }
+  // the 64-bit total decides, as in finalize_count_kernel
+  const bool over = K > (unsigned long long)capacity;
+  const bool split = budget > 0 && !over && K > (unsigned long long)budget;
+  if (tid == 0) s_n = over ? 0u : (uint32_t)K;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kScanRounds; ++k) {
+    const int r = k * kScanThreads + tid;
+    if (k * kScanThreads >= VP) break;
+    const uint32_t o = s_tot[k * kWaves + w] + incl[k] - x[k];
+    incl[k] = o;  // from here: the exclusive prefix
+    if (r < VP) offsets[r] = o;
+    if (x[k] > 0) {
+      const uint64_t e = (uint64_t)o + x[k];
+      for (uint64_t c = ((uint64_t)o + kChunkSlots - 1) / kChunkSlots;
+           c * kChunkSlots < e && (int64_t)c < n_chunks; ++c)
+        chunk_owner[c] = (uint32_t)r;
+      // the record that owns the first slot past the budget ends the prefix
+      if (split && (uint64_t)o <= (uint64_t)budget && (uint64_t)budget < e) {
+        s_cut = (uint32_t)r;
+        s_n = o;
+      }
+    }
+  }
+  __syncthreads();
+  const uint32_t n = s_n;
+#pragma unroll
+  for (int k = 0; k < kScanRounds; ++k) {
+    if (k * kScanThreads >= VP) break;
+    if (n > 0 && x[k] > 0 && incl[k] <= n - 1 && (uint64_t)n - 1 < (uint64_t)incl[k] + x[k])
+      s_last = (uint32_t)(k * kScanThreads + tid);
+  }
+  __syncthreads();
+  if (tid == 0) {
+    st->K = (uint32_t)K;
+    st->K64 = K;
+    store_status(st, K, over, n, over && budget > 0 ? 0u : s_cut, s_last, echo, mirror,
+                 overflow_flag);
   }
 }
 
@@ -552,6 +675,18 @@ hipError_t launch_order_tiles(const uint32_t* work, int64_t n_tiles, uint32_t* o
   if (n_tiles < 1 || n_tiles > kMaxOrderedTiles || !work || !order) return hipErrorInvalidValue;
   hipLaunchKernelGGL(order_tiles_kernel, dim3(1), dim3(kOrderThreads), 0, s, work, (int)n_tiles,
                      order);
+  return hipGetLastError();
+}
+
+hipError_t launch_scan_finalize(const uint32_t* count, const uint32_t* order, int64_t VP,
+                                uint32_t* offsets, uint32_t* chunk_owner, int64_t n_chunks,
+                                Status* st, int64_t capacity, StatusEcho echo,
+                                unsigned long long* mirror, uint32_t* overflow_flag,
+                                int64_t budget, hipStream_t s) {
+  if (VP > kSmallScan) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(scan_finalize_kernel, dim3(1), dim3(kScanThreads), 0, s, count, order,
+                     (int)VP, offsets, chunk_owner, n_chunks, st, capacity, echo, mirror,
+                     overflow_flag, budget);
   return hipGetLastError();
 }
 
