@@ -236,7 +236,7 @@ constexpr int kLaneAddMax = 20;
 //  4 x 4 grids, 16 / 24 / 32 splats: 16 uneven views of 1M splats 6.22 / 6.25 / 7.54 ms, 47k splats
 //  on three uneven views 0.558 / 0.529 / -, 372k splats on 462 tiles 1.27 / - / 1.11.
 //  16 x 16 grids, 1 / 2 / 3 splats: 2.81 / 2.10 / 2.16 ms at 1M splats and 1080p, two in passes of
-//  32 entries (six workgroups per CU instead of five) 1.66. With sides {4, 8, 16} a grid is mostly
+//  48 entries (six workgroups per CU instead of five) 1.63. With sides {4, 8, 16} a grid is mostly
 //  smaller than its slot: 2 / 3 / 4 splats 3.88 / 3.11 / 2.59 ms at 202k splats on three views.
 template <int N, bool MIXED>
 constexpr int bwd_batch(int asked, bool few_tiles) {
@@ -249,7 +249,7 @@ constexpr int bwd_batch(int asked, bool few_tiles) {
 }
 template <int N, int B>
 constexpr int bwd_pass_entries() {
-  return (N == 8 && B == 7) || (N >= 16 && B == 2) ? 32 : kPassEntries;
+  return N == 8 && B == 7 ? 32 : N >= 16 && B == 2 ? 48 : kPassEntries;
 }
 
 // Occupancy target: what the LDS allows (see above), at most 7 waves per SIMD (72 VGPRs): 8 (64
@@ -565,7 +565,9 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
         // next batch.
         constexpr int FL = flush_lanes<N, MIXED>(), PER = 64 / FL;
         const int ft = fresh_tid() & 63, fl = ft & (FL - 1);
-        for (int j = w * PER + (PER > 1 ? ft / FL : 0); j < nb; j += n_waves * PER) {
+        // (two waves share a slot of 768 sums where the batch has no slot for half of the waves)
+        const int parts = N >= 16 && !MIXED && 2 * nb <= n_waves ? 2 : 1, part = w & (parts - 1);
+        for (int j = w / parts * PER + (PER > 1 ? ft / FL : 0); j < nb; j += n_waves / parts * PER) {
           int entry = (int)s_list.entry[b0 + j];
           uint32_t r = s_list.rec[b0 + j];
           if constexpr (PER == 1) {
@@ -574,13 +576,13 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
           }
           double* const gs = s_gtex + j * TEXG;
           // each lane reads the sums its record gradient needs, and only then are they cleared
-          const float rg = record_gradient(fl, &s_sum[j * kSums], s_geo.g1[entry],
+          const float rg = part != 0 ? 0.f : record_gradient(fl, &s_sum[j * kSums], s_geo.g1[entry],
                                            s_geo.g2[entry], p.lp_scale);
           if (p.d_spec) {
             // the view-dependent colour of a record is added to every texel of its lookup, so
             // its adjoint over the tile is the sum of the record's texel sums, one per channel
             float sc[3] = {0.f, 0.f, 0.f};
-            for (int t = fl; t < N * N; t += FL) {
+            for (int t = fl + part * FL; t < N * N; t += parts * FL) {
               sc[0] += (float)gs[3 * t];
               sc[1] += (float)gs[3 * t + 1];
               sc[2] += (float)gs[3 * t + 2];
@@ -621,7 +623,7 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
             float* const dst = d_tex + (int64_t)(r - rec_base) * TEXG;
             // (three reads at a time)
             constexpr int K = (TEXG + FL - 1) / FL, KU = K < 3 ? K : 3;
-            for (int k0 = 0; k0 < K; k0 += KU) {
+            for (int k0 = part * KU; k0 < K; k0 += parts * KU) {
               double x[KU];
 #pragma unroll
               for (int k = 0; k < KU; ++k) {
@@ -640,7 +642,7 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
           }
           __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
           __builtin_amdgcn_wave_barrier();
-          if (fl < kSums) s_sum[j * kSums + fl] = 0.0;
+          if (part == 0 && fl < kSums) s_sum[j * kSums + fl] = 0.0;
           if (fl < kRecGrad && rg != 0.f) atomicAdd(&d_rec[(int64_t)r * kRecGrad + fl], rg);
         }
         // the next batch's texels load while the atomics above drain
