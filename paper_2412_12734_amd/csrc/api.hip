@@ -504,18 +504,23 @@ gb_status densify_apply_launch(const gb_raw_splats* src, const void* work, const
                                 (float)std::log((double)o->split_shrink), dst->means,
                                 dst->log_scales, hs),
           "densify geometry");
-  GBB_TRY(launch_gather_rows(map, d_n, n, 4, src->quats, dst->quats, false, hs), "quats");
-  GBB_TRY(launch_gather_rows(map, d_n, n, 1, src->opacity_logits, dst->opacity_logits, false, hs),
-          "logits");
-  if (src->sh_coef > 0)
-    GBB_TRY(launch_gather_rows(map, d_n, n, 3 * src->sh_coef, src->sh, dst->sh, false, hs), "sh");
-  GBB_TRY(launch_child_texture(map, d_n, n, N, src->textures, noise, sigma,
-                               (float)(1.0 / (double)o->split_shrink), dst->textures, hs),
-          "densify textures");
-  for (int i = 0; i < n_states; ++i)
-    GBB_TRY(launch_gather_rows(map, d_n, n, states[i].width, states[i].src, states[i].dst, true,
-                               hs),
-            "state rows");
+  // the arrays that are gathered row by row, as many per launch as its argument holds
+  const int n_own = src->sh_coef > 0 ? 4 : 3;
+  const RowArray own[4] = {{src->textures, dst->textures, 3 * N * N, kRowGrid},
+                           {src->quats, dst->quats, 4, kRowCopy},
+                           {src->opacity_logits, dst->opacity_logits, 1, kRowCopy},
+                           {src->sh, dst->sh, 3 * src->sh_coef, kRowCopy}};
+  for (int64_t first = 0; first < (int64_t)n_own + n_states; first += kMaxRowArrays) {
+    RowList list;
+    int k = 0;
+    for (int64_t i = first; i < (int64_t)n_own + n_states && k < kMaxRowArrays; ++i, ++k)
+      list.a[k] = i < n_own ? own[i]
+                            : RowArray{states[i - n_own].src, states[i - n_own].dst,
+                                       states[i - n_own].width, kRowState};
+    GBB_TRY(launch_gather_rows(map, d_n, n, list, k, N, noise, sigma,
+                               (float)(1.0 / (double)o->split_shrink), hs),
+            "densify rows");
+  }
   return GB_OK;
 }
 

@@ -304,14 +304,24 @@ hipError_t launch_densify_decide(int64_t P, const float* log_scales, const float
                                  uint32_t* n_out, hipStream_t s);
 hipError_t launch_densify_map(int64_t P, const uint32_t* action, const uint32_t* n_out,
                               const uint32_t* offsets, uint32_t* map, hipStream_t s);
-hipError_t launch_gather_rows(const uint32_t* map, const uint32_t* d_n, int64_t n_new, int width,
-                              const float* src, float* dst, bool zero_new, hipStream_t s);
+// An array of rows of `width` floats that densification gathers from the parents: every output a
+// copy of its parent's row, new rows zero (optimiser state), or split children resampled (grids).
+enum RowKind : int32_t { kRowCopy = 0, kRowState = 1, kRowGrid = 2 };
+struct RowArray {
+  const float* src;
+  float* dst;
+  int32_t width, kind;
+};
+constexpr int kMaxRowArrays = 16;  // per launch (they travel as a kernel argument)
+struct RowList {
+  RowArray a[kMaxRowArrays];
+};
+hipError_t launch_gather_rows(const uint32_t* map, const uint32_t* d_n, int64_t n_new,
+                              const RowList& list, int n_arrays, int N, const float* noise,
+                              float sigma, float inv_shrink, hipStream_t s);
 hipError_t launch_child_geometry(const uint32_t* map, const uint32_t* d_n, int64_t n_new,
                                  const float* means, const float* quats, const float* log_scales,
                                  const float* noise, float log_shrink, float* means_out,
                                  float* log_scales_out, hipStream_t s);
-hipError_t launch_child_texture(const uint32_t* map, const uint32_t* d_n, int64_t n_new, int N,
-                                const float* tex, const float* noise, float sigma,
-                                float inv_shrink, float* tex_out, hipStream_t s);
 
 }  // namespace gbb
