@@ -83,22 +83,24 @@ __global__ void __launch_bounds__(256)
 preprocess_kernel(const float* __restrict__ means, const float* __restrict__ tan_u,
                   const float* __restrict__ tan_v, const float* __restrict__ scales,
                   const float* __restrict__ opacity, const ViewDev* __restrict__ views,
-                  int64_t P, int64_t VP, float alpha_min, float r_lp, int tile_w, int tile_h,
+                  int64_t P, float alpha_min, float r_lp, int tile_w, int tile_h,
                   uint32_t* __restrict__ depth_key, uint32_t* __restrict__ sort_key,
                   uint32_t* __restrict__ count,
                   SplatRec* __restrict__ rec, const float* __restrict__ sh,
                   float4* __restrict__ spec, uint32_t* __restrict__ order,
                   uint32_t* __restrict__ zero, int64_t n_zero) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (order) {
-    // the depth sort's initial order (record indices), and words to clear, in the same launch
-    if (idx < VP) order[idx] = (uint32_t)idx;
-    const int64_t n_threads = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = idx; i < n_zero; i += n_threads) zero[i] = 0u;
+  // a workgroup takes splats of one view: the view is uniform (a 64-bit division per record and
+  // per-lane view reads otherwise)
+  const uint32_t per_view = (uint32_t)((P + 255) / 256), v = blockIdx.x / per_view;
+  const int64_t k = (int64_t)(blockIdx.x - v * per_view) * 256 + threadIdx.x;
+  const int64_t idx = (int64_t)v * P + k;
+  if (zero) {  // words to clear in the same launch
+    const int64_t n_threads = (int64_t)gridDim.x * 256;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_zero; i += n_threads)
+      zero[i] = 0u;
   }
-  if (idx >= VP) return;
-  const int v = (int)(idx / P);
-  const int64_t k = idx - (int64_t)v * P;
+  if (k >= P) return;
+  if (order) order[idx] = (uint32_t)idx;  // the depth sort's initial order (record indices)
   const ViewDev& V = views[v];
   float R[9];
 #pragma unroll
@@ -182,58 +184,54 @@ preprocess_kernel(const float* __restrict__ means, const float* __restrict__ tan
   sort_key[idx] = key;
   count[idx] = n_tiles;
 
-  // ---- blend record (only meaningful for visible records) --------------------------------
+  // ---- blend record: visible records only (nothing reads a record without tiles; writing the 96
+  // bytes of all of them took most of the launch where a view sees a part of the scene) ---------
+  if (n_tiles == 0) return;
   SplatRec r;
-  if (n_tiles > 0) {
-    // The record is computed in float-pair arithmetic from the float32 inputs: the projected
-    // centre must be exact to far below a pixel, and the homography entries of nearly edge-on
-    // splats come out of cancelling differences.
-    f2 pc2[3], a2[3], b2[3];
-    const f2 wa[3] = {two_prod(su, u0), two_prod(su, u1), two_prod(su, u2)};
-    const f2 wb[3] = {two_prod(sv, w0), two_prod(sv, w1), two_prod(sv, w2)};
-    for (int i = 0; i < 3; ++i) {
-      pc2[i] = rot_row_f2(R, i, p0, p1, p2, V.t[i]);
-      a2[i] = f2_add(f2_add(f2_mul(wa[0], R[3 * i + 0]), f2_mul(wa[1], R[3 * i + 1])),
-                     f2_mul(wa[2], R[3 * i + 2]));
-      b2[i] = f2_add(f2_add(f2_mul(wb[0], R[3 * i + 0]), f2_mul(wb[1], R[3 * i + 1])),
-                     f2_mul(wb[2], R[3 * i + 2]));
-    }
-    const f2 iz = f2_div(f2_of(1.0f), pc2[2]);
-    const f2 xi = f2_mul(pc2[0], iz), eta = f2_mul(pc2[1], iz);
-    const f2 c2x = f2_add(f2_mul(xi, V.fx), V.cx);
-    const f2 c2y = f2_add(f2_mul(eta, V.fy), V.cy);
-    const f2 m0 = f2_mul(a2[2], iz), m1 = f2_mul(b2[2], iz);
-    const f2 X0 = f2_mul(f2_mul(f2_sub(a2[0], f2_mul(xi, a2[2])), iz), V.fx);
-    const f2 X1 = f2_mul(f2_mul(f2_sub(b2[0], f2_mul(xi, b2[2])), iz), V.fx);
-    const f2 Y0 = f2_mul(f2_mul(f2_sub(a2[1], f2_mul(eta, a2[2])), iz), V.fy);
-    const f2 Y1 = f2_mul(f2_mul(f2_sub(b2[1], f2_mul(eta, b2[2])), iz), V.fy);
-    const f2 h[7] = {Y1, f2_neg(X1), f2_neg(Y0), X0,
-                     f2_sub(f2_mul(m1, Y0), f2_mul(m0, Y1)),
-                     f2_sub(f2_mul(X1, m0), f2_mul(X0, m1)),
-                     f2_sub(f2_mul(X0, Y1), f2_mul(X1, Y0))};
-    for (int i = 0; i < 7; ++i) {
-      r.h_hi[i] = h[i].hi;
-      r.h_lo[i] = h[i].lo;
-    }
-    r.c2x_hi = c2x.hi;
-    r.c2x_lo = c2x.lo;
-    r.c2y_hi = c2y.hi;
-    r.c2y_lo = c2y.lo;
-  } else {
-    for (int i = 0; i < 7; ++i) r.h_hi[i] = r.h_lo[i] = 0.f;
-    r.c2x_hi = r.c2x_lo = r.c2y_hi = r.c2y_lo = 0.f;
+  // The record is computed in float-pair arithmetic from the float32 inputs: the projected
+  // centre must be exact to far below a pixel, and the homography entries of nearly edge-on
+  // splats come out of cancelling differences.
+  f2 pc2[3], a2[3], b2[3];
+  const f2 wa[3] = {two_prod(su, u0), two_prod(su, u1), two_prod(su, u2)};
+  const f2 wb[3] = {two_prod(sv, w0), two_prod(sv, w1), two_prod(sv, w2)};
+  for (int i = 0; i < 3; ++i) {
+    pc2[i] = rot_row_f2(R, i, p0, p1, p2, V.t[i]);
+    a2[i] = f2_add(f2_add(f2_mul(wa[0], R[3 * i + 0]), f2_mul(wa[1], R[3 * i + 1])),
+                   f2_mul(wa[2], R[3 * i + 2]));
+    b2[i] = f2_add(f2_add(f2_mul(wb[0], R[3 * i + 0]), f2_mul(wb[1], R[3 * i + 1])),
+                   f2_mul(wb[2], R[3 * i + 2]));
   }
+  const f2 iz = f2_div(f2_of(1.0f), pc2[2]);
+  const f2 xi = f2_mul(pc2[0], iz), eta = f2_mul(pc2[1], iz);
+  const f2 c2x = f2_add(f2_mul(xi, V.fx), V.cx);
+  const f2 c2y = f2_add(f2_mul(eta, V.fy), V.cy);
+  const f2 m0 = f2_mul(a2[2], iz), m1 = f2_mul(b2[2], iz);
+  const f2 X0 = f2_mul(f2_mul(f2_sub(a2[0], f2_mul(xi, a2[2])), iz), V.fx);
+  const f2 X1 = f2_mul(f2_mul(f2_sub(b2[0], f2_mul(xi, b2[2])), iz), V.fx);
+  const f2 Y0 = f2_mul(f2_mul(f2_sub(a2[1], f2_mul(eta, a2[2])), iz), V.fy);
+  const f2 Y1 = f2_mul(f2_mul(f2_sub(b2[1], f2_mul(eta, b2[2])), iz), V.fy);
+  const f2 h[7] = {Y1, f2_neg(X1), f2_neg(Y0), X0,
+                   f2_sub(f2_mul(m1, Y0), f2_mul(m0, Y1)),
+                   f2_sub(f2_mul(X1, m0), f2_mul(X0, m1)),
+                   f2_sub(f2_mul(X0, Y1), f2_mul(X1, Y0))};
+  for (int i = 0; i < 7; ++i) {
+    r.h_hi[i] = h[i].hi;
+    r.h_lo[i] = h[i].lo;
+  }
+  r.c2x_hi = c2x.hi;
+  r.c2x_lo = c2x.lo;
+  r.c2y_hi = c2y.hi;
+  r.c2y_lo = c2y.lo;
   r.opacity = o;
   r.rect_x = (i0 & 0xffff) | (i1 << 16);
   r.rect_y = (j0 & 0xffff) | (j1 << 16);
   r.splat = (int32_t)k;
-  r.view = v;
+  r.view = (int32_t)v;
   r.pad = 0;
   rec[idx] = r;
 
   // ---- view-dependent colour (diffuse-specular split): sum_j Y_j(dir) sh[k][j] ---------
   if constexpr (SHD >= 0) {
-    if (n_tiles == 0) return;
     // camera centre -R^T t; dir = (p - centre) / |p - centre|
     float d[3];
     for (int i = 0; i < 3; ++i)
@@ -290,15 +288,15 @@ hipError_t launch_preprocess(const gb_splats& sp, const ViewDev* d_views, int n_
                              const gb_options& o, int tile_w, int tile_h, uint32_t* depth_key,
                              uint32_t* sort_key, uint32_t* count, SplatRec* rec, float4* spec,
                              uint32_t* order, uint32_t* zero, int64_t n_zero, hipStream_t s) {
-  const int64_t VP = (int64_t)sp.P * n_views;
   const int threads = 256;
-  const int64_t blocks = (VP + threads - 1) / threads;
+  const int64_t blocks = ((int64_t)sp.P + threads - 1) / threads * n_views;
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
   const float r_lp = lowpass_radius(o.lowpass_var);
   const int shd = sp.sh ? sp.sh_degree : -1;
 #define GBB_PRE(D)                                                                            \
   hipLaunchKernelGGL(preprocess_kernel<D>, dim3((unsigned)blocks), dim3(threads), 0, s,        \
                      sp.means, sp.tan_u, sp.tan_v, sp.scales, sp.opacity, d_views,            \
-                     (int64_t)sp.P, VP, o.alpha_min, r_lp, tile_w, tile_h, depth_key, sort_key, \
+                     (int64_t)sp.P, o.alpha_min, r_lp, tile_w, tile_h, depth_key, sort_key, \
                      count, rec, sp.sh, spec, order, zero, n_zero)
   switch (shd) {
     case 0: GBB_PRE(0); break;

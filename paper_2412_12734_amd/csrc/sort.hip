@@ -7,8 +7,10 @@
 // digit-major [digit][tile] counts into output offsets (the totals of the smaller digits
 // give the row's base) -> scatter. The totals are kept in kTotCopies copies (workgroup b adds
 // to copy b mod kTotCopies): device-wide atomics on one address are served one at a time,
-// about 55 ns each, so 2048 workgroups adding to a single copy took 35 us. The scatter ranks each element stably among equal digits
-// of its tile: each wave takes a contiguous quarter of the tile in rounds of 64; lanes with
+// about 55 ns each, so 2048 workgroups adding to a single copy took 35 us. With few tiles the
+// scatter works out its offsets itself (two launches; 100k records, four passes 76 -> 58 us), with
+// very few its counts too (one launch). The scatter ranks each element stably among equal digits
+// of its tile: each wave takes a contiguous part of the tile in rounds of 64; lanes with
 // the same digit are found with one ballot per digit bit and counted against the wave's
 // running per-digit counters in LDS. Wave offsets and digit starts then place every element
 // in LDS in digit order, and the tile is written out so that consecutive lanes store
@@ -23,8 +25,9 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kItems = kScanTile / kThreads;  // 16
 
-// Inclusive scan of v over the 256 threads of the block; returns the inclusive value and
-// writes the block total to *total. `wave_tot` is LDS scratch of 4 entries.
+// Inclusive scan of v over the threads of the block; returns the inclusive value and
+// writes the block total to *total. `wave_tot` is LDS scratch of one entry per wave.
+template <int THREADS = kThreads>
 __device__ __forceinline__ uint32_t block_inclusive_scan(uint32_t v, uint32_t* wave_tot,
                                                          uint32_t* total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -37,7 +40,7 @@ __device__ __forceinline__ uint32_t block_inclusive_scan(uint32_t v, uint32_t* w
   __syncthreads();
   uint32_t add = 0, tot = 0;
 #pragma unroll
-  for (int i = 0; i < kThreads / 64; ++i) {
+  for (int i = 0; i < THREADS / 64; ++i) {
     uint32_t t = wave_tot[i];
     if (i < w) add += t;
     tot += t;
@@ -63,7 +66,8 @@ __device__ __forceinline__ int64_t scan_len(int64_t n, const ScanLen& L) {
 template <bool GATHER>
 __global__ void __launch_bounds__(kThreads)
 scan_reduce_kernel(const uint32_t* __restrict__ in, const uint32_t* __restrict__ gather,
-                   int64_t n_cap, ScanLen L, uint32_t* __restrict__ partials,
+                   int64_t n_cap, ScanLen L, uint32_t* __restrict__ gathered,
+                   uint32_t* __restrict__ partials,
                    unsigned long long* __restrict__ partials64) {
   __shared__ uint32_t wave_tot[4];
   __shared__ unsigned long long wave_tot64[4];
@@ -77,6 +81,7 @@ scan_reduce_kernel(const uint32_t* __restrict__ in, const uint32_t* __restrict__
     int64_t i = base + k * kThreads + threadIdx.x;
     if (i < n) {
       const uint32_t x = scan_load<GATHER>(in, gather, i);
+      if (GATHER) gathered[i] = x;
       s += x;
       s64 += x;
     }
@@ -159,12 +164,11 @@ __device__ __forceinline__ int pad_idx(int i) { return i + (i >> 5); }
 // With chunk_owner, element i with value x > 0 and exclusive prefix o also records itself as
 // the owner of every chunk of kChunkSlots slots that starts inside [o, o + x) (chunk indices
 // below n_chunks).
-template <bool GATHER>
+// `in` may be `out`: a workgroup has read its elements before it writes them.
 __global__ void __launch_bounds__(kThreads)
-scan_down_kernel(const uint32_t* __restrict__ in, const uint32_t* __restrict__ gather,
-                 int64_t n_cap, ScanLen L, const uint32_t* __restrict__ partials,
-                 uint32_t* __restrict__ out, uint32_t* __restrict__ chunk_owner,
-                 int64_t n_chunks) {
+scan_down_kernel(const uint32_t* in, int64_t n_cap, ScanLen L,
+                 const uint32_t* __restrict__ partials, uint32_t* out,
+                 uint32_t* __restrict__ chunk_owner, int64_t n_chunks) {
   __shared__ uint32_t tile[kScanTile + kScanTile / 32];
   __shared__ uint32_t wave_tot[4];
   const int64_t n = scan_len(n_cap, L);
@@ -174,7 +178,7 @@ scan_down_kernel(const uint32_t* __restrict__ in, const uint32_t* __restrict__ g
 #pragma unroll 4
   for (int k = 0; k < kItems; ++k) {
     int64_t i = base + k * kThreads + threadIdx.x;
-    tile[pad_idx(k * kThreads + threadIdx.x)] = i < n ? scan_load<GATHER>(in, gather, i) : 0u;
+    tile[pad_idx(k * kThreads + threadIdx.x)] = i < n ? in[i] : 0u;
   }
   __syncthreads();
   uint32_t loc[kItems];
@@ -279,7 +283,7 @@ radix_hist_kernel(const uint32_t* __restrict__ keys, const uint32_t* __restrict_
     }
     __syncthreads();  // the next tile reuses the LDS histograms
   }
-  if (threadIdx.x < kBins && acc != 0)
+  if (digit_tot && threadIdx.x < kBins && acc != 0)
     atomicAdd(&digit_tot[(blockIdx.x % kTotCopies) * 256 + threadIdx.x], acc);
 }
 
@@ -322,8 +326,16 @@ radix_offsets_kernel(const uint32_t* __restrict__ d_n, int64_t n_cap,
   }
 }
 
+// Threads of a scatter workgroup: eight elements each (with 16 a thread took 160 registers and a
+// SIMD held three waves); the reordered tile passes through LDS twice, keys and then values, which
+// halves what a workgroup takes of it. Bound by the writes, runs of a digit 64 bytes long on average
+// with 8-bit digits. Mean of a pass, with the XCD order below: 16M records and 60M and 19M pairs 160
+// -> 126 us (2.8 -> 3.5 TB/s); 1M records 11.6 -> 10.5, 8.4M pairs 21.3 -> 19.1.
+constexpr int kScatterThreads = 512;
+constexpr int kScatterItems = kRadixTile / kScatterThreads;
+
 // Places one tile's elements (from `base`, up to n): gstart is the output index of the tile's first
-// element of digit threadIdx.x (< the number of digits). All 256 threads take part.
+// element of digit threadIdx.x (threads below the number of digits). All threads take part.
 template <int NBITS>
 __device__ __forceinline__ void scatter_tile(const uint32_t* __restrict__ keys_in,
                                              const uint32_t* __restrict__ vals_in,
@@ -332,32 +344,33 @@ __device__ __forceinline__ void scatter_tile(const uint32_t* __restrict__ keys_i
                                              int64_t base, int shift, uint32_t gstart) {
   constexpr int kBins = 1 << NBITS;
   constexpr uint32_t kMask = (uint32_t)kBins - 1u;
-  constexpr int kWaves = kRadixThreads / 64;
+  constexpr int kWaves = kScatterThreads / 64;
   constexpr int kPerWave = kRadixTile / kWaves;  // contiguous elements ranked by one wave
-  __shared__ uint32_t s_keys[kRadixTile];
-  __shared__ uint32_t s_vals[kRadixTile];
-  __shared__ uint32_t s_cnt[kWaves][256];  // running per-wave digit counts, then wave offsets
-  __shared__ uint32_t s_start[256];
+  __shared__ uint32_t s_buf[kRadixTile];  // the tile's keys in digit order, then its values
+  __shared__ uint32_t s_cnt[kWaves][kBins];  // running per-wave digit counts, then wave offsets
   __shared__ uint32_t s_gofs[kBins];  // output index of the tile's element 0 of each digit
-  __shared__ uint32_t wave_tot[4];
+  __shared__ uint32_t wave_tot[kWaves];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int nvalid = (int)((n - base) < kRadixTile ? (n - base) : kRadixTile);
+  keys_in += base;
+  vals_in += base;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) s_cnt[w][lane + 64 * k] = 0;
+  for (int k = 0; k < kBins; k += 64)
+    if (k + lane < kBins) s_cnt[w][k + lane] = 0;
   __builtin_amdgcn_wave_barrier();
-  // Each wave ranks its own contiguous quarter of the tile in rounds of 64 elements; program
+  // Each wave ranks its own contiguous part of the tile in rounds of 64 elements; program
   // order inside the wave keeps equal digits in index order.
-  uint32_t key_r[kRadixItems], val_r[kRadixItems], rank_r[kRadixItems];
+  uint32_t key_r[kScatterItems], val_r[kScatterItems], place[kScatterItems];
   // all loads first (memory-level parallelism)
 #pragma unroll
-  for (int r = 0; r < kRadixItems; ++r) {
+  for (int r = 0; r < kScatterItems; ++r) {
     const int i = w * kPerWave + r * 64 + lane;
     const bool valid = i < nvalid;
-    key_r[r] = valid ? keys_in[base + i] : 0u;
-    val_r[r] = valid ? vals_in[base + i] : 0u;
+    key_r[r] = valid ? keys_in[i] : 0u;
+    val_r[r] = valid ? vals_in[i] : 0u;
   }
 #pragma unroll
-  for (int r = 0; r < kRadixItems; ++r) {
+  for (int r = 0; r < kScatterItems; ++r) {
     const int i = w * kPerWave + r * 64 + lane;
     const bool valid = i < nvalid;
     const uint32_t d = (key_r[r] >> shift) & kMask;
@@ -374,57 +387,104 @@ __device__ __forceinline__ void scatter_tile(const uint32_t* __restrict__ keys_i
     __builtin_amdgcn_wave_barrier();
     if (valid && below == 0) s_cnt[w][d] = cnt + popc64(m);
     __builtin_amdgcn_wave_barrier();
-    rank_r[r] = cnt + below;
+    place[r] = cnt + below;
   }
   __syncthreads();
-  // digit totals of the tile, offsets of each wave inside a digit, digit starts
-  uint32_t tot = 0;
+  // digit totals of the tile, digit starts, and from both where each wave's part of a digit starts
+  uint32_t c[kWaves], tot = 0;
+  if (tid < kBins) {
 #pragma unroll
-  for (int ww = 0; ww < kWaves; ++ww) {
-    const uint32_t c = s_cnt[ww][tid];
-    s_cnt[ww][tid] = tot;
-    tot += c;
+    for (int ww = 0; ww < kWaves; ++ww) c[ww] = s_cnt[ww][tid];
+#pragma unroll
+    for (int ww = 0; ww < kWaves; ++ww) tot += c[ww];
   }
   uint32_t total;
-  const uint32_t incl = block_inclusive_scan(tot, wave_tot, &total);
-  s_start[tid] = incl - tot;
-  // element counts fit in 32 bits, so output indices do too
-  if (tid < kBins) s_gofs[tid] = gstart - (incl - tot);
-  __syncthreads();
+  uint32_t start = block_inclusive_scan<kScatterThreads>(tot, wave_tot, &total) - tot;
+  if (tid < kBins) {
+    s_gofs[tid] = gstart - start;  // element counts fit in 32 bits, so output indices do too
 #pragma unroll
-  for (int r = 0; r < kRadixItems; ++r) {
-    const int i = w * kPerWave + r * 64 + lane;
-    if (i < nvalid) {
-      const uint32_t d = (key_r[r] >> shift) & kMask;
-      const uint32_t pos = s_start[d] + s_cnt[w][d] + rank_r[r];
-      s_keys[pos] = key_r[r];
-      s_vals[pos] = val_r[r];
+    for (int ww = 0; ww < kWaves; ++ww) {
+      s_cnt[ww][tid] = start;
+      start += c[ww];
     }
   }
   __syncthreads();
-  for (int i = tid; i < nvalid; i += kRadixThreads) {
-    const uint32_t key = s_keys[i];
-    const uint32_t gpos = s_gofs[(key >> shift) & kMask] + (uint32_t)i;
-    keys_out[gpos] = key;
-    vals_out[gpos] = s_vals[i];
+#pragma unroll
+  for (int r = 0; r < kScatterItems; ++r) {
+    const int i = w * kPerWave + r * 64 + lane;
+    place[r] += s_cnt[w][(key_r[r] >> shift) & kMask];
+    if (i < nvalid) s_buf[place[r]] = key_r[r];
+  }
+  __syncthreads();
+  uint32_t gpos[kScatterItems];
+#pragma unroll
+  for (int r = 0; r < kScatterItems; ++r) {
+    const int i = r * kScatterThreads + tid;
+    if (i < nvalid) {
+      const uint32_t key = s_buf[i];
+      gpos[r] = s_gofs[(key >> shift) & kMask] + (uint32_t)i;
+      keys_out[gpos[r]] = key;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kScatterItems; ++r) {
+    const int i = w * kPerWave + r * 64 + lane;
+    if (i < nvalid) s_buf[place[r]] = val_r[r];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kScatterItems; ++r) {
+    const int i = r * kScatterThreads + tid;
+    if (i < nvalid) vals_out[gpos[r]] = s_buf[i];
   }
   __syncthreads();  // the next tile reuses the LDS
 }
 
-template <int NBITS>
-__global__ void __launch_bounds__(kRadixThreads)
+// OWN: the workgroup works out its output offsets itself from the tiles' raw counts (few tiles, see
+// kOwnOffsetTiles) where otherwise radix_offsets_kernel has left them in `hist`.
+template <int NBITS, bool OWN>
+__global__ void __launch_bounds__(kScatterThreads)
 radix_scatter_kernel(const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
                      uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out,
                      const uint32_t* __restrict__ d_n, int64_t n_cap, int shift,
-                     const uint32_t* __restrict__ hist_scanned, uint32_t* __restrict__ digit_tot) {
+                     const uint32_t* __restrict__ hist, uint32_t* __restrict__ digit_tot) {
   const int64_t n = sort_count(d_n, n_cap);
   const int64_t nb = (n + kRadixTile - 1) / kRadixTile;
   const int tid = threadIdx.x;
+  if constexpr (OWN) {
+    // one tile per workgroup: this thread's digit, over all tiles and over those before
+    __shared__ uint32_t own_tot[kScatterThreads / 64];
+    const int64_t tile = blockIdx.x;
+    if (tile >= nb) return;
+    uint32_t all = 0, before = 0;
+    if (tid < (1 << NBITS)) {
+      const uint32_t* __restrict__ row = hist + (int64_t)tid * nb;
+#pragma unroll 8
+      for (int64_t t = 0; t < nb; ++t) {
+        const uint32_t c = row[t];
+        all += c;
+        before += t < tile ? c : 0u;
+      }
+    }
+    uint32_t total;
+    const uint32_t first = block_inclusive_scan<kScatterThreads>(all, own_tot, &total) - all;
+    scatter_tile<NBITS>(keys_in, vals_in, keys_out, vals_out, n, tile * kRadixTile, shift,
+                        first + before);
+    return;
+  }
   // the offsets launch has read this pass's digit totals: leave them zero for the next sort
-  for (int c = blockIdx.x; c < kTotCopies; c += gridDim.x) digit_tot[c * 256 + tid] = 0u;
-  for (int64_t tile = blockIdx.x; tile < nb; tile += gridDim.x) {
+  for (int c = blockIdx.x; c < kTotCopies; c += gridDim.x)
+    if (tid < 256) digit_tot[c * 256 + tid] = 0u;
+  // Workgroups go to the eight XCDs in turn: each XCD takes a contiguous eighth of the tiles, so
+  // that neighbouring tiles, whose runs of a digit follow one another in the output, meet in one L2
+  // and fill its lines together.
+  const int64_t per_xcd = (nb + 7) / 8;
+  for (int64_t v = blockIdx.x; v < 8 * per_xcd; v += gridDim.x) {
+    const int64_t tile = (v & 7) * per_xcd + (v >> 3);
+    if (tile >= nb) continue;
     // where each digit of this tile starts in the output (loaded early, used at the end)
-    const uint32_t gstart = tid < (1 << NBITS) ? hist_scanned[(int64_t)tid * nb + tile] : 0u;
+    const uint32_t gstart = tid < (1 << NBITS) ? hist[(int64_t)tid * nb + tile] : 0u;
     scatter_tile<NBITS>(keys_in, vals_in, keys_out, vals_out, n, tile * kRadixTile, shift, gstart);
   }
 }
@@ -436,29 +496,29 @@ radix_scatter_kernel(const uint32_t* __restrict__ keys_in, const uint32_t* __res
 // launches, which each cost 4 to 5 us whatever they do: 5000 pairs in 64 tiles of an image, sort
 // and ranges 28 -> 9 us.
 template <int NBITS>
-__global__ void __launch_bounds__(kRadixThreads)
+__global__ void __launch_bounds__(kScatterThreads)
 radix_direct_kernel(const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
                     uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out,
                     const uint32_t* __restrict__ d_n, int64_t n_cap, int shift,
                     uint32_t* __restrict__ ranges) {
   constexpr int kBins = 1 << NBITS;
   constexpr uint32_t kMask = (uint32_t)kBins - 1u;
-  __shared__ uint32_t s_before[256], s_after[256];
-  __shared__ uint32_t wave_tot[4];
+  __shared__ uint32_t s_before[kBins], s_after[kBins];
+  __shared__ uint32_t own_tot[kScatterThreads / 64];
   const int n = (int)sort_count(d_n, n_cap);
   const int tid = threadIdx.x;
   const int base = (int)blockIdx.x * kRadixTile;
   if (base >= n) return;
-  s_before[tid] = 0u;
-  s_after[tid] = 0u;
+  if (tid < kBins) s_before[tid] = s_after[tid] = 0u;
   __syncthreads();
 #pragma unroll 4
-  for (int i = tid; i < n; i += kRadixThreads)
+  for (int i = tid; i < n; i += kScatterThreads)
     atomicAdd(&(i < base ? s_before : s_after)[(keys_in[i] >> shift) & kMask], 1u);
   __syncthreads();
-  const uint32_t before = s_before[tid], all = before + s_after[tid];
+  const uint32_t before = tid < kBins ? s_before[tid] : 0u;
+  const uint32_t all = tid < kBins ? before + s_after[tid] : 0u;
   uint32_t total;
-  const uint32_t first = block_inclusive_scan(all, wave_tot, &total) - all;
+  const uint32_t first = block_inclusive_scan<kScatterThreads>(all, own_tot, &total) - all;
   if (ranges && blockIdx.x == 0 && all != 0u) {
     ranges[2 * tid] = first;
     ranges[2 * tid + 1] = first + all;
@@ -549,20 +609,18 @@ hipError_t launch_scan_u32(const uint32_t* in, const uint32_t* gather, uint32_t*
   if (nb == 0) return hipSuccess;
   if (!total64) partials64 = nullptr;
   if (total64 && !partials64) return hipErrorInvalidValue;
+  // gathered values are kept in `out` by the first pass: the second then reads them in order (a
+  // second gather took as long as the first; 16M records: 493 -> 300 us)
   if (gather)
     hipLaunchKernelGGL(scan_reduce_kernel<true>, dim3((unsigned)nb), dim3(kThreads), 0, s, in,
-                       gather, n, len, partials, partials64);
+                       gather, n, len, out, partials, partials64);
   else
     hipLaunchKernelGGL(scan_reduce_kernel<false>, dim3((unsigned)nb), dim3(kThreads), 0, s, in,
-                       gather, n, len, partials, partials64);
+                       gather, n, len, nullptr, partials, partials64);
   hipLaunchKernelGGL(scan_partials_kernel, dim3(1), dim3(1024), 0, s, partials, n, len, total,
                      partials64, total64);
-  if (gather)
-    hipLaunchKernelGGL(scan_down_kernel<true>, dim3((unsigned)nb), dim3(kThreads), 0, s, in,
-                       gather, n, len, partials, out, chunk_owner, n_chunks);
-  else
-    hipLaunchKernelGGL(scan_down_kernel<false>, dim3((unsigned)nb), dim3(kThreads), 0, s, in,
-                       gather, n, len, partials, out, chunk_owner, n_chunks);
+  hipLaunchKernelGGL(scan_down_kernel, dim3((unsigned)nb), dim3(kThreads), 0, s,
+                     gather ? out : in, n, len, partials, out, chunk_owner, n_chunks);
   return hipGetLastError();
 }
 
@@ -570,21 +628,33 @@ hipError_t launch_scan_u32(const uint32_t* in, const uint32_t* gather, uint32_t*
 // about 1 us per tile and pass, against 4 to 5 for each of the two launches saved.
 constexpr int64_t kDirectTiles = 4;
 
+// Radix tiles up to which a pass leaves out the offsets launch: every workgroup then reads all
+// tiles' counts, 1 KB per tile.
+constexpr int64_t kOwnOffsetTiles = 128;
+
 template <int NBITS>
 hipError_t radix_pass(const uint32_t* ki, const uint32_t* vi, uint32_t* ko, uint32_t* vo,
                       const uint32_t* d_n, int64_t n_cap, int shift, int64_t nb, uint32_t* hist,
                       uint32_t* digit_tot, uint32_t* ranges, hipStream_t s) {
   if (nb <= kDirectTiles) {
-    hipLaunchKernelGGL(radix_direct_kernel<NBITS>, dim3((unsigned)nb), dim3(kRadixThreads), 0, s,
-                       ki, vi, ko, vo, d_n, n_cap, shift, ranges);
+    hipLaunchKernelGGL(radix_direct_kernel<NBITS>, dim3((unsigned)nb), dim3(kScatterThreads), 0,
+                       s, ki, vi, ko, vo, d_n, n_cap, shift, ranges);
     return hipGetLastError();
   }
   const unsigned grid = (unsigned)(nb < kRadixGrid ? nb : kRadixGrid);
+  const unsigned grid8 = (grid + 7) / 8 * 8;  // whole rounds over the XCDs
+  if (nb <= kOwnOffsetTiles) {
+    hipLaunchKernelGGL(radix_hist_kernel<NBITS>, dim3(grid), dim3(kRadixThreads), 0, s, ki, d_n,
+                       n_cap, shift, hist, nullptr);
+    hipLaunchKernelGGL((radix_scatter_kernel<NBITS, true>), dim3(grid), dim3(kScatterThreads), 0, s,
+                       ki, vi, ko, vo, d_n, n_cap, shift, hist, nullptr);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(radix_hist_kernel<NBITS>, dim3(grid), dim3(kRadixThreads), 0, s, ki, d_n,
                      n_cap, shift, hist, digit_tot);
   hipLaunchKernelGGL(radix_offsets_kernel<NBITS>, dim3(1u << NBITS), dim3(kThreads), 0, s, d_n,
                      n_cap, digit_tot, hist);
-  hipLaunchKernelGGL(radix_scatter_kernel<NBITS>, dim3(grid), dim3(kRadixThreads), 0, s, ki, vi,
+  hipLaunchKernelGGL((radix_scatter_kernel<NBITS, false>), dim3(grid8), dim3(kScatterThreads), 0, s, ki, vi,
                      ko, vo, d_n, n_cap, shift, hist, digit_tot);
   return hipGetLastError();
 }
