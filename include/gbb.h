@@ -311,6 +311,20 @@ gb_status gb_adam_step(int64_t n, float* param, const float* grad, float* m, flo
                        int32_t step, float lr, float beta1, float beta2, float eps,
                        uint16_t* bf16_copy, void* stream);
 
+/* The same step on several parameter arrays, each with its own learning rate, in one launch per
+ * GB_ADAM_GROUPS of them. Arrays of n = 0 are skipped; nothing is updated if any is refused. */
+#define GB_ADAM_GROUPS 8
+typedef struct {
+  int64_t n;
+  float* param;
+  const float* grad;
+  float *m, *v;
+  uint16_t* bf16_copy; /* nullable */
+  float lr;
+} gb_adam_group;
+gb_status gb_adam_steps(const gb_adam_group* groups, int32_t n_groups, int32_t step, float beta1,
+                        float beta2, float eps, void* stream);
+
 /* dst[i] = src[i] rounded to bfloat16 (nearest, ties to even) as uint16 bit patterns: the
  * initial render copy of float32 textures. */
 gb_status gb_to_bf16(int64_t n, const float* src, uint16_t* dst, void* stream);

@@ -21,8 +21,8 @@ EXPORTS = (
     "gb_workspace_layout", "gb_count_pairs", "gb_render_fwd", "gb_render_bwd",
     "gb_read_status", "gb_blend_stats", "gb_timing_enable", "gb_timing_read",
     "gb_timing_stage_name", "gb_default_options", "gb_status_string", "gb_last_error",
-    "gb_activate_fwd", "gb_activate_bwd", "gb_l1_loss", "gb_adam_step", "gb_to_bf16",
-    "gb_mse_loss", "gb_box_filter_textures", "gb_rotz_only",
+    "gb_activate_fwd", "gb_activate_bwd", "gb_l1_loss", "gb_adam_step", "gb_adam_steps",
+    "gb_to_bf16", "gb_mse_loss", "gb_box_filter_textures", "gb_rotz_only",
     "gb_densify_stats", "gb_densify_work_bytes", "gb_densify_plan", "gb_densify_apply",
     "gb_densify_noalloc", "gb_render_fwd_zeroing",
 )
@@ -85,6 +85,11 @@ class GbRowState(ctypes.Structure):
     _fields_ = [("src", c_void_p), ("dst", c_void_p), ("width", c_int32)]
 
 
+class GbAdamGroup(ctypes.Structure):
+    _fields_ = [("n", c_int64), ("param", c_void_p), ("grad", c_void_p), ("m", c_void_p),
+                ("v", c_void_p), ("bf16_copy", c_void_p), ("lr", c_float)]
+
+
 class GbbError(RuntimeError):
     def __init__(self, status: int, where: str, detail: str):
         super().__init__(f"{where}: status {status} ({detail})")
@@ -137,6 +142,8 @@ def load() -> ctypes.CDLL:
     lib.gb_l1_loss.argtypes = [c_int64, c_void_p, c_void_p, c_float, c_void_p, c_void_p, c_void_p]
     lib.gb_adam_step.argtypes = [c_int64, c_void_p, c_void_p, c_void_p, c_void_p, c_int32,
                                  c_float, c_float, c_float, c_float, c_void_p, c_void_p]
+    lib.gb_adam_steps.argtypes = [POINTER(GbAdamGroup), c_int32, c_int32, c_float, c_float,
+                                  c_float, c_void_p]
     lib.gb_to_bf16.argtypes = [c_int64, c_void_p, c_void_p, c_void_p]
     lib.gb_mse_loss.argtypes = [c_int64, c_void_p, c_void_p, c_float, c_void_p, c_void_p, c_void_p]
     lib.gb_box_filter_textures.argtypes = [c_int32, c_int32, c_int32, c_void_p, c_void_p,
@@ -161,7 +168,7 @@ def load() -> ctypes.CDLL:
                  "gb_render_fwd_zeroing",
                  "gb_read_status", "gb_blend_stats", "gb_timing_enable", "gb_timing_read",
                  "gb_activate_fwd", "gb_activate_bwd", "gb_l1_loss", "gb_adam_step",
-                 "gb_to_bf16", "gb_mse_loss", "gb_box_filter_textures", "gb_rotz_only",
+                 "gb_adam_steps", "gb_to_bf16", "gb_mse_loss", "gb_box_filter_textures", "gb_rotz_only",
                  "gb_densify_stats", "gb_densify_plan",
                  "gb_densify_apply", "gb_densify_noalloc"):
         getattr(lib, name).restype = c_int32

@@ -1164,25 +1164,41 @@ gb_status gb_rotz_only(int32_t P, float* d_quats, void* stream) {
   return GB_OK;
 }
 
-gb_status gb_adam_step(int64_t n, float* param, const float* grad, float* m, float* v,
-                       int32_t step, float lr, float beta1, float beta2, float eps,
-                       uint16_t* bf16_copy, void* stream) {
-  if (n < 0) return arg_fail("n must be >= 0");
+gb_status gb_adam_steps(const gb_adam_group* groups, int32_t n_groups, int32_t step, float beta1,
+                        float beta2, float eps, void* stream) {
+  if (n_groups < 0 || (n_groups > 0 && !groups)) return arg_fail("Adam groups NULL");
   if (step < 1) return arg_fail("step must be >= 1");
   if (!(beta1 >= 0.f && beta1 < 1.f) || !(beta2 >= 0.f && beta2 < 1.f))
     return arg_fail("betas must be in [0, 1)");
-  if (n == 0) return GB_OK;
-  const void* ptrs[] = {param, grad, m, v};
-  for (const void* p : ptrs)
-    if (!p || !aligned(p, 16)) return arg_fail("Adam array NULL or not 16-byte aligned");
-  if (bf16_copy && !aligned(bf16_copy, 8)) return arg_fail("bf16 copy not 8-byte aligned");
+  for (int32_t k = 0; k < n_groups; ++k) {
+    const gb_adam_group& g = groups[k];
+    if (g.n < 0) return arg_fail("n must be >= 0");
+    if (g.n == 0) continue;
+    const void* ptrs[] = {g.param, g.grad, g.m, g.v};
+    for (const void* p : ptrs)
+      if (!p || !aligned(p, 16)) return arg_fail("Adam array NULL or not 16-byte aligned");
+    if (g.bf16_copy && !aligned(g.bf16_copy, 8)) return arg_fail("bf16 copy not 8-byte aligned");
+  }
   // bias corrections in double precision
   const double c1 = 1.0 / (1.0 - std::pow((double)beta1, (double)step));
   const double c2 = 1.0 / (1.0 - std::pow((double)beta2, (double)step));
-  GBB_TRY(launch_adam(n, param, grad, m, v, lr, beta1, beta2, (float)c1, (float)c2, eps, bf16_copy,
-                      reinterpret_cast<hipStream_t>(stream)),
-          "adam");
+  for (int32_t k = 0; k < n_groups;) {
+    gb_adam_group list[GB_ADAM_GROUPS];
+    int n = 0;
+    for (; k < n_groups && n < GB_ADAM_GROUPS; ++k)
+      if (groups[k].n > 0) list[n++] = groups[k];
+    GBB_TRY(launch_adam(list, n, beta1, beta2, (float)c1, (float)c2, eps,
+                        reinterpret_cast<hipStream_t>(stream)),
+            "adam");
+  }
   return GB_OK;
+}
+
+gb_status gb_adam_step(int64_t n, float* param, const float* grad, float* m, float* v,
+                       int32_t step, float lr, float beta1, float beta2, float eps,
+                       uint16_t* bf16_copy, void* stream) {
+  const gb_adam_group g{n, param, grad, m, v, bf16_copy, lr};
+  return gb_adam_steps(&g, 1, step, beta1, beta2, eps, stream);
 }
 
 gb_status gb_to_bf16(int64_t n, const float* src, uint16_t* dst, void* stream) {

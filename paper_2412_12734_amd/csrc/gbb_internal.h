@@ -283,9 +283,9 @@ hipError_t launch_box_filter(int64_t P, int N, int M, const float* in, float* ou
                              hipStream_t s);
 hipError_t launch_rotz_only(int64_t P, float* d_quats, hipStream_t s);
 hipError_t launch_to_bf16(int64_t n, const float* src, uint16_t* dst, hipStream_t s);
-hipError_t launch_adam(int64_t n, float* theta, const float* grad, float* m, float* v, float lr,
-                       float b1, float b2, float c1, float c2, float eps, uint16_t* bf16,
-                       hipStream_t s);
+// One Adam step on up to GB_ADAM_GROUPS arrays (none empty) in one launch.
+hipError_t launch_adam(const gb_adam_group* groups, int n_groups, float b1, float b2, float c1,
+                       float c2, float eps, hipStream_t s);
 // With sp.sh != null, d_spec[v P + k] holds the adjoint of record v P + k's view-dependent
 // colour; g.d_sh receives the coefficients' gradient and the centres' gradient includes the
 // term through the view direction.

@@ -151,14 +151,31 @@ __device__ __forceinline__ float adam_one(float& theta, float g, float& m, float
   return theta;
 }
 
-// One Adam step; c1 = 1 / (1 - beta1^t), c2 = 1 / (1 - beta2^t) come from the host in double
-// precision. With bf16 the updated values are also stored rounded to bfloat16.
+// One Adam step on every array of the list; c1 = 1 / (1 - beta1^t), c2 = 1 / (1 - beta2^t) come from
+// the host in double precision. With bf16 the updated values are also stored rounded to bfloat16.
+// An array has its own run of workgroups, from first_block on. Bound by memory (30 bytes per
+// parameter with the copy: 101M parameters 0.62 ms, 4.9 TB/s); small clouds by launches, of which
+// one takes the place of one per array (10k splats, five arrays 23 -> 6 us).
+struct AdamList {
+  gb_adam_group g[GB_ADAM_GROUPS];
+  unsigned first_block[GB_ADAM_GROUPS + 1];
+};
+
 __global__ void __launch_bounds__(kThreads)
-adam_kernel(int64_t n, float* __restrict__ theta, const float* __restrict__ grad,
-            float* __restrict__ m, float* __restrict__ v, float lr, float b1, float b2, float c1,
-            float c2, float eps, uint16_t* __restrict__ bf16) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; 4 * i < n; i += stride) {
+adam_kernel(AdamList list, float b1, float b2, float c1, float c2, float eps) {
+  int k = 0;
+  while (blockIdx.x >= list.first_block[k + 1]) ++k;
+  const unsigned block = blockIdx.x - list.first_block[k],
+                 blocks = list.first_block[k + 1] - list.first_block[k];
+  const int64_t n = list.g[k].n;
+  float* __restrict__ theta = list.g[k].param;
+  const float* __restrict__ grad = list.g[k].grad;
+  float* __restrict__ m = list.g[k].m;
+  float* __restrict__ v = list.g[k].v;
+  uint16_t* __restrict__ bf16 = list.g[k].bf16_copy;
+  const float lr = list.g[k].lr;
+  const int64_t stride = (int64_t)blocks * kThreads;
+  for (int64_t i = (int64_t)block * kThreads + threadIdx.x; 4 * i < n; i += stride) {
     if (4 * i + 3 < n) {
       float4 th = reinterpret_cast<float4*>(theta)[i];
       const float4 g = reinterpret_cast<const float4*>(grad)[i];
@@ -288,11 +305,17 @@ hipError_t launch_l1_loss(int64_t n, const float* rgb, const float* target, floa
   return hipGetLastError();
 }
 
-hipError_t launch_adam(int64_t n, float* theta, const float* grad, float* m, float* v, float lr,
-                       float b1, float b2, float c1, float c2, float eps, uint16_t* bf16,
-                       hipStream_t s) {
-  hipLaunchKernelGGL(adam_kernel, dim3(grid_for(n, 4)), dim3(kThreads), 0, s, n, theta, grad, m,
-                     v, lr, b1, b2, c1, c2, eps, bf16);
+hipError_t launch_adam(const gb_adam_group* groups, int n_groups, float b1, float b2, float c1,
+                       float c2, float eps, hipStream_t s) {
+  if (n_groups < 1) return hipSuccess;
+  if (n_groups > GB_ADAM_GROUPS) return hipErrorInvalidValue;
+  AdamList list{};
+  for (int k = 0; k < n_groups; ++k) {
+    list.g[k] = groups[k];
+    list.first_block[k + 1] = list.first_block[k] + grid_for(groups[k].n, 4);
+  }
+  hipLaunchKernelGGL(adam_kernel, dim3(list.first_block[n_groups]), dim3(kThreads), 0, s, list, b1,
+                     b2, c1, c2, eps);
   return hipGetLastError();
 }
 

@@ -147,12 +147,13 @@ class TrainState:
     def adam(self, raw_grads: Dict[str, torch.Tensor]) -> None:
         self.step_count += 1
         b1, b2 = self.betas
-        for g in GROUPS:
-            t = self.params[g]
-            bits = self.tex_bits if (g == "textures" and self.bf16) else None
-            L.check(self.lib.gb_adam_step(t.numel(), _p(t), _p(raw_grads[g]), _p(self.m[g]),
-                                          _p(self.v[g]), self.step_count, self.lr[g], b1, b2,
-                                          self.eps, _p(bits), self.stream()), "gb_adam_step")
+        groups = (L.GbAdamGroup * len(GROUPS))(*(
+            L.GbAdamGroup(self.params[g].numel(), _p(self.params[g]), _p(raw_grads[g]),
+                          _p(self.m[g]), _p(self.v[g]),
+                          _p(self.tex_bits if (g == "textures" and self.bf16) else None),
+                          self.lr[g]) for g in GROUPS))
+        L.check(self.lib.gb_adam_steps(groups, len(GROUPS), self.step_count, b1, b2, self.eps,
+                                       self.stream()), "gb_adam_steps")
 
 
 def l1_loss(rgb: torch.Tensor, target: torch.Tensor, scale: float, loss: torch.Tensor,
@@ -285,11 +286,16 @@ class Trainer:
             # a completed earlier step overflowed: re-size for this batch and render again
             self.rast.plan(sp, int(self.rast.count_pairs(sp) * 1.5) + 4096)
             rgb, T = self.rast.forward(sp, rgb, T, zero_grads=zg)
-        at = 0
-        for i in batch:  # device-to-device copies of the batch's target images
-            hw = self.views[i].width * self.views[i].height
-            target[at:at + hw].copy_(self.targets[i].view(-1, 3)[:hw])
-            at += hw
+        one = self.targets[batch[0]].view(-1, 3)[:n_px] if len(batch) == 1 else None
+        if (one is not None and one.dtype == torch.float32 and one.device == rgb.device
+                and one.is_contiguous() and one.data_ptr() % 16 == 0):
+            target = one  # a single image is compared where it lies
+        else:
+            at = 0
+            for i in batch:  # device-to-device copies of the batch's target images
+                hw = self.views[i].width * self.views[i].height
+                target[at:at + hw].copy_(self.targets[i].view(-1, 3)[:hw])
+                at += hw
         self.loss_fn(rgb, target, 1.0 / (3 * n_px), self.loss, d_rgb)
         self.grads = self.rast.backward(sp, T, d_rgb, self.grads)
         if self.grad_accum is not None:
