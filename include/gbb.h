@@ -106,15 +106,14 @@ typedef struct {
   float bg[3];        /* background colour composited with the final transmittance */
   int32_t tile_w;     /* tile width in px: 8, 16 or 32 */
   int32_t tile_h;     /* tile height in px: 8, 16 or 32; tile_w * tile_h <= 256 */
-  int32_t batch;      /* most splats staged in LDS per forward batch: 0 = default (4 for N = 16,
-                         16 for N = 8, 32 for N = 4, else 64), or 8, 16, 32, 64 (N < 16), 4
-                         (N = 16, its only batch). The kernels take fewer where that lets
-                         another workgroup share a CU (N = 8: 12 of 16; N = 16: 3), and 64
-                         one-texel grids at a time whatever is asked. */
-  int32_t batch_bwd;  /* most splats staged in LDS per backward batch: 0 = default (4 for N = 16,
-                         8 for N = 8, else 32), or 8, 16, 32 (N < 16), 4 (N = 16, its only
-                         batch); on many tiles fewer as above (N = 4: 24 of 32; N = 8: 7 of 8;
-                         N = 16: 2), 64 one-texel grids at a time. */
+  int32_t batch;      /* most splats staged in LDS per forward batch: 0 = the library's choice (by
+                         the grid's side and the number of tiles), or 8, 16, 32, 64 (N < 16),
+                         4 (N = 16, whose batch the library always chooses). The kernels take
+                         fewer where that lets another workgroup share a CU (12 of 16 for N = 8),
+                         and 64 one-texel grids at a time whatever is asked. */
+  int32_t batch_bwd;  /* most splats staged in LDS per backward batch: 0 as above, or 8, 16, 32
+                         (N < 16), 4 (N = 16); on many tiles fewer as above (N = 4: 24 of 32;
+                         N = 8: 7 of 8), 64 one-texel grids at a time. */
   int32_t prefix_pairs_per_tile;
                       /* depth-prefix split. The first pass renders the longest prefix of the
                          depth order whose pairs fit this many pairs per tile (0 = default 1024);

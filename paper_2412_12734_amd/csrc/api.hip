@@ -129,17 +129,16 @@ gb_status make_plan(int32_t P, int32_t N, const gb_view* views, int32_t n_views,
   pl->capacity = capacity;
   pl->tile_w = o->tile_w == 0 ? 16 : o->tile_w;
   pl->tile_h = o->tile_h == 0 ? 16 : o->tile_h;
-  // defaults: the largest batches that the kernels' own limits leave worth while (fwd_batch and
-  // bwd_batch, which may take fewer and say what each measured)
-  pl->batch_fwd = o->batch != 0 ? o->batch : (N >= 16 ? 4 : N >= 8 ? 16 : N >= 4 ? 32 : 64);
-  pl->batch_bwd = o->batch_bwd != 0 ? o->batch_bwd : (N >= 16 ? 4 : N >= 8 ? 8 : 32);
+  // 0: the blends choose by the grid's side and the number of tiles (fwd_batch, bwd_batch)
+  pl->batch_fwd = o->batch;
+  pl->batch_bwd = o->batch_bwd;
   // N = 16 holds 10.6 KB of texels and sums per splat: batches of 4 are built for it only, and it
   // only with them
-  if (N >= 16 && (pl->batch_fwd != 4 || pl->batch_bwd != 4)) {
+  if (N >= 16 && ((o->batch != 0 && o->batch != 4) || (o->batch_bwd != 0 && o->batch_bwd != 4))) {
     g_last_error = "N = 16 takes batch and batch_bwd 4 (or 0)";
     return GB_ERR_UNSUPPORTED;
   }
-  if (N < 16 && (pl->batch_fwd == 4 || pl->batch_bwd == 4)) {
+  if (N < 16 && (o->batch == 4 || o->batch_bwd == 4)) {
     g_last_error = "batches of 4 are built for N = 16 only";
     return GB_ERR_UNSUPPORTED;
   }
@@ -347,8 +346,7 @@ gb_status run_preprocess(const gb_splats* s, const gb_view* views, int32_t n_vie
                          int64_t n_zero = 0) {
   GBB_TRY(stage_mark(kStPreprocess, 0, st), "timing");
   ViewDev* d_views = at<ViewDev>(ws, pl.off_views);
-  GBB_TRY(launch_upload_views(views, n_views, pl.tile_w, pl.tile_h, d_views, st), "upload views");
-  GBB_TRY(launch_preprocess(*s, d_views, n_views, *o, pl.tile_w, pl.tile_h,
+  GBB_TRY(launch_preprocess(*s, views, d_views, n_views, *o, pl.tile_w, pl.tile_h,
                             at<uint32_t>(ws, pl.off_depth_key),
                             at<uint32_t>(ws, pl.off_depth_key_alt), at<uint32_t>(ws, pl.off_count),
                             at<SplatRec>(ws, pl.off_rec), at<float4>(ws, pl.off_spec), order,

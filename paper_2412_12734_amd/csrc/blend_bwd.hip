@@ -226,26 +226,35 @@ __device__ __forceinline__ float record_gradient(int r, const double* x, const f
 // 0.64.)
 constexpr int kLaneAddMax = 20;
 
-// Splats per batch: a whole pass for one-texel grids; else the number asked for while the call's
-// tiles all run at once (few_tiles), and fewer where that lets another workgroup share a CU's 160
-// KB of LDS. Backward times:
+// Splats per batch: the number asked for, by default as many as let all tiles run at once, up to a
+// whole pass; on more tiles fewer, where that lets another workgroup share a CU's 160 KB of LDS.
+// Backward times:
 //  8 x 8 grids hold 2.8 KB per splat (texels and 64-bit sums) beside the pass's geometry: seven
 //  splats and passes of 32 entries (3 KB) are 22.7 KB, seven workgroups. 6 of 64 / 7 of 32 / 8 of
 //  64: 1.063 / 1.045 / 1.101 ms at 1M splats and 1080p, 11.4 / 10.8 / 11.9 at 3M splats on four
-//  1080p views, but 324 / 323 / 286 us at 120k small splats on 999 tiles.
+//  1080p views, but 324 / 323 / 286 us at 120k small splats on 999 tiles; 8 / 16 / 32 of 64 1.37 /
+//  1.13 / 1.03 ms at 235k splats on 112 tiles.
 //  4 x 4 grids, 16 / 24 / 32 splats: 16 uneven views of 1M splats 6.22 / 6.25 / 7.54 ms, 47k splats
-//  on three uneven views 0.558 / 0.529 / -, 372k splats on 462 tiles 1.27 / - / 1.11.
+//  on three uneven views 0.558 / 0.529 / -, 372k splats on 462 tiles 1.27 / - / 1.09.
 //  16 x 16 grids, 1 / 2 / 3 splats: 2.81 / 2.10 / 2.16 ms at 1M splats and 1080p, two in passes of
 //  48 entries (six workgroups per CU instead of five) 1.63. With sides {4, 8, 16} a grid is mostly
 //  smaller than its slot: 2 / 3 / 4 splats 3.88 / 3.11 / 2.59 ms at 202k splats on three views.
 template <int N, bool MIXED>
-constexpr int bwd_batch(int asked, bool few_tiles) {
-  return N == 1                                ? kPassEntries
-         : few_tiles || (N >= 16 && MIXED)     ? asked
-         : N >= 16                             ? 2
-         : N == 8 && asked == 8                ? 7
-         : N == 4 && asked == 32               ? 24
-                                               : asked;
+int bwd_batch(int asked, int64_t tiles) {
+  if (N == 1) return 64;
+  if (N == 16)
+    return tiles <= tiles_at_once(1) ? 8
+           : tiles <= tiles_at_once(2) ? 6
+           : tiles <= tiles_at_once(3) || MIXED ? 4 : 2;
+  if (N == 8) {
+    if (asked == 0 && tiles <= tiles_at_once(3)) return tiles <= tiles_at_once(1) ? 32 : 16;
+    return asked > 8 ? asked : tiles <= tiles_at_once(5) ? 8 : 7;
+  }
+  if (N == 4) {
+    if (asked == 0 && tiles <= tiles_at_once(2)) return 64;
+    return asked != 0 && asked < 32 ? asked : tiles <= tiles_at_once(5) ? 32 : 24;
+  }
+  return asked != 0 ? asked : tiles <= tiles_at_once(6) ? 64 : 32;
 }
 template <int N, int B>
 constexpr int bwd_pass_entries() {
@@ -257,10 +266,10 @@ constexpr int bwd_pass_entries() {
 // 13.2.
 template <int N, int B>
 constexpr int bwd_min_waves() {
-  return N <= 2 || (N == 4 && B <= 16) || (N == 8 && B <= 7)         ? 7
-         : (N == 4 && B == 24) || (N == 16 && B == 2)                ? 6
-         : N == 4 || (N == 8 && B == 8)                              ? 5
-                                                                     : 1;
+  return (N <= 2 && B <= 32) || N == 1 || (N == 4 && B <= 16) || (N == 8 && B <= 7) ? 7
+         : N == 2 || (N == 4 && B == 24) || (N == 16 && B == 2)                     ? 6
+         : (N == 4 && B == 32) || (N == 8 && B == 8)                                ? 5
+                                                                                    : 1;
 }
 
 // Lanes that flush one splat's sums: as few as keep the number of reads per lane small, so that a
@@ -654,13 +663,6 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
   }  // lists
 }
 
-// Whether the tiles of a call all find room at once with the larger batches: then the LDS limits
-// nothing and a larger batch only means fewer barriers and flushes.
-template <int N>
-bool few_tiles(int64_t tiles) {
-  return tiles <= 256 * (N >= 16 ? 3 : 5);  // CUs times workgroups per CU
-}
-
 template <int N, bool BF16, bool MIXED = false>
 hipError_t launch_np(const Plan& pl, const gb_splats& sp, const BlendParams& bp,
                      const ViewDev* views, const SplatRec* rec, const PairList& first,
@@ -669,25 +671,46 @@ hipError_t launch_np(const Plan& pl, const gb_splats& sp, const BlendParams& bp,
   const dim3 grid((unsigned)(bp.tile_order ? (int64_t)bp.total_tiles
                                            : 8 * (int64_t)bp.tiles_per_xcd));
   const dim3 block((unsigned)(pl.tile_w * pl.tile_h));
-#define GBB_BWD_B(ASKED, FEW)                                                                  \
-  hipLaunchKernelGGL((blend_bwd_kernel<N, BF16, bwd_batch<N, MIXED>(ASKED, FEW), MIXED>), grid,  \
-                     block, 0, s, views, rec, first, rest, open_bits, sp.textures, bp, T_final,  \
-                     d_rgb, d_rec, d_tex)
-  const bool few = few_tiles<N>(bp.total_tiles);
-  if constexpr (N >= 16) {
-    if (few) GBB_BWD_B(4, true);
-    else GBB_BWD_B(4, false);
+#define GBB_BWD_B(BB)                                                                          \
+  case BB:                                                                                     \
+    hipLaunchKernelGGL((blend_bwd_kernel<N, BF16, BB, MIXED>), grid, block, 0, s, views, rec,  \
+                       first, rest, open_bits, sp.textures, bp, T_final, d_rgb, d_rec, d_tex); \
+    break
+  const int batch = bwd_batch<N, MIXED>(pl.batch_bwd, bp.total_tiles);
+  if constexpr (N == 1) {
+    switch (batch) { GBB_BWD_B(64); }
+  } else if constexpr (N == 2) {
+    switch (batch) {
+      GBB_BWD_B(8);
+      GBB_BWD_B(16);
+      GBB_BWD_B(32);
+      GBB_BWD_B(64);
+      default: return hipErrorInvalidValue;
+    }
+  } else if constexpr (N == 4) {
+    switch (batch) {
+      GBB_BWD_B(8);
+      GBB_BWD_B(16);
+      GBB_BWD_B(24);
+      GBB_BWD_B(32);
+      GBB_BWD_B(64);
+      default: return hipErrorInvalidValue;
+    }
+  } else if constexpr (N == 8) {
+    switch (batch) {
+      GBB_BWD_B(7);
+      GBB_BWD_B(8);
+      GBB_BWD_B(16);
+      GBB_BWD_B(32);
+      default: return hipErrorInvalidValue;
+    }
   } else {
-    switch (pl.batch_bwd) {
-      case 8:
-        if (few) GBB_BWD_B(8, true);
-        else GBB_BWD_B(8, false);
-        break;
-      case 32:
-        if (few) GBB_BWD_B(32, true);
-        else GBB_BWD_B(32, false);
-        break;
-      default: GBB_BWD_B(16, true); break;
+    switch (batch) {
+      GBB_BWD_B(2);
+      GBB_BWD_B(4);
+      GBB_BWD_B(6);
+      GBB_BWD_B(8);
+      default: return hipErrorInvalidValue;
     }
   }
 #undef GBB_BWD_B

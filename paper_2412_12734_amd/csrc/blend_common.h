@@ -165,6 +165,10 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
   return (uint64_t)hi << 32 | lo;
 }
 
+// Most tiles that all run at once when `per_cu` workgroups share a CU (256 CUs): up to there the LDS
+// that a larger batch takes costs nothing, and it saves barriers and trips to memory.
+__host__ __device__ constexpr int64_t tiles_at_once(int per_cu) { return 256 * (int64_t)per_cu; }
+
 // Entries (consecutive pairs of the tile's list) whose geometry one staging pass prepares: one
 // per lane of each wave, which tests them against its own pixel block.
 constexpr int kPassEntries = 64;

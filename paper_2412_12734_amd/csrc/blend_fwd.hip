@@ -37,14 +37,20 @@ constexpr int fwd_min_waves() {
   return 160 * 1024 / lds < 8 ? 160 * 1024 / lds : 8;
 }
 
-// Splats per batch: the number asked for, or fewer where that lets eight workgroups share a CU's
-// LDS beside the pass's 6 KB of geometry. 8 x 8 grids (1.1 KB of texels per splat), when a step
-// still took 0.458 ms at 1M splats and 1080p, there and at 3M splats on four 1080p views: batches
-// of 8 0.482 / 5.26, 12 0.458 / 4.75, 16 0.501 / 5.28. 16 x 16 grids (4.3 KB) at 1M splats: 2 0.915,
-// 3 0.840, 4 0.854. One-texel grids stage their texels with the geometry, a whole pass at once.
+// Splats per batch: the number asked for; by default a whole pass, or as many as let all tiles run
+// at once, and on more tiles as many as let eight workgroups share a CU's LDS beside the pass's 6 KB
+// of geometry. 8 x 8 grids (1.1 KB of texels per splat), when a step still took 0.458 ms at 1M splats
+// and 1080p, there and at 3M splats on four 1080p views: batches of 8 0.482 / 5.26, 12 0.458 / 4.75,
+// 16 0.501 / 5.28; 350k small splats on 135 tiles, 12 / 64: 305 / 229 us. 4 x 4 grids, 372k small
+// splats on 462 tiles, 32 / 64: 437 / 382 us. 16 x 16 grids (4.3 KB) at 1M splats: 2 0.915, 3
+// 0.840, 4 0.854. One-texel grids stage their texels with the geometry, a whole pass at once.
 template <int N>
-constexpr int fwd_batch(int asked) {
-  return N == 1 ? kPassEntries : N >= 16 ? 3 : N == 8 && asked == 16 ? 12 : asked;
+int fwd_batch(int asked, int64_t tiles) {
+  if (N == 1) return 64;
+  if (N == 16) return tiles <= tiles_at_once(2) ? 16 : tiles <= tiles_at_once(3) ? 8 : 3;
+  if (asked != 0) return N == 8 && asked == 16 ? 12 : asked;
+  if (N == 8) return tiles <= tiles_at_once(2) ? 64 : tiles <= tiles_at_once(3) ? 32 : 12;
+  return N == 2 || tiles <= tiles_at_once(6) ? 64 : 32;
 }
 
 // This workgroup's slices of the arrays to zero (the coming backward's texture and record
@@ -327,14 +333,22 @@ hipError_t launch_n(const Plan& pl, const gb_splats& sp, const BlendParams& bp,
                      views,                                                                   \
                      rec, pair_vals, ranges, sp.textures, bp, rgb, T_final, n_last, split,    \
                      stats)
-  if constexpr (N >= 16) {
-    GBB_FWD_B(fwd_batch<N>(4));
+  const int batch = fwd_batch<N>(pl.batch_fwd, bp.total_tiles);
+  if constexpr (N == 1) {
+    GBB_FWD_B(64);
+  } else if constexpr (N == 16) {
+    switch (batch) {
+      case 16: GBB_FWD_B(16); break;
+      case 8: GBB_FWD_B(8); break;
+      default: GBB_FWD_B(3); break;
+    }
   } else {
-    switch (pl.batch_fwd) {
-      case 8: GBB_FWD_B(fwd_batch<N>(8)); break;
-      case 16: GBB_FWD_B(fwd_batch<N>(16)); break;
-      case 32: GBB_FWD_B(fwd_batch<N>(32)); break;
-      default: GBB_FWD_B(fwd_batch<N>(64)); break;
+    switch (batch) {
+      case 8: GBB_FWD_B(8); break;
+      case 12: GBB_FWD_B(12); break;
+      case 16: GBB_FWD_B(16); break;
+      case 32: GBB_FWD_B(32); break;
+      default: GBB_FWD_B(64); break;
     }
   }
 #undef GBB_FWD_B

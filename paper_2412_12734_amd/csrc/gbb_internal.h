@@ -130,15 +130,14 @@ constexpr int64_t kDigitTotWords = 4 * kTotCopies * 256;
 float lowpass_radius(float lowpass_var);
 
 // ---- launchers (all stream-ordered, no synchronisation) --------------------------------
-hipError_t launch_upload_views(const gb_view* views, int n_views, int tile_w, int tile_h,
-                               ViewDev* d_views, hipStream_t s);
 // With sp.sh != null it also writes spec[v P + k] = (view-dependent colour of splat k seen
 // from view v, 0) for every visible record. With order != null it also writes order[r] = r
 // for every record r and zero[i] = 0 for i < n_zero.
-hipError_t launch_preprocess(const gb_splats& sp, const ViewDev* d_views, int n_views,
-                             const gb_options& o, int tile_w, int tile_h, uint32_t* depth_key,
-                             uint32_t* sort_key, uint32_t* count, SplatRec* rec, float4* spec,
-                             uint32_t* order, uint32_t* zero, int64_t n_zero, hipStream_t s);
+hipError_t launch_preprocess(const gb_splats& sp, const gb_view* host_views, ViewDev* d_views,
+                             int n_views, const gb_options& o, int tile_w, int tile_h,
+                             uint32_t* depth_key, uint32_t* sort_key, uint32_t* count,
+                             SplatRec* rec, float4* spec, uint32_t* order, uint32_t* zero,
+                             int64_t n_zero, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t s);
 // Pair slots per chunk of the duplicate kernels (one workgroup round).
 constexpr int kChunkSlots = 1024;

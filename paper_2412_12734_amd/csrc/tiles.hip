@@ -139,6 +139,11 @@ scan_finalize_kernel(const uint32_t* __restrict__ count, const uint32_t* __restr
   unsigned long long sum = 0;
 #pragma unroll
   for (int k = 0; k < kScanRounds; ++k) {
+    if (k * kScanThreads >= VP) {  // (uniform)
+      incl[k] = 0u;
+      if (lane == 63) s_tot[k * kWaves + w] = 0u;
+      continue;
+    }
     sum += x[k];
     uint32_t v = x[k];
 #pragma unroll

@@ -26,12 +26,14 @@ def test_lists_at_the_edges_of_a_pass(gb, N, P):  # noqa: F811
     check_grads(gb, scene, view, opts, (0, 0, 37, 29), seed=P)
 
 
-@pytest.mark.parametrize("N", [4, 8, 16])
-def test_batches_of_a_call_with_many_tiles(gb, N):  # noqa: F811
-    # 41 x 37 tiles: more than run at once with the larger batches, so that smaller ones are taken
+@pytest.mark.parametrize("N", [2, 4, 8, 16])
+@pytest.mark.parametrize("size", [(272, 272), (400, 400), (480, 480), (656, 592)])
+def test_batches_by_the_number_of_tiles(gb, N, size):  # noqa: F811
+    # 289, 625, 900 and 1517 tiles: how many run at once decides the batch sizes
     scene = sg.make_scene(17, 150, -0.1, 0.1, 0.002, 0.1, N, op_lo=0.02, op_hi=0.2)
-    view = sg.look_at_view((0.05, 0.02, -2.0), 656, 592)
-    check_grads(gb, scene, view, O.Options(), (304, 276, 48, 40), seed=N)
+    view = sg.look_at_view((0.05, 0.02, -2.0), *size)
+    crop = (size[0] // 2 - 24, size[1] // 2 - 20, 48, 40)
+    check_grads(gb, scene, view, O.Options(), crop, seed=N)
 
 
 @pytest.mark.parametrize("layout,sides", [(8, (1, 2, 3, 8)), (16, (1, 2, 5, 16))])
