@@ -669,7 +669,7 @@ hipError_t launch_np(const Plan& pl, const gb_splats& sp, const BlendParams& bp,
                      const PairList& rest, const uint32_t* open_bits, const float* T_final,
                      const float* d_rgb, float* d_rec, float* d_tex, hipStream_t s) {
   const dim3 grid((unsigned)(bp.tile_order ? (int64_t)bp.total_tiles
-                                           : 8 * (int64_t)bp.tiles_per_xcd));
+                                           : tile_blocks(bp.total_tiles)));
   const dim3 block((unsigned)(pl.tile_w * pl.tile_h));
 #define GBB_BWD_B(BB)                                                                          \
   case BB:                                                                                     \

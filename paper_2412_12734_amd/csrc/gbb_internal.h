@@ -100,7 +100,7 @@ struct Plan {
   int32_t tile_bits;
   bool split;            // depth-prefix split enabled
   bool rest;             // a rest pass can have pairs: split, and more pair slots than the prefix's
-  bool ordered;          // blend workgroups take tiles in work order (else fixed XCD bands)
+  bool ordered;          // blend workgroups take tiles in work order (else a fixed order)
   int64_t prefix_cap;    // pair slots of the prefix pass (0 without the split)
   int64_t nb_vp;      // radix blocks over V*P records
   int64_t nb_pairs;   // radix blocks over the pair capacity
@@ -240,11 +240,11 @@ hipError_t launch_duplicate_rest(const uint32_t* order, const uint32_t* count_re
 hipError_t launch_ranges(const uint32_t* pair_keys, const uint32_t* d_n, int64_t n_cap,
                          uint32_t* ranges, hipStream_t s);
 // Work order of the tiles: order[0..n_tiles) is a permutation of the tiles by decreasing
-// cost work[t]. Costs are compared in buckets (exact below 16, then 1/16 of the cost wide);
+// cost work[t], or with ranges != null by decreasing length of the tile's list. Costs are compared in buckets (exact below 16, then 1/16 of the cost wide);
 // the order inside a bucket is unspecified. One workgroup; n_tiles <= kMaxOrderedTiles.
 constexpr int64_t kMaxOrderedTiles = (int64_t)1 << 20;
-hipError_t launch_order_tiles(const uint32_t* work, int64_t n_tiles, uint32_t* order,
-                              hipStream_t s);
+hipError_t launch_order_tiles(const uint32_t* work, const uint32_t* ranges, int64_t n_tiles,
+                              uint32_t* order, hipStream_t s);
 // Forward blend of one pass (mode in split.mode). REST launches the open-tile kernel.
 // tile_work (nullable): per tile, the span of pairs (first pair to one past the last pair any
 // pixel blended) is written by the first pass and added to by the rest pass. zero (nullable):
@@ -253,7 +253,7 @@ hipError_t launch_blend_fwd(const Plan& pl, const gb_splats& sp, const gb_option
                             const ViewDev* views, int n_views, const SplatRec* rec,
                             const uint32_t* pair_vals, const uint32_t* ranges, float* rgb,
                             float* T_final, uint32_t* n_last, const SplitState& split,
-                            uint32_t* tile_work, const float4* spec, unsigned long long* stats,
+                            uint32_t* tile_work, const uint32_t* tile_order, const float4* spec, unsigned long long* stats,
                             float* zero, int64_t zero_n, float* zero2, int64_t zero2_n,
                             hipStream_t s);
 // Backward blend over the prefix (or only) pass's pairs `first`; with open_bits != null the

@@ -617,7 +617,8 @@ __device__ __forceinline__ uint32_t cost_bucket(uint32_t c) {
 }
 
 __global__ void __launch_bounds__(kOrderThreads)
-order_tiles_kernel(const uint32_t* __restrict__ work, int n, uint32_t* __restrict__ order) {
+order_tiles_kernel(const uint32_t* __restrict__ work, const uint32_t* __restrict__ ranges, int n,
+                   uint32_t* __restrict__ order) {
   __shared__ uint32_t s_next[kOrderBuckets];
   __shared__ uint32_t s_wave[kOrderBuckets / 64];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -627,7 +628,7 @@ order_tiles_kernel(const uint32_t* __restrict__ work, int n, uint32_t* __restric
 #pragma unroll
     for (int k = 0; k < kOrderUnroll; ++k) {
       const int t = t0 + k * kOrderThreads;
-      c[k] = t < n ? work[t] : 0u;
+      c[k] = t >= n ? 0u : ranges ? ranges[2 * t + 1] - ranges[2 * t] : work[t];
     }
 #pragma unroll
     for (int k = 0; k < kOrderUnroll; ++k)
@@ -675,11 +676,12 @@ order_tiles_kernel(const uint32_t* __restrict__ work, int n, uint32_t* __restric
 
 }  // namespace
 
-hipError_t launch_order_tiles(const uint32_t* work, int64_t n_tiles, uint32_t* order,
-                              hipStream_t s) {
-  if (n_tiles < 1 || n_tiles > kMaxOrderedTiles || !work || !order) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(order_tiles_kernel, dim3(1), dim3(kOrderThreads), 0, s, work, (int)n_tiles,
-                     order);
+hipError_t launch_order_tiles(const uint32_t* work, const uint32_t* ranges, int64_t n_tiles,
+                              uint32_t* order, hipStream_t s) {
+  if (n_tiles < 1 || n_tiles > kMaxOrderedTiles || (!work && !ranges) || !order)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(order_tiles_kernel, dim3(1), dim3(kOrderThreads), 0, s, work, ranges,
+                     (int)n_tiles, order);
   return hipGetLastError();
 }
 

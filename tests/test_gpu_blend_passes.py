@@ -8,7 +8,7 @@ import torch
 
 import scenegen as sg
 from oracle import gb_oracle as O
-from test_gpu_parity import check_grads, gb, run_gpu  # noqa: F401
+from test_gpu_parity import check_grads, gb, gpu_opts, run_gpu  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -34,6 +34,24 @@ def test_batches_by_the_number_of_tiles(gb, N, size):  # noqa: F811
     view = sg.look_at_view((0.05, 0.02, -2.0), *size)
     crop = (size[0] // 2 - 24, size[1] // 2 - 20, 48, 40)
     check_grads(gb, scene, view, O.Options(), crop, seed=N)
+
+
+@pytest.mark.parametrize("size", [(448, 432), (448, 449), (1139, 1145), (1152, 1137)])
+def test_forward_tile_order_changes_no_pixel(gb, size):  # noqa: F811
+    # 756, 812, 5184 and 5112 tiles: on both sides of the numbers that are walked longest list first
+    scene = sg.make_scene(23, 400, -0.6, 0.6, 0.002, 0.2, 4, op_lo=0.05, op_hi=0.6)
+    views = [sg.look_at_view((0.05, 0.02, -2.0), *size)]
+    out = []
+    for order in (1, -1):
+        o = gpu_opts(O.Options())
+        o.tile_order = order
+        sp = gb.Splats.from_numpy(scene)
+        rast = gb.Rasterizer(views, o)
+        rast.plan(sp)
+        out.append(rast.forward(sp))
+    (rgb0, T0), (rgb1, T1) = out
+    assert float(T0.min()) < 0.5
+    assert torch.equal(rgb0, rgb1) and torch.equal(T0, T1)
 
 
 @pytest.mark.parametrize("layout,sides", [(8, (1, 2, 3, 8)), (16, (1, 2, 5, 16))])
