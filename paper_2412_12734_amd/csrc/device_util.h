@@ -88,10 +88,6 @@ __device__ __forceinline__ f2 f2_div(f2 a, f2 b) {
 // compared that again (two vector instructions per vote in the blend loops).
 __device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
-__device__ __forceinline__ uint32_t lane_id() {
-  return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-}
-
 __device__ __forceinline__ uint32_t popc64(uint64_t m) { return (uint32_t)__popcll(m); }
 
 // Number of set bits of m below this lane.
