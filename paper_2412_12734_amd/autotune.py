@@ -31,9 +31,9 @@ KNOBS: Dict[str, List] = {
 
 
 def resolve_defaults(opts, N: int):
-    """The options with the library's defaults written out (batch 0 -> 8, 16, 32 or 64,
-    batch_bwd 0 -> 8 or 32, prefix budget 0 -> 1024 pairs per tile, tile order 0 -> 1), so that
-    search results are explicit."""
+    """The options with explicit values where 0 leaves the choice to the library (batch 8, 16, 32
+    or 64, batch_bwd 8 or 32: its choices on many tiles; prefix budget 1024 pairs per tile, tile
+    order 1), so that search results are explicit."""
     return dataclasses.replace(
         opts,
         batch=opts.batch or (4 if N >= 16 else 16 if N >= 8 else 32 if N >= 4 else 64),

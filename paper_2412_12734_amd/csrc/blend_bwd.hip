@@ -23,11 +23,11 @@
 // the CU's LDS (12 lanes 6.5, and 3 per lane on one address), where ds_add_f32 takes 3 cycles for
 // every lane whatever the addresses (12 lanes 38, 64 lanes 193), which had made the LDS the
 // limit. What bounds the kernel now is VALU issue where tiles fill the chip (1M splats at 1080p:
-// 88 % of the cycles; 0.65 G wave instructions, about 228 per wave step), and the latency of a
+// every cycle; 0.65 G wave instructions, about 225 per wave step), and the latency of a
 // wave's step where a few tiles hold the work. At 1M splats and 1080p 1.35 -> 1.02 ms, 3M splats on
 // four 1080p views 14.5 -> 10.9, 16 uneven views with 4 x 4 grids 8.28 -> 6.2, 16 x 16 grids 2.33 ->
-// 1.66, sides {2, 4, 8} 1.53 -> 1.13, 100k splats at 800 x 800 0.73 -> 0.53, 372k small splats on
-// 462 tiles 1.10 -> 1.11.
+// 1.63, sides {2, 4, 8} 1.53 -> 1.13, 100k splats at 800 x 800 0.73 -> 0.53, 235k splats on 112 tiles
+// 1.46 -> 1.03, 372k small splats on 462 tiles 1.10 -> 1.09.
 #include "blend_common.h"
 
 namespace gbb {

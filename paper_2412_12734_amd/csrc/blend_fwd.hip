@@ -8,8 +8,9 @@
 // round trips) where they do not. Staging only the splats that reach a block and their geometry by
 // all waves at once, the four corner texels in flight together, and the open pixels as a scalar
 // lane mask (a flag per lane cost copies of the pixel's state around every branch): at 1M splats
-// and 1080p 0.509 -> 0.382 ms, 16 x 16 grids 1.24 -> 0.80, sides {2, 4, 8} 0.745 -> 0.490, 3M splats
-// on four 1080p views 4.91 -> 3.85, 350k small splats on 135 tiles 0.363 -> 0.312.
+// and 1080p 0.509 -> 0.370 ms, 16 x 16 grids 1.24 -> 0.76, sides {2, 4, 8} 0.745 -> 0.468, 3M splats
+// on four 1080p views 4.91 -> 3.51, 350k small splats on 135 tiles 0.363 -> 0.229 (with the tile
+// order and the batches of later lines of this file and of blend_common.h).
 //
 // Per pixel and splat: (u, v) from the centre-relative homography, G = exp(-min(q_uv, q_lp)),
 // alpha = min(alpha_max, o G); alpha < alpha_min is skipped; if T (1 - alpha) < t_min the
