@@ -146,7 +146,8 @@ __device__ __forceinline__ void pixel_step(const float4* tex, const PixelEval& e
   const float dalpha = (act && e.oG <= p.alpha_max) ? da : 0.f;
   // the falloff's adjoint goes to (u, v) or to the low-pass offset, selected without a branch
   const float dq = -e.oG * dalpha;
-  const float dq_uv = e.uv_branch ? dq : 0.f, dq_lp = e.uv_branch ? 0.f : dq;
+  const bool from_uv = __builtin_amdgcn_inverse_ballot_w64(e.uv_branch);
+  const float dq_uv = from_uv ? dq : 0.f, dq_lp = from_uv ? 0.f : dq;
   {
 #pragma clang fp contract(off)
     du = __builtin_fmaf(u, dq_uv, du);
@@ -479,7 +480,7 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
           const float inv = act ? e.inv : 0.f, u = act ? e.u : 0.f, v = act ? e.v : 0.f;
           po.in_u = ballot(fabsf(u) < p.sigma);  // (-sigma, sigma): one compare with |u|
           po.in_v = ballot(fabsf(v) < p.sigma);
-          const uint64_t low_pass = pend_px & ~ballot(e.uv_branch);
+          const uint64_t low_pass = pend_px & ~e.uv_branch;
           // Sums of the per-splat scalars; the owner lanes of a total add it to the splat's slot.
           if (N > 1 && (low_pass & (po.in_u | po.in_v)) != 0) {
             pixel_step<N, MIXED, true>(tex, e, inv, u, v, act, ps, p, po, gc);

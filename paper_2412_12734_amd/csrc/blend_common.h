@@ -406,12 +406,14 @@ struct PixelEval {
   float G;            // exp(-q)
   float oG;           // opacity times G
   float alpha;        // min(alpha_max, oG)
-  bool uv_branch;     // q came from the uv Gaussian (else from the screen low-pass)
+  uint64_t uv_branch;  // lanes whose q came from the uv Gaussian (else from the screen low-pass)
 };
 
 // (lx, ly): pixel centre minus the wave block's centre; (tx, ty): minus the tile's centre.
 // Both falloff exponents are compared and scaled as 2 q (doubling is exact, so the result is
-// that of q); the minimum is one instruction (fminf first canonicalises alpha_max).
+// that of q); each minimum is one instruction (fminf first canonicalises its operands), and
+// the branch is a lane mask that only the backward asks for: 16 uneven views of 1M splats 12.52 -> 12.44
+// ms, 3M splats on four 1080p views 16.67 -> 16.58.
 __device__ __forceinline__ PixelEval eval_splat(const StagedGeo& s, float lx, float ly, float tx,
                                                 float ty, const BlendParams& p) {
   PixelEval e;
@@ -425,8 +427,9 @@ __device__ __forceinline__ PixelEval eval_splat(const StagedGeo& s, float lx, fl
   e.v = r1 * e.inv;
   const float q_uv = e.u * e.u + e.v * e.v;
   const float q_lp = (e.dx * e.dx + e.dy * e.dy) * p.lp_scale2;
-  e.uv_branch = q_uv <= q_lp;
-  const float q = e.uv_branch ? q_uv : q_lp;
+  e.uv_branch = ballot(q_uv <= q_lp);
+  float q;  // the smaller one; q_lp where q_uv is not a number
+  __asm__("v_min_f32 %0, %1, %2" : "=v"(q) : "v"(q_uv), "v"(q_lp));
   e.G = __builtin_amdgcn_exp2f(q * (-0.5f * 1.4426950408889634f));
   e.oG = s.g0.w * e.G;
   __asm__("v_min_f32 %0, %1, %2" : "=v"(e.alpha) : "s"(p.alpha_max), "v"(e.oG));
