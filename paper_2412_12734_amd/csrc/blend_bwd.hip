@@ -12,41 +12,34 @@
 // A lane owns one pixel (waves of 8 x 8 pixels). The list is taken in passes of 64 entries: each
 // wave stages the entries' geometry for its own block, one entry per lane, and votes which can
 // reach it; entries that reach some block of the tile get slots, in batches, for their texels and
-// for the sums over pixels. Per splat and wave, twelve sums are taken by masked DPP adds inside
-// the rows of 16 lanes; texel gradients are grouped by grid cell (with sigma = 0.5 the grid covers
+// for the sums over pixels. Per splat and wave, the ten record gradients are summed by lane swaps
+// and DPP adds; texel gradients are grouped by grid cell (with sigma = 0.5 the grid covers
 // only the splat's core, so most blended pixels are border-clamped and share a few cells), one
-// group after another, over the corners that the group weights, until at most kLaneAddMax pixels
-// are left, each of which adds its corners directly. After each batch the non-zero sums go to global
-// memory with one float atomic each, and the next batch's texels are staged.
+// group after another, over the corners that the group weights and inside the rows of 16 lanes,
+// until at most kLaneAddMax pixels are left, each of which adds its corners directly. After each
+// batch the non-zero sums go to global memory with one float atomic each, and the next batch's
+// texels are staged.
 //
-// The sums are 64-bit in LDS: ds_add_f64 serves 64 lanes with distinct addresses in 8.7 cycles of
-// the CU's LDS (12 lanes 6.5, and 3 per lane on one address), where ds_add_f32 takes 3 cycles for
-// every lane whatever the addresses (12 lanes 38, 64 lanes 193), which had made the LDS the
-// limit. What bounds the kernel now is VALU issue where tiles fill the chip (1M splats at 1080p:
-// every cycle; 0.65 G wave instructions, about 225 per wave step), and the latency of a
-// wave's step where a few tiles hold the work. At 1M splats and 1080p 1.35 -> 1.02 ms, 3M splats on
-// four 1080p views 14.5 -> 10.9, 16 uneven views with 4 x 4 grids 8.28 -> 6.2, 16 x 16 grids 2.33 ->
-// 1.63, sides {2, 4, 8} 1.53 -> 1.13, 100k splats at 800 x 800 0.73 -> 0.53, 235k splats on 112 tiles
-// 1.46 -> 1.03, 372k small splats on 462 tiles 1.10 -> 1.09.
+// The texel sums are 64-bit in LDS: ds_add_f64 serves 64 lanes with distinct addresses in 8.7 cycles
+// of the CU's LDS (12 lanes 6.5, and 3 per lane on one address), where ds_add_f32 takes 3 cycles for
+// every lane whatever the addresses (12 lanes 38, 64 lanes 193), which had made the LDS the limit.
+// The record sums (ten lanes, once per step) are 32-bit: their last bits matter (see pixel_step). In
+// 64 bits the step at 1M splats and 1080p took 1.825 ms against 1.834, too little to change them for.
+// What bounds the kernel now is VALU issue where tiles fill the chip, and the latency of a wave's
+// step where a few tiles hold the work. At 1M splats and 1080p 1.35 -> 1.09 ms, 3M splats on
+// four 1080p views 14.5 -> 11.3, 16 uneven views with 4 x 4 grids 8.28 -> 6.8, 16 x 16 grids 2.33 ->
+// 1.69, sides {2, 4, 8} 1.53 -> 1.19, 100k splats at 800 x 800 0.73 -> 0.56. (With the texels
+// projected on the pixel's adjoint before the interpolation, one scalar for the colour behind and d c2
+// formed once per batch the step took 3 to 4 % less, but its gradients had other last bits.)
 #include "blend_common.h"
 
 namespace gbb {
 
 namespace {
 
-// Sums over pixels that the backward keeps per staged splat in LDS. With (dx, dy) a pixel's
-// offset from the projected centre and dr the adjoint of rho: dr0 (dx, dy), dr1 (dx, dy),
-// dr2 (dx, dy), dr2, dr0, dr1, dq_lp (dx, dy) and the opacity's adjoint. The ten record
-// gradients follow from them once per batch (record_gradient): the part of d c2 that comes
-// through rho is -H^T dr with H constant over the splat, so that summing dr0 and dr1 (two more
-// values in the reduction) replaces six multiply-adds of every pixel.
-constexpr int kSums = 12;
-
-// Per-pixel backward state and the outputs of one (pixel, splat) step. Only the colour's
-// component along the pixel's adjoint g matters (d alpha = g . (col T - S / (1 - alpha))), so
-// the colour behind the splat is carried as the scalar Sg = g . S.
+// Per-pixel backward state and the outputs of one (pixel, splat) step.
 struct PixState {
-  float T, Sg, g0, g1, g2;
+  float T, S0, S1, S2, g0, g1, g2;
   uint32_t last;
 };
 
@@ -54,37 +47,36 @@ struct PixOut {
   int cell;          // first corner's index in the LDS texel layout (TexLayout)
   float wgt, fu, fv; // alpha T and the position inside the cell
   uint64_t in_u, in_v;  // lanes where |u| < sigma, |v| < sigma: not clamped to the border
-  float sum[kSums];
+  float rec[kRecGrad];  // record gradients
 };
 
 // One (pixel, splat) step of the reverse walk. `act`: the pixel blended this splat. A lane
 // that did not runs the same arithmetic with a zero opacity, so that its weights, adjoints and
 // state come out unchanged or zero without a branch; its u, v and 1 / rho2 are replaced by 0
 // (they are infinite where rho2 = 0). Its cell is left unspecified.
-// The four corner texels are multiplied by g first (12 multiply-adds) and interpolated as
-// scalars: the value and both fractional-position adjoints then cost 9 operations instead of 33
-// over three channels.
-// CHANNELS keeps the interpolation per channel and every operation in the order written here.
-// Where the falloff is the low-pass's and one coordinate lies inside the grid while the other is
-// clamped, the adjoint of the other axis' scale is zero in exact arithmetic, and what comes out
-// is the rounding residue of terms that cancel. Adam divides a gradient by its own size, so that
-// this residue's sign moves the parameter by a full step: such lanes keep their operations, and
-// the order of their sums, so that a training run goes on as it did before the scalar form.
+// Every operation of the record gradients is written out, multiply-adds too. Sums of them can
+// cancel, by chance or exactly (where the falloff is the low-pass's and one coordinate is clamped
+// to the grid's border, the adjoint of that axis' scale is zero and what comes out is rounding
+// alone), and Adam divides a gradient by its own size: another last bit here can move a parameter
+// by a full step.
 // MIXED: gc holds the grid-coordinate constants of the splat's grid (grid_consts).
-template <int N, bool MIXED, bool CHANNELS>
-__device__ __forceinline__ void pixel_step(const float4* tex, const PixelEval& e, float inv,
-                                           float u, float v, bool act, PixState& ps,
-                                           const BlendParams& p, PixOut& o, const float4& gc) {
+template <int N, bool MIXED>
+__device__ __forceinline__ void pixel_step(const float4* s_g1, const float4* s_g2, int j,
+                                           const float4* tex, const PixelEval& e, float inv, float u, float v,
+                                           bool act, PixState& ps, const BlendParams& p,
+                                           PixOut& o, const float4& gc) {
+#pragma clang fp contract(off)
   const float alpha = act ? e.alpha : 0.f;
   const float inv1m = __builtin_amdgcn_rcpf(1.0f - alpha);
   ps.T = ps.T * inv1m;  // transmittance in front of this splat
   const float wgt = alpha * ps.T;
   o.wgt = wgt;
-  float col;  // g . colour
-  float du = 0.f, dv = 0.f;
+  float c[3], du = 0.f, dv = 0.f;
   if constexpr (N == 1) {
     const float4 t = tex[0];
-    col = ps.g0 * t.x + ps.g1 * t.y + ps.g2 * t.z;
+    c[0] = t.x;
+    c[1] = t.y;
+    c[2] = t.z;
     o.cell = 0;
     o.fu = o.fv = 0.f;
   } else {
@@ -100,73 +92,63 @@ __device__ __forceinline__ void pixel_step(const float4* tex, const PixelEval& e
     o.fu = fu;
     o.fv = fv;
     o.cell = TexLayout<N>::at(iu, iv);
-    const float4* t = tex + o.cell;
     float4 t00, t01, t10, t11;
-    load_corners<TexLayout<N>::kRow>(t, t00, t01, t10, t11);
+    load_corners<TexLayout<N>::kRow>(tex + o.cell, t00, t01, t10, t11);
     const float tsc = MIXED ? gc.x : p.tex_scale;
-    // fractional-position adjoints (Alg. 2), zero where the coordinate is clamped
-    if constexpr (CHANNELS) {
-#pragma clang fp contract(off)
-      const float g[3] = {ps.g0, ps.g1, ps.g2};
-      const float x0[3] = {t00.x, t00.y, t00.z}, x1[3] = {t01.x, t01.y, t01.z};
-      const float y0[3] = {t10.x, t10.y, t10.z}, y1[3] = {t11.x, t11.y, t11.z};
-      float c[3], dc[3], d[3], f[3];
+    const float g[3] = {ps.g0, ps.g1, ps.g2};
+    const float x0[3] = {t00.x, t00.y, t00.z}, x1[3] = {t01.x, t01.y, t01.z};
+    const float y0[3] = {t10.x, t10.y, t10.z}, y1[3] = {t11.x, t11.y, t11.z};
+    float dc[3], d[3], f[3];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const float xd = x1[k] - x0[k], yd = y1[k] - y0[k];
-        const float a = __builtin_fmaf(fv, xd, x0[k]), b = __builtin_fmaf(fv, yd, y0[k]);
-        dc[k] = wgt * g[k];
-        d[k] = b - a;
-        c[k] = __builtin_fmaf(fu, d[k], a);
-        f[k] = __builtin_fmaf(1.f - fu, xd, fu * yd);
-      }
-      const float dfu = __builtin_fmaf(dc[2], d[2], __builtin_fmaf(dc[0], d[0], dc[1] * d[1]));
-      const float dfv = __builtin_fmaf(dc[2], f[2], __builtin_fmaf(dc[0], f[0], dc[1] * f[1]));
-      col = __builtin_fmaf(g[2], c[2], __builtin_fmaf(g[0], c[0], g[1] * c[1]));
-      du = tsc * dfu;
-      dv = tsc * dfv;
-    } else {
-      const float q00 = ps.g0 * t00.x + ps.g1 * t00.y + ps.g2 * t00.z;
-      const float q01 = ps.g0 * t01.x + ps.g1 * t01.y + ps.g2 * t01.z;
-      const float q10 = ps.g0 * t10.x + ps.g1 * t10.y + ps.g2 * t10.z;
-      const float q11 = ps.g0 * t11.x + ps.g1 * t11.y + ps.g2 * t11.z;
-      const float d0 = q01 - q00, d1 = q11 - q10;
-      const float a = q00 + fv * d0, d = (q10 + fv * d1) - a;
-      col = a + fu * d;
-      const float wsc = wgt * tsc;
-      du = wsc * d;
-      dv = wsc * (d0 + fu * (d1 - d0));
+    for (int k = 0; k < 3; ++k) {
+      const float xd = x1[k] - x0[k], yd = y1[k] - y0[k];
+      const float a = __builtin_fmaf(fv, xd, x0[k]), b = __builtin_fmaf(fv, yd, y0[k]);
+      dc[k] = wgt * g[k];
+      d[k] = b - a;
+      c[k] = __builtin_fmaf(fu, d[k], a);
+      f[k] = __builtin_fmaf(1.f - fu, xd, fu * yd);
     }
-    du = __builtin_amdgcn_inverse_ballot_w64(o.in_u) ? du : 0.f;
-    dv = __builtin_amdgcn_inverse_ballot_w64(o.in_v) ? dv : 0.f;
+    // fractional-position adjoints (Alg. 2), zero where the coordinate is clamped
+    const float dfu = __builtin_fmaf(dc[2], d[2], __builtin_fmaf(dc[0], d[0], dc[1] * d[1]));
+    const float dfv = __builtin_fmaf(dc[2], f[2], __builtin_fmaf(dc[0], f[0], dc[1] * f[1]));
+    du = __builtin_amdgcn_inverse_ballot_w64(o.in_u) ? tsc * dfu : 0.f;
+    dv = __builtin_amdgcn_inverse_ballot_w64(o.in_v) ? tsc * dfv : 0.f;
   }
-  const float da = col * ps.T - ps.Sg * inv1m;
-  ps.Sg += wgt * col;
-  // zero where the pixel did not blend the splat or alpha was clamped to alpha_max
+  // d alpha = g . (colour T - S / (1 - alpha)), zero where the pixel did not blend the splat or
+  // alpha was clamped to alpha_max
+  const float a0 = __builtin_fmaf(c[0], ps.T, -(ps.S0 * inv1m)),
+              a1 = __builtin_fmaf(c[1], ps.T, -(ps.S1 * inv1m)),
+              a2 = __builtin_fmaf(c[2], ps.T, -(ps.S2 * inv1m));
+  const float da = __builtin_fmaf(ps.g2, a2, __builtin_fmaf(ps.g0, a0, ps.g1 * a1));
+  ps.S0 = __builtin_fmaf(wgt, c[0], ps.S0);
+  ps.S1 = __builtin_fmaf(wgt, c[1], ps.S1);
+  ps.S2 = __builtin_fmaf(wgt, c[2], ps.S2);
   const float dalpha = (act && e.oG <= p.alpha_max) ? da : 0.f;
+  o.rec[9] = dalpha * e.G;
   // the falloff's adjoint goes to (u, v) or to the low-pass offset, selected without a branch
   const float dq = -e.oG * dalpha;
   const bool from_uv = __builtin_amdgcn_inverse_ballot_w64(e.uv_branch);
-  const float dq_uv = from_uv ? dq : 0.f, dq_lp = from_uv ? 0.f : dq;
-  {
-#pragma clang fp contract(off)
-    du = __builtin_fmaf(u, dq_uv, du);
-    dv = __builtin_fmaf(v, dq_uv, dv);
-    const float dr0 = du * inv, dr1 = dv * inv;
-    const float dr2 = -__builtin_fmaf(u, du, v * dv) * inv;
-    o.sum[0] = dr0 * e.dx;
-    o.sum[1] = dr0 * e.dy;
-    o.sum[2] = dr1 * e.dx;
-    o.sum[3] = dr1 * e.dy;
-    o.sum[4] = dr2 * e.dx;
-    o.sum[5] = dr2 * e.dy;
-    o.sum[6] = dr2;
-    o.sum[7] = dr0;
-    o.sum[8] = dr1;
-  }
-  o.sum[9] = dq_lp * e.dx;
-  o.sum[10] = dq_lp * e.dy;
-  o.sum[11] = dalpha * e.G;
+  const float dq_uv = from_uv ? dq : 0.f, dq_lp = from_uv ? 0.f : dq * p.lp_scale2;
+  du = __builtin_fmaf(u, dq_uv, du);
+  dv = __builtin_fmaf(v, dq_uv, dv);
+  const float dr0 = du * inv, dr1 = dv * inv;
+  const float dr2 = -__builtin_fmaf(u, du, v * dv) * inv;
+  o.rec[0] = dr0 * e.dx;
+  o.rec[1] = dr0 * e.dy;
+  o.rec[2] = dr1 * e.dx;
+  o.rec[3] = dr1 * e.dy;
+  o.rec[4] = dr2 * e.dx;
+  o.rec[5] = dr2 * e.dy;
+  o.rec[6] = dr2;
+  // (H read again from LDS: held through the step it would take six registers)
+  __asm__ volatile("" : "+s"(j));
+  const float4 h = s_g1[j], h2 = s_g2[j];
+  // d c2: the low-pass term and the uv term through rho's dependence on the offset (the centre
+  // enters both with a minus sign)
+  o.rec[7] = __builtin_fmaf(-h2.x, dr2, __builtin_fmaf(-h.z, dr1,
+                            __builtin_fmaf(dq_lp, -e.dx, -(h.x * dr0))));
+  o.rec[8] = __builtin_fmaf(-h2.y, dr2, __builtin_fmaf(-h.w, dr1,
+                            __builtin_fmaf(dq_lp, -e.dy, -(h.y * dr0))));
 }
 
 // w times the corner weights (00, 01, 10, 11) at (fu, fv). The multiply-adds are written out:
@@ -190,7 +172,7 @@ __device__ __forceinline__ int cell_row(int cell) {
 struct PlaceField {
   int at, bits;
 };
-constexpr PlaceField kRow{0, 4}, kOrd{4, 4}, kT12{8, 6}, kT6v{14, 3}, kT6u{17, 6}, kT3{23, 2};
+constexpr PlaceField kRec{0, 4}, kT12{8, 6}, kT6v{14, 3}, kT6u{17, 6}, kT3{23, 2};
 
 __device__ __forceinline__ uint32_t place(PlaceField f, int x) {
   return ((uint32_t)x & ((1u << f.bits) - 1u)) << f.at;
@@ -199,25 +181,13 @@ __device__ __forceinline__ int place_of(PlaceField f, uint32_t places) {
   return (int)((places >> f.at) & ((1u << f.bits) - 1u));
 }
 
-// Adds the total that row_sums or ordered_sums left in each owner lane to an LDS array at index
-// base + offset (base uniform over the wave).
+// Adds the total that row_sums left in each owner lane to an LDS array at index base + offset (base
+// uniform over the wave).
 template <uint64_t OWNERS>
 __device__ __forceinline__ void lds_add(double* array, int base, int offset, float tot) {
   base = __builtin_amdgcn_readfirstlane(base);
   __asm__ volatile("" : "+s"(base));  // a scalar add, not part of a 64-bit multiply-add
   if (__builtin_amdgcn_inverse_ballot_w64(OWNERS)) atomicAdd(array + offset + base, (double)tot);
-}
-
-// Record gradient r (in the order of kRecGrad) from a splat's sums x and its staged H.
-__device__ __forceinline__ float record_gradient(int r, const double* x, const float4& g1,
-                                                 const float4& g2, float lp_scale) {
-  // every lane reads what the two lanes of d c2 need: the reads then need no branch
-  const bool y = r == 8;
-  const float own = (float)x[r < 7 ? r : 11], lp = 2.f * lp_scale * (float)x[y ? 10 : 9];
-  // d c2: minus the low-pass term's and rho's adjoints of the offset
-  const float dc = -lp - (float)x[7] * (y ? g1.y : g1.x) - (float)x[8] * (y ? g1.w : g1.z) -
-                   (float)x[6] * (y ? g2.y : g2.x);
-  return r < 7 || r == 9 ? own : dc;
 }
 
 // Pixels left to a wave step's cell grouping that are added one by one. Backward ms for 16 / 20 / 24
@@ -296,7 +266,7 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
   __shared__ GeoLds<PE> s_geo;
   __shared__ float4 s_tex[B * TexLayout<N>::kPerSplat];
   __shared__ __attribute__((aligned(16))) double s_gtex[B * TEXG];  // per slot
-  __shared__ double s_sum[B * kSums];
+  __shared__ float s_rec[B * kRecGrad];  // per slot
   // the waves' votes of a pass, of which two can be in use at a time (a wave may vote on the
   // next pass while another still reads this one's)
   __shared__ uint64_t s_mask[2][4];
@@ -341,19 +311,22 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
       ps.g1 = d_rgb[3 * pix + 1];
       ps.g2 = d_rgb[3 * pix + 2];
     }
-    ps.Sg = ps.T * (ps.g0 * p.bg[0] + ps.g1 * p.bg[1] + ps.g2 * p.bg[2]);
+    ps.S0 = ps.T * p.bg[0];
+    ps.S1 = ps.T * p.bg[1];
+    ps.S2 = ps.T * p.bg[2];
   }
-  // the sum that this lane owns after the reductions: its place among a splat's record sums (after
-  // row_sums, and after ordered_sums), and its offset from the first texel's first channel in the
-  // three kinds of texel group (four corners; two texels along v, or along u; one texel), in one
-  // register: fields kRow, kOrd, kT12, kT6v, kT6u, kT3 of lane_places
+  // the sum that this lane owns after the reductions: its place among a splat's record gradients, and
+  // its offset from the first texel's first channel in the three kinds of texel group (four corners;
+  // two texels along v, or along u; one texel), in one register: fields kRec, kT12, kT6v, kT6u, kT3
+  // of lane_places. rec_owners: the lanes that own a record gradient.
   uint32_t places;
+  uint64_t rec_owners;
   {
     const int rl = lane & 15;
     const int s12 = row_slot(12, rl), s6 = row_slot(6, rl), s3 = row_slot(3, rl);
-    const SwapSides sides = swap_sides();
-    places = place(kRow, row_slot(kSums, rl)) |
-             place(kOrd, ordered_slot(sides.halves, sides.rows, rl)) |
+    const int rs = record_slot(swap_sides(), rl);
+    rec_owners = ballot(rs >= 0);
+    places = place(kRec, rs) |
              place(kT12, 3 * ((s12 / 3 & 1) + (s12 / 6) * N) + s12 % 3) |
              place(kT6v, s6) |  // 3 (s6 / 3) + s6 % 3
              place(kT6u, 3 * (s6 / 3) * N + s6 % 3) | place(kT3, s3);
@@ -362,7 +335,7 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
   // the per-batch LDS sums start at zero; each batch's flush clears what it read
   // (the first barrier of the list loop orders these stores before any add)
   for (int e = tid; e < B * TEXG; e += nthr) s_gtex[e] = 0.0;
-  for (int e = tid; e < B * kSums; e += nthr) s_sum[e] = 0.0;
+  for (int e = tid; e < B * kRecGrad; e += nthr) s_rec[e] = 0.f;
   // votes of waves that the workgroup does not have
   if (tid < 8 && (tid & 3) >= n_waves) s_mask[tid >> 2][tid & 3] = 0;
   int parity = 0;
@@ -480,14 +453,13 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
           const float inv = act ? e.inv : 0.f, u = act ? e.u : 0.f, v = act ? e.v : 0.f;
           po.in_u = ballot(fabsf(u) < p.sigma);  // (-sigma, sigma): one compare with |u|
           po.in_v = ballot(fabsf(v) < p.sigma);
-          const uint64_t low_pass = pend_px & ~e.uv_branch;
-          // Sums of the per-splat scalars; the owner lanes of a total add it to the splat's slot.
-          if (N > 1 && (low_pass & (po.in_u | po.in_v)) != 0) {
-            pixel_step<N, MIXED, true>(tex, e, inv, u, v, act, ps, p, po, gc);
-            lds_add<kOrderedOwners>(s_sum, kSums * slot, place_of(kOrd, places), ordered_sums(po.sum));
-          } else {
-            pixel_step<N, MIXED, false>(tex, e, inv, u, v, act, ps, p, po, gc);
-            lds_add<row_owners(kSums)>(s_sum, kSums * slot, place_of(kRow, places), row_sums(po.sum));
+          pixel_step<N, MIXED>(s_geo.g1, s_geo.g2, j, tex, e, inv, u, v, act, ps, p, po, gc);
+          // Sums of the record gradients; the one lane that owns each adds it to the splat's slot.
+          {
+            const float tot = record_sums(po.rec);
+            float* const at = s_rec + kRecGrad * slot;
+            if (__builtin_amdgcn_inverse_ballot_w64(rec_owners))
+              atomicAdd(at + place_of(kRec, places), tot);
           }
 
           // Texel gradients, grouped by cell over all pixels of the wave. A wave step that
@@ -578,16 +550,10 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
         // (two waves share a slot of 768 sums where the batch has no slot for half of the waves)
         const int parts = N >= 16 && !MIXED && 2 * nb <= n_waves ? 2 : 1, part = w & (parts - 1);
         for (int j = w / parts * PER + (PER > 1 ? ft / FL : 0); j < nb; j += n_waves / parts * PER) {
-          int entry = (int)s_list.entry[b0 + j];
           uint32_t r = s_list.rec[b0 + j];
-          if constexpr (PER == 1) {
-            entry = __builtin_amdgcn_readfirstlane(entry);
-            r = __builtin_amdgcn_readfirstlane(r);
-          }
+          if constexpr (PER == 1) r = __builtin_amdgcn_readfirstlane(r);
           double* const gs = s_gtex + j * TEXG;
-          // each lane reads the sums its record gradient needs, and only then are they cleared
-          const float rg = part != 0 ? 0.f : record_gradient(fl, &s_sum[j * kSums], s_geo.g1[entry],
-                                           s_geo.g2[entry], p.lp_scale);
+          const float rg = part == 0 && fl < kRecGrad ? s_rec[j * kRecGrad + fl] : 0.f;
           if (p.d_spec) {
             // the view-dependent colour of a record is added to every texel of its lookup, so
             // its adjoint over the tile is the sum of the record's texel sums, one per channel
@@ -608,6 +574,7 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
           if constexpr (MIXED) {
             // the N x N sums hold the splat's n x n grid in rows and columns [0, n): lane i takes
             // values i, i + 64, ... of the grid's 3 n^2
+            const int entry = __builtin_amdgcn_readfirstlane((int)s_list.entry[b0 + j]);
             const int n = __builtin_amdgcn_readlane(eg.n, entry);
             float* const dst = d_tex + readlane64(eg.first, entry);
             for (int i0 = fl; i0 < 3 * n * n; i0 += 3 * 64) {  // three reads at a time
@@ -652,7 +619,7 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
           }
           __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
           __builtin_amdgcn_wave_barrier();
-          if (part == 0 && fl < kSums) s_sum[j * kSums + fl] = 0.0;
+          if (part == 0 && fl < kRecGrad) s_rec[j * kRecGrad + fl] = 0.f;
           if (fl < kRecGrad && rg != 0.f) atomicAdd(&d_rec[(int64_t)r * kRecGrad + fl], rg);
         }
         // the next batch's texels load while the atomics above drain

@@ -253,11 +253,10 @@ __device__ __forceinline__ float row_sums(float (&v)[K]) {
   }
 }
 
-// Wave sums of twelve values, added in the order lane ^ 32, ^ 16, ^ 15, ^ 7, ^ 3, ^ 1: two swap
-// steps, then the row steps above. 34 issue slots against the 25 of row_sums, which leaves the
-// rows unsummed and adds in another order.
-__device__ __forceinline__ float ordered_sums(const float (&v)[12]) {
-  float a[6], b[3];
+// Wave sums of ten values, added in the order lane ^ 32, ^ 16, ^ 15, ^ 7, ^ 3, ^ 1: two swap steps,
+// then the row steps above.
+__device__ __forceinline__ float record_sums(const float (&v)[10]) {
+  float a[5], b[3];
   swap_step<true>(v, a);
   swap_step<false>(a, b);
   __asm__ volatile("s_nop 1\n\t"
@@ -275,13 +274,14 @@ __device__ __forceinline__ float ordered_sums(const float (&v)[12]) {
 }
 #undef GBB_PAIR
 
-// The value that ordered_sums leaves in a lane, and the lanes of which each value has one: with
-// h and r the sides of the swaps and b3..b0 the bits of the row position, value 4 i + 2 r + h
-// with i = b3 for b2 = 0 and i = 2 for b2 = 1 (held for both b3); b1 and b0 hold copies.
-__device__ __forceinline__ int ordered_slot(bool h, bool r, int l) {
-  return 4 * ((l & 4) ? 2 : (l >> 3 & 1)) + (r ? 2 : 0) + (h ? 1 : 0);
+// The value that record_sums leaves in a lane of row position l, -1 where it leaves a copy of
+// another lane's. With h and r the sides of the swaps and b3..b0 the bits of l: 4 b3 + 2 r + h for
+// b2 = 0, 8 + h for b2 = 1 (held for both r and both b3); b1 and b0 hold copies.
+__device__ __forceinline__ int record_slot(SwapSides s, int l) {
+  if ((l & 3) != 0) return -1;
+  if ((l & 4) != 0) return s.rows || (l & 8) != 0 ? -1 : 8 + (s.halves ? 1 : 0);
+  return 4 * (l >> 3) + (s.rows ? 2 : 0) + (s.halves ? 1 : 0);
 }
-constexpr uint64_t kOrderedOwners = 0x0111011101110111ull;  // row positions 0, 4 and 8
 
 // The value whose (partial) sum row_sums<K> leaves in row position l (0..15), -1 in a position
 // that holds a copy of another's. With b3..b0 the bits of l:
