@@ -287,12 +287,13 @@ class Trainer:
             self.rast.plan(sp, int(self.rast.count_pairs(sp) * 1.5) + 4096)
             rgb, T = self.rast.forward(sp, rgb, T, zero_grads=zg)
         one = self.targets[batch[0]].view(-1, 3)[:n_px] if len(batch) == 1 else None
-        if (one is not None and one.dtype == torch.float32 and one.device == rgb.device
-                and one.is_contiguous() and one.data_ptr() % 16 == 0):
+        if (one is not None and one.shape[0] == n_px and one.dtype == torch.float32
+                and one.device == rgb.device and one.is_contiguous()
+                and one.data_ptr() % 16 == 0):
             target = one  # a single image is compared where it lies
         else:
             at = 0
-            for i in batch:  # device-to-device copies of the batch's target images
+            for i in batch:  # copies of the batch's target images (too few rows raise here)
                 hw = self.views[i].width * self.views[i].height
                 target[at:at + hw].copy_(self.targets[i].view(-1, 3)[:hw])
                 at += hw
