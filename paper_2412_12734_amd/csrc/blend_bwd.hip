@@ -366,34 +366,34 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
 
     // the record of the lane's entry of the pass that ends at `end`
     auto load_rec = [&](uint32_t end) {
-      const uint32_t at = (end - start > (uint32_t)PE ? end - (uint32_t)PE : start) + (uint32_t)lane;
-      return at < end ? pair_vals[at] : rec_base;
+      const int n = pass_size(start, end, PE);
+      return lane < n ? pair_vals[end - (uint32_t)n + (uint32_t)lane] : rec_base;
     };
     uint32_t my_rec = load_rec(tile_last);  // loaded a pass ahead
     for (uint32_t pend = tile_last; pend > start;) {
       // a pass: entries [pbase, pend) of the list, one per lane
-      const uint32_t pbase = pend - start > (uint32_t)PE ? pend - (uint32_t)PE : start;
+      const int n = pass_size(start, pend, PE);
+      const uint32_t pbase = pend - (uint32_t)n;
       uint64_t mine = 0;
       EntryGrid eg{1, 0.f, 0};
       // wave 0 also stores what the blocks share of a splat's geometry
       if (w == 0 || pbase < wave_last) {
         bool may = false;
         const int e = fresh_tid() & 63;
-        const uint32_t idx = pbase + (uint32_t)e;
-        if (idx < pend) {
+        if (e < n) {
           const SplatRec R = rec[my_rec];
           const StagedGeo g = stage_geo(R, kbx + 4, kby + 4, tcx, tcy);
           s_geo.store(w, e, g);
           if constexpr (N == 1) {
             if (w == 0) s_tex[e] = one_texel<BF16>(textures, my_rec, rec_base, p.spec);
           }
-          may = idx < wave_last && block_may_contribute(g, bcx, bcy, kbx, kby, p);
+          may = pbase + (uint32_t)e < wave_last &&
+                block_may_contribute(g, bcx, bcy, kbx, kby, p);
         }
         mine = ballot(may);
       }
       if constexpr (MIXED) {
-        const uint32_t idx = pbase + (uint32_t)lane;
-        if (idx < pend) eg = entry_grid<N>(p, my_rec, rec_base);
+        if (lane < n) eg = entry_grid<N>(p, my_rec, rec_base);
       }
       if (lane == 0) s_mask[parity][w] = mine;
       __syncthreads();

@@ -182,6 +182,13 @@ __host__ __device__ constexpr int64_t tiles_at_once(int per_cu) { return 256 * (
 // per lane of each wave, which tests them against its own pixel block.
 constexpr int kPassEntries = 64;
 
+// Entries of the pass over what is left of a list, [b, end) in the forward (from its front) and in
+// the backward (from its end). Pair slots go up to 2^32 - 16: a bound of 64 past a list's end can
+// wrap, so that the passes count entries and compare the lane with the count.
+__host__ __device__ constexpr int pass_size(uint32_t b, uint32_t end, int most) {
+  return end - b < (uint32_t)most ? (int)(end - b) : most;
+}
+
 // The part of a staging pass that every wave works out alike from the waves' votes: `mine` marks
 // the entries that can reach this wave's block, `any` those that can reach some block of the
 // tile. Only the latter are given texel slots, in batches, so that a splat whose screen

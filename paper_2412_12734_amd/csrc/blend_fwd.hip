@@ -157,11 +157,12 @@ blend_fwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
   if (tid < 8 && (tid & 3) >= n_waves) s_mask[tid >> 2][tid & 3] = s_open[tid >> 2][tid & 3] = 0;
 
   // the record of the lane's entry, loaded a pass ahead
-  uint32_t my_rec = start + (uint32_t)lane < end ? pair_vals[start + (uint32_t)lane] : rec_base;
+  uint32_t my_rec = lane < pass_size(start, end, kPassEntries) ? pair_vals[start + (uint32_t)lane]
+                                                               : rec_base;
 
-  for (uint32_t b = start; b < end && !all_done; b += (uint32_t)kPassEntries) {
+  for (uint32_t b = start, n = 0; b < end && !all_done; b += n) {
     // a pass: entries [b, b + n) of the list, one per lane, for the wave's own block
-    const int n = (int)((end - b) < (uint32_t)kPassEntries ? (end - b) : (uint32_t)kPassEntries);
+    n = (uint32_t)pass_size(b, end, kPassEntries);
     if (STATS && tid == 0) atomicAdd(&stats[3], (unsigned long long)n);
     uint64_t mine = 0;
     EntryGrid eg{1, 0.f, 0};
@@ -169,7 +170,7 @@ blend_fwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
     // wave 0 also stores what the blocks share of a splat's geometry
     if (w == 0 || wave_open) {
       bool may = false;
-      if (lane < n) {
+      if (lane < (int)n) {
         const SplatRec R = rec[my_rec];
         const StagedGeo g = stage_geo(R, kbx + 4, kby + 4, tcx, tcy);
         s_geo.store(w, lane, g);
@@ -182,16 +183,13 @@ blend_fwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
       mine = ballot(may);
     }
     if constexpr (MIXED) {
-      if (lane < n) eg = entry_grid<N>(p, my_rec, rec_base);
+      if (lane < (int)n) eg = entry_grid<N>(p, my_rec, rec_base);
     }
     if (lane == 0) s_mask[parity][w] = mine;
     __syncthreads();
     const PassVotes votes =
         pass_votes<false>(mine, s_mask[parity], lane, my_rec, s_list);
-    {
-      const uint32_t next = b + (uint32_t)(kPassEntries + lane);
-      if (next < end) my_rec = pair_vals[next];
-    }
+    if (lane < pass_size(b + n, end, kPassEntries)) my_rec = pair_vals[b + n + (uint32_t)lane];
     parity ^= 1;
 
     uint64_t ahead = ~0ull;  // entries that no batch has taken yet
