@@ -203,7 +203,8 @@ __device__ __forceinline__ SwapSides swap_sides() {
 // entry has an owner in each. The four rows are not summed with each other: each owner lane adds
 // its row's total to the LDS, where the four adds to one address cost less than two more
 // swaps. Written as assembly because the compiler does not form masked DPP adds; the s_nop are
-// the wait states a DPP read needs after a write of its source.
+// the wait states a DPP read needs after a write of its source. Outputs are written before all inputs
+// are read ("+&": no input, not even an equal one, may have an output's register).
 #define GBB_PAIR(A, B, OP, MASK)                                    \
   "v_add_f32_dpp " A ", " A ", " A " " OP " row_mask:0xf bank_mask:0xf\n\t" \
   "v_add_f32_dpp " A ", " B ", " B " " OP " row_mask:0xf bank_mask:" MASK "\n\t"
@@ -224,7 +225,7 @@ __device__ __forceinline__ float row_sums(float (&v)[K]) {
                      GBB_PAIR("%2", "%3", "row_half_mirror", "0xa")
                      GBB_PAIR("%4", "%5", "row_half_mirror", "0xa")
                      "s_nop 1"
-                     : "+v"(v[0]), "+v"(v[2]), "+v"(v[4]), "+v"(v[6]), "+v"(v[8]), "+v"(v[10])
+                     : "+&v"(v[0]), "+&v"(v[2]), "+&v"(v[4]), "+&v"(v[6]), "+&v"(v[8]), "+&v"(v[10])
                      : "v"(v[1]), "v"(v[3]), "v"(v[5]), "v"(v[7]), "v"(v[9]), "v"(v[11]));
     const float x = (b1 ? v[4] : v[0]) + dpp_f<0x4E>(b1 ? v[0] : v[4]);
     const float y = v[8] + dpp_f<0x4E>(v[8]);
@@ -236,7 +237,7 @@ __device__ __forceinline__ float row_sums(float (&v)[K]) {
                      GBB_PAIR("%2", "%5", "row_mirror", "0xc")
                      GBB_PAIR("%0", "%1", "row_half_mirror", "0xa")
                      "s_nop 1"
-                     : "+v"(v[0]), "+v"(v[2]), "+v"(v[4])
+                     : "+&v"(v[0]), "+&v"(v[2]), "+&v"(v[4])
                      : "v"(v[1]), "v"(v[3]), "v"(v[5]));
     const float x = (b1 ? v[4] : v[0]) + dpp_f<0x4E>(b1 ? v[0] : v[4]);
     return x + dpp_f<0xB1>(x);
@@ -246,7 +247,7 @@ __device__ __forceinline__ float row_sums(float (&v)[K]) {
                      "s_nop 1\n\t"
                      GBB_PAIR("%0", "%2", "row_half_mirror", "0xa")
                      "s_nop 1"
-                     : "+v"(v[0])
+                     : "+&v"(v[0])
                      : "v"(v[1]), "v"(v[2]));
     const float x = v[0] + dpp_f<0x4E>(v[0]);
     return x + dpp_f<0xB1>(x);
