@@ -7,7 +7,8 @@ of the depth-prefix pass. Every candidate computes the same image up to float32 
 shape moves the centre the per-pixel solve is re-centred on; batch sizes and the prefix budget
 do not change any arithmetic).
 
-The search is coordinate descent from the library defaults: each knob in turn takes the value
+The search is coordinate descent from the library defaults (batch sizes of 0: the library's choice by
+grid side and number of tiles, which is also a candidate of its own): each knob in turn takes the value
 with the lowest measured cost while the others stay fixed; two sweeps at most. The cost of a
 candidate is the median forward + backward time of a few steps, measured with HIP events on the
 launch stream. Results are cached in a JSON file keyed by the workload class: texture side and
@@ -23,17 +24,17 @@ from typing import Callable, Dict, Iterable, List, Optional, Sequence, Tuple
 
 KNOBS: Dict[str, List] = {
     "tile": [(16, 16), (16, 8), (8, 8)],
-    "batch": [8, 16, 32, 64],
-    "batch_bwd": [8, 16, 32],
+    "batch": [0, 8, 16, 32, 64],
+    "batch_bwd": [0, 8, 16, 32],
     "prefix_pairs_per_tile": [256, 512, 1024, 2048, -1],
     "tile_order": [1, -1],
 }
 
 
 def resolve_defaults(opts, N: int):
-    """The options with explicit values where 0 leaves the choice to the library (batch 8, 16, 32
-    or 64, batch_bwd 8 or 32: its choices on many tiles; prefix budget 1024 pairs per tile, tile
-    order 1), so that search results are explicit."""
+    """The options with explicit values where 0 leaves the choice to the library: prefix budget 1024
+    pairs per tile, tile order 1, and for the batches the explicit sizes nearest to its choices on
+    many tiles (on few tiles it takes others)."""
     return dataclasses.replace(
         opts,
         batch=opts.batch or (4 if N >= 16 else 16 if N >= 8 else 32 if N >= 4 else 64),
@@ -131,7 +132,10 @@ def autotune(splats, views, base=None, cache_path: Optional[str] = None,
     (options, record) where record holds the cost of every candidate measured."""
     from .render import Options
 
-    base = resolve_defaults(base or Options(), splats.N)
+    given = base or Options()
+    base = resolve_defaults(given, splats.N)
+    if splats.N < 16:  # the search starts from the batches that the library would take
+        base = dataclasses.replace(base, batch=given.batch, batch_bwd=given.batch_bwd)
     bf16 = "bfloat16" in str(getattr(splats.textures, "dtype", ""))
     key = workload_key(splats.N, bf16, splats.P, [(v.width, v.height) for v in views])
     cache = {}
@@ -143,7 +147,7 @@ def autotune(splats, views, base=None, cache_path: Optional[str] = None,
         fields["bg"] = tuple(fields["bg"])  # JSON keeps tuples as lists
         return Options(**fields), cache[key]
     cost = cost or gpu_cost(splats, views, steps=steps)
-    if knobs is None and splats.N >= 16:  # the library builds only batches of 4 for N = 16
+    if knobs is None and splats.N >= 16:  # 4 or 0, and both leave N = 16 to the library
         knobs = dict(KNOBS, batch=[4], batch_bwd=[4])
     best, best_cost, log = search(base, cost, knobs)
     record = {"options": dataclasses.asdict(best), "ms": best_cost,
