@@ -792,13 +792,18 @@ static gb_status render_fwd_impl(const gb_splats* s, const gb_view* views, int32
   const int64_t cap_a = pl.rest ? pl.prefix_cap : pl.capacity;
   const bool odd = (radix_passes(pl.tile_bits) & 1) != 0;  // where the sort takes its input
   GBB_TRY(stage_mark(kStDuplicate, 0, hs), "timing");
-  // the duplicate launch also zeroes the tile ranges and, with the split, the open-tile bitmap
+  // the duplicate launch also zeroes the tile ranges and, with the split, the open-tile bitmap and
+  // (where no rest pass follows that would) the rest pass's ranges
   ClearList clear_a;
   clear_a.p[0] = ranges;
   clear_a.n[0] = 2 * pl.total_tiles;
   if (pl.split) {
     clear_a.p[1] = at<uint32_t>(ws, pl.off_open_bits);
     clear_a.n[1] = (pl.total_tiles + 31) / 32;
+    if (!pl.rest) {
+      clear_a.p[2] = at<uint32_t>(ws, pl.off_ranges_rest);
+      clear_a.n[2] = 2 * pl.total_tiles;
+    }
   }
   GBB_TRY(launch_duplicate(order, count, offsets, chunk_owner, rec, d_views, pl.tile_w, pl.tile_h,
                            d_st, cap_a, odd ? pk_a : pk, odd ? pv_a : pv, clear_a, hs),
@@ -817,12 +822,14 @@ static gb_status render_fwd_impl(const gb_splats* s, const gb_view* views, int32
   uint32_t* tile_work = pl.ordered ? at<uint32_t>(ws, pl.off_tile_work) : nullptr;
   if (stats)
     GBB_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(d_stats), 0u, 16, hs), "clear stats");
-  SplitState split{kSinglePass, nullptr, nullptr, nullptr};
-  if (pl.rest) {
-    split.mode = kPrefixPass;
+  SplitState split{kSinglePass, nullptr, nullptr, nullptr, nullptr};
+  if (pl.split) {
+    // (without a rest pass the sections a caller may read back say the same as with an empty one)
+    split.mode = pl.rest ? kPrefixPass : kSinglePass;
     split.open_bits = at<uint32_t>(ws, pl.off_open_bits);
     split.fwd_state = at<float4>(ws, pl.off_fwd_state);
     split.any_open = &d_st->any_open;  // cleared by the count's finalisation
+    split.n_last_rest = at<uint32_t>(ws, pl.off_n_last_rest);
   }
   GBB_TRY(stage_mark(kStBlendFwd, 0, hs), "timing");
   const float4* spec = s->sh ? at<float4>(ws, pl.off_spec) : nullptr;

@@ -293,16 +293,20 @@ blend_fwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
     T_final[pix] = T;
     n_last[pix] = last;
   }
-  if (!REST && split.mode == kPrefixPass) {
-    // a tile with an open pixel takes part in the rest pass
+  if (!REST && split.open_bits) {
+    // a tile with an open pixel takes part in the rest pass, if there is one
     if (tile_open()) {
       if (tid == 0) {
         atomicOr(&split.open_bits[tile >> 5], 1u << (tile & 31));
         atomicOr(split.any_open, 1u);
       }
-      if (inside)
-        split.fwd_state[pix] = make_float4(
-            acc0, acc1, acc2, __builtin_amdgcn_inverse_ballot_w64(open) ? 0.f : 1.f);
+      if (inside) {
+        if (split.mode == kPrefixPass)
+          split.fwd_state[pix] = make_float4(
+              acc0, acc1, acc2, __builtin_amdgcn_inverse_ballot_w64(open) ? 0.f : 1.f);
+        else
+          split.n_last_rest[pix] = 0u;
+      }
     }
   }
   if (STATS) {

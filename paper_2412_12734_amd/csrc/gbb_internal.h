@@ -77,9 +77,11 @@ enum BlendMode : int32_t { kSinglePass = 0, kPrefixPass = 1, kRestPass = 2 };
 
 struct SplitState {
   int32_t mode;
-  uint32_t* open_bits;  // one bit per global tile: set if the prefix left a pixel open
+  uint32_t* open_bits;  // one bit per global tile: set if the first pass left a pixel open (nullable)
   float4* fwd_state;    // per pixel after the prefix: accumulated colour, done flag (0 / 1)
   uint32_t* any_open;   // Status::any_open (prefix pass)
+  // where no rest pass follows (single pass with open_bits): its n_last, zeroed on open tiles
+  uint32_t* n_last_rest;
 };
 
 // The sorted pairs of one pass as the backward reads them.
@@ -207,10 +209,10 @@ hipError_t launch_view_pairs(const uint32_t* count, int64_t P, int n_views,
                              unsigned long long* out, hipStream_t s);
 // Pairs of the first pass: the st->n_sorted slots of the depth order's offsets, expanded in
 // chunks of kChunkSlots (chunk_owner from the offset scan); cap bounds the slot count.
-// Up to two u32 arrays that a duplicate launch also zeroes (p[k] may be null when n[k] = 0).
+// Up to three u32 arrays that a duplicate launch also zeroes (p[k] may be null when n[k] = 0).
 struct ClearList {
-  uint32_t* p[2] = {nullptr, nullptr};
-  int64_t n[2] = {0, 0};
+  uint32_t* p[3] = {nullptr, nullptr, nullptr};
+  int64_t n[3] = {0, 0, 0};
 };
 hipError_t launch_duplicate(const uint32_t* order, const uint32_t* count,
                             const uint32_t* offsets, const uint32_t* chunk_owner,

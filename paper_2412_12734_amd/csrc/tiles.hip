@@ -329,7 +329,7 @@ expand_kernel(const uint32_t* __restrict__ order, const uint32_t* __restrict__ c
   __shared__ int s_wave_max[kDupThreads / 64];
   // arrays the later stages of the pass expect zeroed (the pass's tile ranges, the open-tile
   // bitmap), whatever the pair count, so that they need no launches of their own
-  for (int k = 0; k < 2; ++k) {
+  for (int k = 0; k < 3; ++k) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < clear.n[k];
          i += (int64_t)gridDim.x * blockDim.x)
       clear.p[k][i] = 0u;
