@@ -230,6 +230,27 @@ gather_rows_kernel(RowList list, const uint32_t* __restrict__ map,
   else gather_rows<false>(a, map, j0, rows, N, noise, sigma, inv_shrink);
 }
 
+// Rows too wide for the kernel above, which counts a workgroup's units in 32 bits and would move 64 of
+// such rows one after another: every workgroup takes its share of all values.
+constexpr int32_t kGatherMaxWidth = 1 << 16;
+static_assert((int64_t)kGatherRows * kGatherMaxWidth + kGatherSteps * kGatherThreads < 0x7fffffff,
+              "a workgroup's units fit 32 bits");
+
+__global__ void __launch_bounds__(kGatherThreads)
+gather_wide_rows_kernel(RowArray a, const uint32_t* __restrict__ map,
+                        const uint32_t* __restrict__ d_n, int64_t n_cap) {
+  const int64_t n_new = *d_n < n_cap ? *d_n : n_cap;
+  const int64_t total = n_new * a.width;
+  for (int64_t e = (int64_t)blockIdx.x * kGatherThreads + threadIdx.x; e < total;
+       e += (int64_t)gridDim.x * kGatherThreads) {
+    const int64_t j = e / a.width, c = e - j * a.width;
+    const uint32_t m = map[j];
+    a.dst[e] = a.kind == kRowState && (m >> 30) != kKeep
+                   ? 0.f
+                   : a.src[(int64_t)(m & 0x3FFFFFFFu) * a.width + c];
+  }
+}
+
 unsigned grid1(int64_t n) { return (unsigned)((n + 255) / 256 < 1 ? 1 : (n + 255) / 256); }
 
 }  // namespace
@@ -263,10 +284,22 @@ hipError_t launch_densify_map(int64_t P, const uint32_t* action, const uint32_t*
 hipError_t launch_gather_rows(const uint32_t* map, const uint32_t* d_n, int64_t n_new,
                               const RowList& list, int n_arrays, int N, const float* noise,
                               float sigma, float inv_shrink, hipStream_t s) {
-  if (n_new <= 0 || n_arrays <= 0) return hipSuccess;
+  if (n_new <= 0) return hipSuccess;
+  RowList some;
+  int n_some = 0;
+  for (int i = 0; i < n_arrays; ++i) {
+    if (list.a[i].width <= kGatherMaxWidth) {
+      some.a[n_some++] = list.a[i];
+      continue;
+    }
+    const int64_t blocks = (n_new * list.a[i].width + kGatherThreads - 1) / kGatherThreads;
+    hipLaunchKernelGGL(gather_wide_rows_kernel, dim3((unsigned)(blocks < 8192 ? blocks : 8192)),
+                       dim3(kGatherThreads), 0, s, list.a[i], map, d_n, n_new);
+  }
+  if (n_some == 0) return hipGetLastError();
   const unsigned blocks = (unsigned)((n_new + kGatherRows - 1) / kGatherRows);
-  hipLaunchKernelGGL(gather_rows_kernel, dim3(blocks, (unsigned)n_arrays), dim3(kGatherThreads), 0,
-                     s, list, map, d_n, n_new, N, noise, sigma, inv_shrink);
+  hipLaunchKernelGGL(gather_rows_kernel, dim3(blocks, (unsigned)n_some), dim3(kGatherThreads), 0,
+                     s, some, map, d_n, n_new, N, noise, sigma, inv_shrink);
   return hipGetLastError();
 }
 
