@@ -198,28 +198,39 @@ __device__ __forceinline__ void lds_add(double* array, int base, int offset, flo
 constexpr int kLaneAddMax = 20;
 
 // Splats per batch: the number asked for, by default as many as let all tiles run at once, up to a
-// whole pass; on more tiles fewer, where that lets another workgroup share a CU's 160 KB of LDS.
-// Backward times:
-//  8 x 8 grids hold 2.8 KB per splat (texels and 64-bit sums) beside the pass's geometry: seven
-//  splats and passes of 32 entries (3 KB) are 22.7 KB, seven workgroups. 6 of 64 / 7 of 32 / 8 of
+// whole pass; on more tiles fewer, where that lets another workgroup share a CU's 160 KB of LDS. On
+// numbers of tiles between, where the crowded tiles of an uneven image are what the launch waits for,
+// larger batches stay ahead beyond the tiles that all run at once: they meet fewer flushes.
+// Backward times (of the step when it was 3 to 6 % lighter, but where "now" is said):
+//  8 x 8 grids hold 2.7 KB per splat (texels and 64-bit sums) beside the pass's geometry: seven
+//  splats and passes of 32 entries (3 KB) are 22.4 KB, seven workgroups. 6 of 64 / 7 of 32 / 8 of
 //  64: 1.063 / 1.045 / 1.101 ms at 1M splats and 1080p, 11.4 / 10.8 / 11.9 at 3M splats on four
 //  1080p views, but 324 / 323 / 286 us at 120k small splats on 999 tiles; 8 / 16 / 32 of 64 1.37 /
-//  1.13 / 1.03 ms at 235k splats on 112 tiles.
+//  1.13 / 1.03 ms at 235k splats on 112 tiles. Sides {2, 4, 8}, now, 7 / 8 / 16: 300k splats on 1000
+//  tiles 634 / 563 / 501 us, 100k on 1530 353 / 335 / 373, 300k on 1900 438 / 382 / 443, 500k on 2880
+//  579 / 591 / 734.
 //  4 x 4 grids, 16 / 24 / 32 splats: 16 uneven views of 1M splats 6.22 / 6.25 / 7.54 ms, 47k splats
 //  on three uneven views 0.558 / 0.529 / -, 372k splats on 462 tiles 1.27 / - / 1.09.
+//  2 x 2 grids, now, 8 / 16 / 32 / 64: 300k splats on 1000 tiles 396 / 335 / 295 / 277 us, 300k on
+//  1900 281 / 242 / 219 / 202, 500k on 3600 648 / 610 / 584 / 587.
 //  16 x 16 grids, 1 / 2 / 3 splats: 2.81 / 2.10 / 2.16 ms at 1M splats and 1080p, two in passes of
-//  48 entries (six workgroups per CU instead of five) 1.63. With sides {4, 8, 16} a grid is mostly
-//  smaller than its slot: 2 / 3 / 4 splats 3.88 / 3.11 / 2.59 ms at 202k splats on three views.
+//  48 entries (six workgroups per CU instead of five) 1.63. Now, 2 / 3 / 4: 100k splats on 800 tiles
+//  572 / 490 / 423 us, 300k on 1280 919 / 790 / 670, 100k on 1530 558 / 556 / 550, 300k small ones on
+//  1900 635 / 540 / 590, on 2332 592 / 592 / 624, 300k on 2475 613 / 687 / 755, 500k on 3600 1829 / 2078
+//  / 2293; 4 / 6 or 8 on 475 and 240 tiles 354 / 352 and 724 / 656. Sides {4, 8, 16}: 300k on 1000
+//  tiles 1247 / 1012 / 865, 300k on 1900 860 / 673 / 749, 1M at 1080p 1570 / 1790 / 2033.
 template <int N, bool MIXED>
 int bwd_batch(int asked, int64_t tiles) {
   if (N == 1) return 64;
   if (N == 16)
     return tiles <= tiles_at_once(1) ? 8
            : tiles <= tiles_at_once(2) ? 6
-           : tiles <= tiles_at_once(3) || MIXED ? 4 : 2;
+           : tiles <= tiles_at_once(6) ? 4
+           : tiles <= tiles_at_once(9) ? 3 : 2;
   if (N == 8) {
-    if (asked == 0 && tiles <= tiles_at_once(3)) return tiles <= tiles_at_once(1) ? 32 : 16;
-    return asked > 8 ? asked : tiles <= tiles_at_once(5) ? 8 : 7;
+    if (asked == 0 && tiles <= tiles_at_once(MIXED ? 5 : 3))
+      return tiles <= tiles_at_once(1) ? 32 : 16;
+    return asked > 8 ? asked : tiles <= tiles_at_once(MIXED ? 8 : 5) ? 8 : 7;
   }
   if (N == 4) {
     if (asked == 0 && tiles <= tiles_at_once(2)) return 64;
@@ -675,6 +686,7 @@ hipError_t launch_np(const Plan& pl, const gb_splats& sp, const BlendParams& bp,
   } else {
     switch (batch) {
       GBB_BWD_B(2);
+      GBB_BWD_B(3);
       GBB_BWD_B(4);
       GBB_BWD_B(6);
       GBB_BWD_B(8);

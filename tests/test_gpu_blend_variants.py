@@ -12,8 +12,8 @@ from test_gpu_parity import assert_decreasing_in_buckets, check_grads, gb, gpu_o
 
 pytestmark = pytest.mark.gpu
 
-# 225, 289, 625, 900 and 1517 tiles
-SIZES = [(240, 240), (272, 272), (400, 400), (480, 480), (656, 592)]
+# 225, 289, 625, 900, 1517, 1681 and 2401 tiles
+SIZES = [(240, 240), (272, 272), (400, 400), (480, 480), (656, 592), (656, 656), (784, 784)]
 
 
 def centre(size):
@@ -28,8 +28,8 @@ def test_lists_at_the_edges_of_a_short_pass(gb, N, P):  # noqa: F811
     view = sg.look_at_view((0.0, 0.0, -2.0), *size)
     rast = gb.Rasterizer([view])
     rast.forward(gb.Splats.from_numpy(scene))
-    assert rast.layout.total_tiles == 1517
-    ranges = rast.section("ranges", 2 * 1517).cpu().numpy().reshape(-1, 2)
+    assert rast.layout.total_tiles == 2401
+    ranges = rast.section("ranges", 2 * 2401).cpu().numpy().reshape(-1, 2)
     assert (ranges[:, 1] - ranges[:, 0]).max() == P
     check_grads(gb, scene, view, O.Options(), centre(size), seed=P)
 
