@@ -120,7 +120,6 @@ struct GeoLds {
   float4 g1[B];
   float4 g2[B];
   float4 g0[4][B];
-  static constexpr int kBytesPerSplat = 6 * 16;
 
   __device__ void store(int b, int j, const StagedGeo& g) {
     if (b == 0) {
@@ -498,17 +497,9 @@ __device__ __forceinline__ void grid_coord_n(float u, float scale, int n, int& i
   f = up - (float)i;
 }
 
-// Constants of grid_coord_c for an n-texel side: slope (grid_scale), offset (n - 1) / 2,
-// upper clamp n - 1 and the largest cell index (its int bits in w), staged once per splat so
-// that the per-pixel coordinate costs what the uniform grid's does.
-__device__ __forceinline__ float4 grid_consts(int n, float sigma) {
-  const float hi = (float)(n - 1);
-  const int cmax = n > 2 ? n - 2 : 0;
-  return make_float4(grid_scale(n, sigma), 0.5f * hi, hi, __int_as_float(cmax));
-}
-
-// grid_coord_n from the side's staged constants (the same operations in the same order, so
-// the same results).
+// grid_coord_n from constants of the side, formed once per splat: gc holds the slope (grid_scale),
+// the offset (n - 1) / 2, the upper clamp n - 1 and the largest cell index (its int bits). The same
+// operations in the same order, so the same results.
 __device__ __forceinline__ void grid_coord_c(float u, const float4& gc, int& i, float& f) {
   const float up = fminf(fmaxf(__builtin_fmaf(u, gc.x, gc.y), 0.0f), gc.z);
   const int fi = (int)up;

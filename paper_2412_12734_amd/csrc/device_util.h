@@ -304,10 +304,6 @@ __host__ __device__ constexpr uint64_t row_owners(int K) {
   return m;
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_sum_to_lane63(v)), 63));
-}
-
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) {
   return __uint_as_float(((uint32_t)b) << 16);
 }

@@ -11,7 +11,6 @@
 
 namespace gbb {
 
-constexpr int kWave = 64;
 constexpr uint32_t kCulledKey = 0xFFFFFFFFu;
 constexpr int kRecGrad = 10;  // dh00 dh01 dh10 dh11 dh20 dh21 dh22 dc2x dc2y dopacity
 
