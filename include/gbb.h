@@ -112,19 +112,21 @@ typedef struct {
                          fewer where that lets another workgroup share a CU (12 of 16 for N = 8),
                          and 64 one-texel grids at a time whatever is asked. */
   int32_t batch_bwd;  /* most splats staged in LDS per backward batch: 0 as above, or 8, 16, 32
-                         (N < 16), 4 (N = 16); on many tiles fewer as above (N = 4: 24 of 32;
-                         N = 8: 7 of 8), 64 one-texel grids at a time. */
+                         (N < 16), 4 (N = 16, whose batch the library always chooses: 2 to 8); on
+                         many tiles fewer as above (N = 4: 24 of 32; N = 8: 7 of 8), 64 one-texel
+                         grids at a time. */
   int32_t prefix_pairs_per_tile;
                       /* depth-prefix split. The first pass renders the longest prefix of the
                          depth order whose pairs fit this many pairs per tile (0 = default 1024);
                          a second pass renders the remaining records on the tiles where some
                          pixel is still open (not stopped by t_min). Results are those of one
                          pass over all pairs. -1 = a single pass over all pairs. */
-  int32_t tile_order; /* order in which workgroups take tiles in the blend backward: 0 = default
-                         (1), 1 = most work first (ranked on the device by the pair span each
-                         tile blended in the forward), -1 = fixed bands of neighbouring tiles
-                         per XCD (the forward always uses these). Results are the same either
-                         way, up to the order of the backward's float atomics. */
+  int32_t tile_order; /* order in which workgroups take tiles in the blends: 0 = default (1), 1 =
+                         most work first in the backward (ranked on the device by the pair span
+                         each tile blended in the forward) and, on 769 to 5120 tiles, longest
+                         list first in the forward's first pass; -1, and the forward otherwise =
+                         a fixed order, runs of four neighbouring tiles per XCD. Results are the
+                         same either way, up to the order of the backward's float atomics. */
 } gb_options;
 
 /* Output gradients (device, float32, overwritten -- not accumulated). */
@@ -150,8 +152,8 @@ typedef struct {
   size_t depth_key;   /* uint32[V*P]: float bits of the centre depth, 0xFFFFFFFF if culled */
   size_t tile_count;  /* uint32[V*P]: tiles covered by record v*P+k */
   size_t records;     /* 96-byte record per (view, splat): 19 floats of blend geometry, then
-                         int32 i0 | i1 << 16, int32 j0 | j1 << 16 (inclusive pixel rectangle,
-                         valid if the tile count is > 0), int32 splat, int32 view, pad */
+                         int32 i0 | i1 << 16, int32 j0 | j1 << 16 (inclusive pixel rectangle),
+                         int32 splat, int32 view, pad; written only if the tile count is > 0 */
   size_t order;       /* uint32[V*P]: records sorted by (depth, record index) */
   size_t pair_keys;   /* uint32[]: sorted global tile index of each pair of the first (or only)
                          pass */
@@ -169,7 +171,8 @@ typedef struct {
   size_t open_tiles;        /* uint32[ceil(tiles / 32)]: bit t set if tile t had an open pixel
                                after the first pass */
   size_t tile_order;        /* with work-ordered tiles (else 0): uint32[total tiles], the tile
-                               taken by each workgroup of the backward */
+                               taken by each workgroup of the backward; before it, on 769 to 5120
+                               tiles, that of the forward's first pass */
   size_t tile_work;         /* with work-ordered tiles (else 0): uint32[total tiles], the
                                tile's blended span over both passes (the backward's cost) */
 } gb_layout;

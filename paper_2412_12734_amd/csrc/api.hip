@@ -132,8 +132,8 @@ gb_status make_plan(int32_t P, int32_t N, const gb_view* views, int32_t n_views,
   // 0: the blends choose by the grid's side and the number of tiles (fwd_batch, bwd_batch)
   pl->batch_fwd = o->batch;
   pl->batch_bwd = o->batch_bwd;
-  // N = 16 holds 10.6 KB of texels and sums per splat: batches of 4 are built for it only, and it
-  // only with them
+  // N = 16 holds 10.5 KB of texels and sums per splat: the library always chooses its batches, and
+  // 4 is the only number that can be asked for (and for no other side)
   if (N >= 16 && ((o->batch != 0 && o->batch != 4) || (o->batch_bwd != 0 && o->batch_bwd != 4))) {
     g_last_error = "N = 16 takes batch and batch_bwd 4 (or 0)";
     return GB_ERR_UNSUPPORTED;
@@ -838,10 +838,13 @@ static gb_status render_fwd_impl(const gb_splats* s, const gb_view* views, int32
   float* d_rec = at<float>(ws, pl.off_drec);
   const int64_t rec_n = (int64_t)kRecGrad * pl.VP;
   // With some workgroups per CU the longest lists start first (their lengths bound the blended spans,
-  // which only the backward knows): the launch then ends with short ones. 100k splats on 2500 tiles
-  // 204 -> 177 us, 444k on 4263 of four views 728 -> 546, with 3 us for the order. On more tiles the
-  // fixed order's neighbours in an XCD's L2 are worth more (8160 tiles 370 -> 393, 6172 of 16 x 16
-  // grids 624 -> 661), on fewer nothing waits (64 tiles 42 -> 46 with the launch).
+  // which only the backward knows): the launch then ends with short ones. Fixed against ordered, with 3
+  // us for the order: uneven lists of 100k splats on 1200 tiles 232 / 221 us, on 2500 221 / 191, 300k
+  // on 4320 329 / 295, on 5120 351 / 322, 444k on 4263 of four views 728 / 546. On fewer tiles nothing
+  // waits (810 tiles 279 / 273, 64 tiles 42 / 46). The upper limit is where even images begin to lose,
+  // whose neighbours in an XCD's L2 are worth more: 1M splats on 5610 tiles 315 / 325, on 8160 370 /
+  // 393, 6172 tiles of 16 x 16 grids 624 / 661; uneven ones would gain beyond it (444k on 8000 tiles of
+  // four views 1122 / 947, 300k on 8160 417 / 401), but the host does not know which it has.
   uint32_t* fwd_order = nullptr;
   if (pl.ordered && pl.total_tiles > 3 * 256 && pl.total_tiles <= 20 * 256) {
     fwd_order = at<uint32_t>(ws, pl.off_tile_order);

@@ -478,7 +478,8 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
           // LDS directly; up to kLaneAddMax lanes this costs less than group passes.
           const int base = TEXG * slot;
           if constexpr (N == 1) {
-            float red[3] = {po.wgt * ps.g0, po.wgt * ps.g1, po.wgt * ps.g2};
+            float red[3] = {po.wgt * (act ? ps.g0 : 0.f), po.wgt * (act ? ps.g1 : 0.f),
+                            po.wgt * (act ? ps.g2 : 0.f)};
             const float tot = row_sums(red);
             lds_add<row_owners(3)>(s_gtex, base, place_of(kT3, places), tot);
           } else {
@@ -488,7 +489,7 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
             // of the clamped axis are 0 and 1, the same for the whole group, and only two texels
             // or one take a sum (at 1M splats and 1080p one texel in 25 % of the groups, two in
             // 61 %). The clamped end follows from the cell when the axis has at least two
-            // cells. Other lanes contribute through a zero weight.
+            // cells. Other lanes contribute through a zero adjoint.
             const uint64_t in_u = n_side > 2 ? po.in_u : ~0ull,
                            in_v = n_side > 2 ? po.in_v : ~0ull;
             const int key = act ? po.cell : -1;
@@ -515,36 +516,38 @@ blend_bwd_kernel(const ViewDev* __restrict__ views, const SplatRec* __restrict__
               const int lead = __builtin_amdgcn_readlane(key, (int)__builtin_ctzll(left));
               const uint64_t members = ballot(key == lead);
               left &= ~members;
-              const float wm = __builtin_amdgcn_inverse_ballot_w64(members) ? po.wgt : 0.f;
+              // (adjoints, not weights, are zeroed: one that is not finite stays with its splats)
+              const bool in = __builtin_amdgcn_inverse_ballot_w64(members);
+              const float g0 = in ? ps.g0 : 0.f, g1 = in ? ps.g1 : 0.f, g2 = in ? ps.g2 : 0.f;
               const int lu = cell_row<N>(lead), lv = lead - lu * TexLayout<N>::kRow;
               // the texel row and column of a clamped coordinate
               const int bu = lu == 0 ? 0 : n_side - 1, bv = lv == 0 ? 0 : n_side - 1;
               if ((members & in_v) == 0) {
                 if ((members & in_u) == 0) {
-                  float red[3] = {wm * ps.g0, wm * ps.g1, wm * ps.g2};
+                  float red[3] = {po.wgt * g0, po.wgt * g1, po.wgt * g2};
                   const float tot = row_sums(red);
                   lds_add<row_owners(3)>(s_gtex, base + 3 * (bu * N + bv), place_of(kT3, places), tot);
                 } else {
-                  const float w1 = wm * po.fu, w0 = __builtin_fmaf(-wm, po.fu, wm);
-                  float red[6] = {w0 * ps.g0, w0 * ps.g1, w0 * ps.g2,
-                                  w1 * ps.g0, w1 * ps.g1, w1 * ps.g2};
+                  const float w1 = po.wgt * po.fu, w0 = __builtin_fmaf(-po.wgt, po.fu, po.wgt);
+                  float red[6] = {w0 * g0, w0 * g1, w0 * g2,
+                                  w1 * g0, w1 * g1, w1 * g2};
                   const float tot = row_sums(red);
                   lds_add<row_owners(6)>(s_gtex, base + 3 * (lu * N + bv), place_of(kT6u, places), tot);
                 }
               } else if ((members & in_u) == 0) {
-                const float w1 = wm * po.fv, w0 = __builtin_fmaf(-wm, po.fv, wm);
-                float red[6] = {w0 * ps.g0, w0 * ps.g1, w0 * ps.g2,
-                                w1 * ps.g0, w1 * ps.g1, w1 * ps.g2};
+                const float w1 = po.wgt * po.fv, w0 = __builtin_fmaf(-po.wgt, po.fv, po.wgt);
+                float red[6] = {w0 * g0, w0 * g1, w0 * g2,
+                                w1 * g0, w1 * g1, w1 * g2};
                 const float tot = row_sums(red);
                 lds_add<row_owners(6)>(s_gtex, base + 3 * (bu * N + lv), place_of(kT6v, places), tot);
               } else {
                 float wc[4], red[12];
-                corner_weights(wm, po.fu, po.fv, wc);
+                corner_weights(po.wgt, po.fu, po.fv, wc);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                  red[3 * q] = wc[q] * ps.g0;
-                  red[3 * q + 1] = wc[q] * ps.g1;
-                  red[3 * q + 2] = wc[q] * ps.g2;
+                  red[3 * q] = wc[q] * g0;
+                  red[3 * q + 1] = wc[q] * g1;
+                  red[3 * q + 2] = wc[q] * g2;
                 }
                 const float tot = row_sums(red);
                 lds_add<row_owners(12)>(s_gtex, base + 3 * (lu * N + lv), place_of(kT12, places), tot);

@@ -43,8 +43,11 @@ constexpr int fwd_min_waves() {
 // of geometry. 8 x 8 grids (1.1 KB of texels per splat), when a step still took 0.458 ms at 1M splats
 // and 1080p, there and at 3M splats on four 1080p views: batches of 8 0.482 / 5.26, 12 0.458 / 4.75,
 // 16 0.501 / 5.28; 350k small splats on 135 tiles, 12 / 64: 305 / 229 us. 4 x 4 grids, 372k small
-// splats on 462 tiles, 32 / 64: 437 / 382 us. 16 x 16 grids (4.3 KB) at 1M splats: 2 0.915, 3
-// 0.840, 4 0.854. One-texel grids stage their texels with the geometry, a whole pass at once.
+// splats on 462 tiles, 32 / 64: 437 / 382 us. 2 x 2 grids, 8 / 16 / 32 / 64: 300k splats on 1000
+// tiles 207 / 159 / 136 / 120 us, 500k on 3600 285 / 246 / 227 / 213. 16 x 16 grids (4.3 KB) at 1M
+// splats: 2 0.915, 3 0.840, 4 0.854; 3 / 8 / 16 on 240 tiles 396 / 290 / 264 us, on 475 200 / 151 /
+// 136; 3 / 8 on 1000 tiles 500 / 410, on 1900 427 / 400, on 3600 814 / 972 (8 is not taken beyond 768
+// tiles yet). One-texel grids stage their texels with the geometry, a whole pass at once.
 template <int N>
 int fwd_batch(int asked, int64_t tiles) {
   if (N == 1) return 64;

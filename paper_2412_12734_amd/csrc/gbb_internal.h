@@ -241,8 +241,9 @@ hipError_t launch_duplicate_rest(const uint32_t* order, const uint32_t* count_re
 hipError_t launch_ranges(const uint32_t* pair_keys, const uint32_t* d_n, int64_t n_cap,
                          uint32_t* ranges, hipStream_t s);
 // Work order of the tiles: order[0..n_tiles) is a permutation of the tiles by decreasing
-// cost work[t], or with ranges != null by decreasing length of the tile's list. Costs are compared in buckets (exact below 16, then 1/16 of the cost wide);
-// the order inside a bucket is unspecified. One workgroup; n_tiles <= kMaxOrderedTiles.
+// cost work[t], or with ranges != null by decreasing length of the tile's list. Costs are compared
+// in buckets (exact below 16, then 1/16 of the cost wide); the order inside a bucket is unspecified.
+// One workgroup; n_tiles <= kMaxOrderedTiles.
 constexpr int64_t kMaxOrderedTiles = (int64_t)1 << 20;
 hipError_t launch_order_tiles(const uint32_t* work, const uint32_t* ranges, int64_t n_tiles,
                               uint32_t* order, hipStream_t s);

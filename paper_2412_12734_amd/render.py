@@ -29,8 +29,8 @@ class Options:
     batch_bwd: int = 0
     # depth-prefix split: pairs per tile of the first pass (0 = default), -1 = one pass
     prefix_pairs_per_tile: int = 0
-    # order of the tiles over the blend workgroups: 0 = default, 1 = most work first,
-    # -1 = fixed bands of neighbouring tiles per XCD
+    # order of the tiles over the blend workgroups: 0 = default, 1 = most work first (the forward:
+    # longest lists first, on 769 to 5120 tiles), -1 = fixed runs of neighbouring tiles per XCD
     tile_order: int = 0
 
     def c(self) -> L.GbOptions:
