@@ -26,9 +26,9 @@
 // The record sums (ten lanes, once per step) are 32-bit: their last bits matter (see pixel_step). In
 // 64 bits the step at 1M splats and 1080p took 1.825 ms against 1.834, too little to change them for.
 // What bounds the kernel now is VALU issue where tiles fill the chip, and the latency of a wave's
-// step where a few tiles hold the work. At 1M splats and 1080p 1.35 -> 1.09 ms, 3M splats on
-// four 1080p views 14.5 -> 11.3, 16 uneven views with 4 x 4 grids 8.28 -> 6.8, 16 x 16 grids 2.33 ->
-// 1.69, sides {2, 4, 8} 1.53 -> 1.19, 100k splats at 800 x 800 0.73 -> 0.56. (With the texels
+// step where a few tiles hold the work. At 1M splats and 1080p 1.35 -> 1.10 ms, 3M splats on
+// four 1080p views 14.5 -> 11.3, 16 uneven views with 4 x 4 grids 8.28 -> 6.9, 16 x 16 grids 2.33 ->
+// 1.68, sides {2, 4, 8} 1.53 -> 1.20, 100k splats at 800 x 800 0.73 -> 0.55. (With the texels
 // projected on the pixel's adjoint before the interpolation, one scalar for the colour behind and d c2
 // formed once per batch the step took 3 to 4 % less, but its gradients had other last bits.)
 #include "blend_common.h"
