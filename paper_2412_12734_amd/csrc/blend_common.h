@@ -207,7 +207,8 @@ struct PassVotes {
 };
 
 template <bool REVERSE, int PE>
-__device__ __forceinline__ PassVotes pass_votes(uint64_t mine, const uint64_t* s_mask, int lane, uint32_t my_rec, SlotList<PE>& list) {
+__device__ __forceinline__ PassVotes pass_votes(uint64_t mine, const uint64_t* s_mask, int lane,
+                                                uint32_t my_rec, SlotList<PE>& list) {
   PassVotes v;
   v.mine = mine;
   v.any = uniform64((s_mask[0] | s_mask[1]) | (s_mask[2] | s_mask[3]));
